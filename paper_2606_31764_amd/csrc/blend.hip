@@ -327,29 +327,38 @@ struct FwdRec {
                       // converted: the bits of the axis ratio r)
 };
 constexpr int FWD_ENTRY_BYTES = sizeof(FwdRec) + 16;
-constexpr int BWD_ENTRY_BYTES = 48;   // geometry, opacity + colour, (g, curve, position, 1/sigma^3)
+// An adjoint entry: geometry (centre, squared support radius, exp2
+// coefficient), (g, or ~g for fills, list position, opacity bits, 1/sigma^3
+// bits), and the colour with the curve's bits.
+constexpr int BWD_ENTRY_BYTES = 48;
 // The adjoint parks the per-lane gradient values it still has to sum over
-// the wavefront in LDS rows of 64 floats, one row per value (three for a
-// stroke Gaussian, one for a fill Gaussian), each with its (Gaussian, value
-// index) target, and sums park_rows rows at a time (see flush_rows).  Rows
-// are padded to 68 floats so that the flush's reads fall into different
-// banks.  One-pixel-per-lane adjoints at depth 64 park 12 rows, which keeps a
-// wavefront's LDS slice small enough for six wavefronts per SIMD; the others
-// (held to fewer wavefronts by their registers) park 16.
+// the wavefront in LDS rows of 64 floats and sums 16 rows at a time
+// (flush_moments, flush_triples, flush_rows): one row for a stroke or fill entry at
+// one pixel per lane, three at 2 x 2 or of a very long curve (LONG_TAUS), five
+// for a tangent-aligned one.  Rows are padded
+// to 68 floats so that the 16-byte reads of 8 rows fall into different banks.
+constexpr int RB = 16;      // parked rows
 constexpr int RB_ROW = 68;  // floats per parked row
-__host__ __device__ constexpr bool bwd_six_waves(int tile, int E, int kind) {
-  return tile <= 16 && E == 1 && !(kind & KIND_FILL);
-}
-__host__ __device__ constexpr int park_rows(int tile, int E, int kind) { return bwd_six_waves(tile, E, kind) ? 12 : 16; }
-// wavefronts per SIMD the adjoint is built for: six without the fill-run
-// walk at one pixel per lane and one entry per lane, four with it (or at
-// several pixels per lane), one at several entries per lane
+// wavefronts per SIMD the adjoint is built for: five without the fill-run
+// walk at one pixel per lane and one entry per lane (their LDS slices, 7.6 KB
+// each, fill the CU), four with it (or at several pixels per lane), one at
+// several entries per lane
 __host__ __device__ constexpr int bwd_waves(int tile, int E, int kind) {
-  return bwd_six_waves(tile, E, kind) ? 6 : (E == 1 ? 4 : 1);
+  return tile <= 16 && E == 1 && !(kind & KIND_FILL) ? 5 : (E == 1 ? 4 : 1);
 }
-__host__ __device__ constexpr size_t bwd_wave_bytes(int tile, int E, int kind) {
-  return ((size_t)64 * E * BWD_ENTRY_BYTES + (size_t)park_rows(tile, E, kind) * (RB_ROW * 4 + 8) + 15) / 16 * 16;
+__host__ __device__ constexpr size_t bwd_wave_bytes(int E) {
+  return (size_t)64 * E * BWD_ENTRY_BYTES + (size_t)RB * (RB_ROW * 4 + 8);
 }
+// Stroke curves of more knot intervals than this keep their per-pixel FP32
+// terms and the order of their sums (three parked rows per entry, flush_rows)
+// instead of the moments of flush_moments: their knot-interval gradients are
+// suffix sums over thousands of samples that nearly cancel, so any other order
+// moves them by that many roundings.  The moments (FP64 sums) agree with them
+// within 3e-6 at 2,000 intervals and are nearer to the exact values, but at
+// 10,240 they differ by 1.2e-5 to 2.0e-5, where a change of version should not.
+constexpr int LONG_TAUS = 6000;
+// the flush's basis table (one per block): four functions of the 64 lanes
+constexpr int BASIS_BYTES = 4 * RB_ROW * 4;
 
 // Lower end of the step that starts at list position h (walking down from
 // the list end): at most `depth` entries, not below `start`, and not across
@@ -907,10 +916,8 @@ __device__ inline void flush_curve(double* gcurve, int c, double& tot) {
 // Sums the first n (<= RB) parked rows over the 64 lanes and adds each total
 // to its target ggrad[g * GG + value] (tgt[row] = (g, value)).  Lane (r, part)
 // = (lane / 4, lane % 4) adds up floats part, part + 4, ..., part + 60 of row
-// r (lanes of rows past RB add nothing); two DPP row shifts finish the sum in
-// the quad's last lane, which issues the atomic.  Every lane of the wavefront
-// must call it.
-template <int RB>
+// r; two DPP row shifts finish the sum in the quad's last lane, which issues
+// the atomic.  Every lane of the wavefront must call it.
 __device__ inline void flush_rows(const float* park, const int2* tgt, int n, float* __restrict__ ggrad) {
   static_assert(RB <= 16, "four lanes per parked row");
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -919,15 +926,125 @@ __device__ inline void flush_rows(const float* park, const int2* tgt, int n, flo
   const int lane = __lane_id(), r = lane >> 2, part = lane & 3;
   const float* row = park + r * RB_ROW + part;
   float t = 0.0f;
-  if (r < RB) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) t += row[4 * j];
-  }
+  for (int j = 0; j < 16; ++j) t += row[4 * j];
   t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x111, 0xf, 0xf, true));  // row_shr:1
   t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x112, 0xf, 0xf, true));  // row_shr:2
   if (part == 3 && r < n && t != 0.0f) {
     const int2 tg = tgt[r];
     unsafeAtomicAdd(ggrad + (int64_t)tg.x * GG + tg.y, t);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Basis table of flush_moments: function f of lane p at table[f * RB_ROW + p]:
+// 1, x, y, x^2 + y^2 with (x, y) = (p & 7, p >> 3) - 3.5, the lane's pixel
+// relative to the middle of its 8 x 8 block.  One thread per entry.
+__device__ inline void basis_table(float* table) {
+  static_assert(BLOCK == 256, "one thread per basis value");
+  const int f = threadIdx.x >> 6, p = threadIdx.x & 63;
+  const float x = (float)(p & 7) - 3.5f, y = (float)(p >> 3) - 3.5f;
+  table[f * RB_ROW + p] = f == 0 ? 1.0f : (f == 1 ? x : (f == 2 ? y : x * x + y * y));
+}
+
+// Lane 4 (l / 4) + Q's value of v (quad_perm broadcast).
+template <int Q>
+__device__ inline double quad_bcast(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  constexpr int ctrl = Q * 0x55;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, ctrl, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), ctrl, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Per-Gaussian gradients of up to RB entries (e0 .. e0 + n - 1 of the
+// wavefront's LDS arrays) of a block with one pixel per lane, from their
+// parked rows: row i holds, per lane, entry e0 + i's v = dL/dalpha G.  Every
+// gradient of an isotropic Gaussian is a fixed combination of four sums over
+// the pixels, sum v {1, x, y, x^2 + y^2} (x, y relative to the block's middle
+// (mx, my)):
+//   dL/dmu    = -2 ln2 a o  sum v (x - mu),     a the exp2 coefficient
+//   dL/dsigma = o / sigma^3 sum v |x - mu|^2
+//   dL/do_j   = sum v (fills)
+// so the rows contract with the 64 x 4 basis, 16 rows at a time, on the matrix
+// cores: v_mfma_f64_4x4x4, whose four blocks take four rows each.  Lane l holds
+// row l & 15 in A and function l & 3 in B at pixels 16 (l >> 4) + t for step t,
+// and receives function l & 3 of row 4 ((l >> 2) & 3) + (l >> 4); quad
+// broadcasts give it all four sums of that row, of which it forms gradient
+// value l & 3, and one atomic instruction adds them all.  An entry's lanes only form v and store it, where they formed and
+// stored dL/dmu and dL/dsigma each before (adjoint of 16 closed strokes at
+// 512^2 0.132 -> 0.076 ms, of 16 x 2000 key points at 1024^2 0.940 -> 0.705 ms).
+// In FP64, because moving the sums to the Gaussian's centre cancels: in FP32
+// (0.076, 0.726 ms, v_mfma_f32_16x16x4) the knot-interval gradients of long splines, themselves
+// sums that cancel, were ten times further from the exact ones.  Every lane of
+// the wavefront must call it.
+__device__ inline void flush_moments(const float* park, const float* basis, const float4* geo, const int4* meta,
+                                     int e0, int n, float mx, float my, float* __restrict__ ggrad) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int lane = __lane_id();
+  const f4* ap = (const f4*)(park + (lane & 15) * RB_ROW + 16 * (lane >> 4));
+  const f4* bp = (const f4*)(basis + (lane & 3) * RB_ROW + 16 * (lane >> 4));
+  double m = 0.0;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const f4 a = ap[s], b = bp[s];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      m = __builtin_amdgcn_mfma_f64_4x4x4f64((double)a[t], (double)b[t], m, 0, 0, 0);
+  }
+  const int e = 4 * ((lane >> 2) & 3) + (lane >> 4), val = lane & 3;
+  const bool ok = e < n;
+  const float4 gm = geo[e0 + (ok ? e : 0)];
+  const int4 mt = meta[e0 + (ok ? e : 0)];
+  const double M0 = quad_bcast<0>(m), Mx = quad_bcast<1>(m), My = quad_bcast<2>(m), Mr = quad_bcast<3>(m);
+  const double cx = (double)gm.x - (double)mx, cy = (double)gm.y - (double)my;
+  const double Ax = __builtin_fma(-cx, M0, Mx), Ay = __builtin_fma(-cy, M0, My);
+  const double Ar = __builtin_fma(-cy, My + Ay, __builtin_fma(-cx, Mx + Ax, Mr));
+  const float op = __int_as_float(mt.z);
+  const float k1 = -2.0f * (float)LN2 * gm.w * op, k2 = op * __int_as_float(mt.w);
+  const double A = val == 0 ? Ax : (val == 1 ? Ay : Ar);
+  const float v = mt.x < 0 ? (float)M0 : (val == 2 ? k2 : k1) * (float)A;
+  // strokes take values 0..2, fills value 3
+  if (ok && ((val == 3) == (mt.x < 0)) && v != 0.0f)
+    unsafeAtomicAdd(ggrad + (int64_t)(mt.x < 0 ? ~mt.x : mt.x) * GG + val, v);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same for up to RB / 3 entries of a block with 2 x 2 pixels per lane,
+// whose lanes park three rows per entry: sum v dx, sum v dy and sum v |d|^2
+// over their pixels (a fill entry: sum v first), formed from the in-lane sums
+// of v, which is cheaper there than four rows of v (batches of 16 scenes:
+// adjoint 1.746 ms with four rows, 1.381 ms with three).  Summed as in
+// flush_rows.  Every lane of the wavefront must call it.
+__device__ inline void flush_triples(const float* park, const float4* geo, const int4* meta, int e0, int n,
+                                     float* __restrict__ ggrad) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int lane = __lane_id(), r = lane >> 2, part = lane & 3;
+  const float* row = park + r * RB_ROW + part;
+  float t = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) t += row[4 * j];
+  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x111, 0xf, 0xf, true));  // row_shr:1
+  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x112, 0xf, 0xf, true));  // row_shr:2
+  if (part == 3 && r < 3 * n) {
+    const int e = (r * 11) >> 5, val = r - 3 * e;  // r / 3, r % 3 below 16
+    const int4 mt = meta[e0 + e];
+    if (mt.x < 0) {
+      if (val == 0 && t != 0.0f) unsafeAtomicAdd(ggrad + (int64_t)~mt.x * GG + 3, t);
+    } else {
+      const float op = __int_as_float(mt.z);
+      const float v = t * (val == 2 ? op * __int_as_float(mt.w) : -2.0f * (float)LN2 * geo[e0 + e].w * op);
+      if (v != 0.0f) unsafeAtomicAdd(ggrad + (int64_t)mt.x * GG + val, v);
+    }
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -980,16 +1097,19 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
   const bool fill_h1 = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
   const float inv_tile = 1.0f / (float)TILE;
   const int lane = __lane_id(), wv = threadIdx.x >> 6;
-  constexpr int RB = park_rows(TILE, E, KIND);
-  char* mine_lds = smem + (size_t)wv * bwd_wave_bytes(TILE, E, KIND);
+  float* basis = (float*)smem;  // (shared by the block's wavefronts)
+  basis_table(basis);
+  __syncthreads();
+  char* mine_lds = smem + BASIS_BYTES + (size_t)wv * bwd_wave_bytes(E);
   float4* wgeo = (float4*)mine_lds;
-  float4* wpc = wgeo + 64 * E;
-  int4* wmeta = (int4*)(wpc + 64 * E);  // (g, or ~g for fills), curve, list position, 1/sigma^3 bits
-  float* park = (float*)(wmeta + 64 * E);  // [RB][RB_ROW] parked gradient values
-  int2* ptgt = (int2*)(park + RB * RB_ROW);  // [RB] their (Gaussian, value index) targets
-  int n_rows = 0;                          // parked rows (wavefront-uniform)
+  int4* wmeta = (int4*)(wgeo + 64 * E);  // (g, or ~g for fills), list position, opacity bits, 1/sigma^3 bits
+  float4* wpc = (float4*)(wmeta + 64 * E);  // colour, curve bits
+  float* park = (float*)(wpc + 64 * E);  // [RB][RB_ROW] parked gradient values
+  int2* ptgt = (int2*)(park + RB * RB_ROW);  // [RB] targets of flush_rows
   const uint64_t below = lanes_below();
   float* __restrict__ ggrad = w.ggrad;
+  const const_i32 taus = (const_i32)cv.tau_off;
+  const bool any_long = cv.n_taus > LONG_TAUS;
   const const_i32 item_off = (const_i32)w.item_off;  // not written during the kernel: scalar loads
   const int n_items = item_off[n_tiles];
   for (int it = 0;; ++it) {
@@ -1068,7 +1188,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
     const int lo = max(wave_min(my_lo), c_lo);
     if (c_hi <= lo) return;
     int cur = -1, since = 0;
-    bool cur_fill = false, cur_aniso = false;
+    bool cur_fill = false, cur_aniso = false, cur_long = false;
     // per pixel: K of the current curve, W (fixed over a run of one curve),
     // and the run's sum of alpha T (the curve's colour gradient is dL/dI_c
     // times it)
@@ -1079,6 +1199,13 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
       if (cur < 0) return;
       fold_curve<C, PPT>(cur_fill, gI, aT, accO, ctot);
       flush_curve<C>(w.gcurve, cur, ctot);
+    };
+    // the parked rows of the n entries before entry j
+    auto flush_pending = [&](int j, int n) {
+      if constexpr (PPT == 1)
+        flush_moments(park, basis, wgeo, wmeta, j - n, n, (float)qx + 3.5f, (float)qy + 3.5f, ggrad);
+      else
+        flush_triples(park, wgeo, wmeta, j - n, n, ggrad);
     };
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
@@ -1109,10 +1236,6 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
       constexpr int NS = FR_NS;                // LDS row stride (conflict-free rows)
       float* ol = (float*)mine_lds;  // [NB][NS] opacities (0: no Gaussian at p0 .. p1 there)
       float* gl = park;              // [NB][NS] dL/do_j
-      if (n_rows > 0) {
-        flush_rows<RB>(park, ptgt, n_rows, ggrad);
-        n_rows = 0;
-      }
       if (cur != fr.c) {  // a new curve: close the previous one, W for the new K
         close_curve();
         const float4 pc = w.gcol[fr.g_top];
@@ -1282,8 +1405,9 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           // tangent-aligned entries: -1 (negative: the kind) in place of 1 / sigma^3
           const float wbits = (ANI && e[u].kind == 2) ? -1.0f : (float)(1.0 / (sg * sg * sg));
           wgeo[dst] = geo;
-          wpc[dst] = make_float4(e[u].r.opacity, e[u].c0, e[u].c1, e[u].c2);
-          wmeta[dst] = make_int4(e[u].kind == 1 ? ~e[u].g : e[u].g, e[u].r.curve, mypos, __float_as_int(wbits));
+          wmeta[dst] = make_int4(e[u].kind == 1 ? ~e[u].g : e[u].g, mypos, __float_as_int(e[u].r.opacity),
+                                 __float_as_int(wbits));
+          wpc[dst] = make_float4(e[u].c0, e[u].c1, e[u].c2, __int_as_float(e[u].r.curve));
         }
         cnt += __popcll(m);
       }
@@ -1319,10 +1443,10 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
 #pragma unroll
       for (int g = 0; g < E; ++g) {
         const int i = 64 * g + lane;
-        const int prev = i == 0 ? cur : wmeta[i > 0 ? i - 1 : 0].y;
-        rs[g] = __ballot(i < cnt && wmeta[i < cnt ? i : 0].y != prev);
+        const int prev = i == 0 ? cur : __float_as_int(wpc[i > 0 ? i - 1 : 0].w);
+        rs[g] = __ballot(i < cnt && __float_as_int(wpc[i < cnt ? i : 0].w) != prev);
       }
-      const float* wop = (const float*)wpc;  // opacities
+      int n_ent = 0;  // entries with parked rows: the n_ent before j (wavefront-uniform)
       for (int j = 0; j < cnt;) {
         // this segment: j up to the next run start (or the step's end)
         int jend = cnt;
@@ -1336,7 +1460,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           close_curve();
           const int4 mt = wmeta[j];
           const float4 pc = wpc[j];
-          const float col[3] = {pc.y, pc.z, pc.w};
+          const float col[3] = {pc.x, pc.y, pc.z};
 #pragma unroll
           for (int q = 0; q < PPT; ++q) {
             float K = 0.0f;
@@ -1346,9 +1470,10 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             Wc[q] = __builtin_fmaf(-K, T[q], __builtin_fmaf(Kc[q], T[q], Wc[q]));
             Kc[q] = K;
           }
-          cur = __builtin_amdgcn_readfirstlane(mt.y);
+          cur = __builtin_amdgcn_readfirstlane(__float_as_int(pc.w));
           cur_fill = __builtin_amdgcn_readfirstlane(mt.x) < 0;
           cur_aniso = ANI && !cur_fill && __builtin_amdgcn_readfirstlane(mt.w) < 0;
+          cur_long = any_long && !cur_fill && taus[cur + 1] - taus[cur] > LONG_TAUS;
           since = 0;
         }
         if (ANI && cur_aniso) {
@@ -1359,6 +1484,9 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           // rewritten in a, b).
           const float lim = ANI_CK * ks * ks;
           const float two_ln2 = 2.0f * ln2;
+          if (n_ent > 0) flush_pending(j, n_ent);  // the rows are shared
+          n_ent = 0;
+          int n_rows = 0;
           for (; j < jend; ++j) {
             if (since >= FLUSH) {
               fold_curve<C, PPT>(false, gI, aT, accO, ctot);
@@ -1366,8 +1494,8 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             }
             ++since;
             const float4 gm = wgeo[j];
-            const float op = wop[4 * j];
             const int4 mt = wmeta[j];
+            const float op = __int_as_float(mt.z);
             const float rq = -__int_as_float(mt.w);
             const float isg = __builtin_sqrtf(__builtin_fmaf(gm.z, gm.z, gm.w * gm.w)) * (1.0f / ANI_SQRT_CK);
             const float isp = isg * rq;           // 1 / sp
@@ -1381,7 +1509,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
               const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
               const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
               const float m = __builtin_fmaf(a, a, b * b);
-              const bool in = (mt.z >= stop[q]) && (m <= lim);
+              const bool in = (mt.y >= stop[q]) && (m <= lim);
               act = act || in;
               const float G = __builtin_amdgcn_exp2f(-m);
               const float oG = op * G;
@@ -1401,7 +1529,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             }
             if (__ballot(act) == 0ull) continue;
             if (n_rows + 5 > RB) {
-              flush_rows<RB>(park, ptgt, n_rows, ggrad);
+              flush_rows(park, ptgt, n_rows, ggrad);
               n_rows = 0;
             }
             accO += v[5];
@@ -1410,66 +1538,13 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             if (lane < 5) ptgt[n_rows + lane] = make_int2(mt.x, lane);
             n_rows = __builtin_amdgcn_readfirstlane(n_rows + 5);
           }
-        } else if (cur_fill) {
-          // fill Gaussians: one value each (dL/do_j), parked in one row;
-          // entries are evaluated two at a time (independent work of the
-          // pair overlaps) and parked in order
-          auto fill_eval = [&](int jj, float& v3, bool& act, int& gneg) {
-            const float4 gm = wgeo[jj];
-            const float op = wop[4 * jj];
-            const int4 mt = wmeta[jj];
-            gneg = mt.x;
-            v3 = 0.0f;
-            act = false;
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-              const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-              const float d2 = __builtin_fmaf(dx, dx, dy * dy);
-              const bool in = (mt.z >= stop[q]) && (d2 <= gm.z);
-              act = act || in;
-              const float G = __builtin_amdgcn_exp2f(gm.w * d2);
-              const float oG = op * G;
-              const bool lt = oG < amax;
-              const float alpha = in ? fminf(oG, amax) : 0.0f;  // = lt ? oG : amax
-              const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
-              // dL/dalpha = (T' K - B) / (1 - alpha) = -W / (1 - alpha)
-              const float dLda = (in && lt) ? -Wc[q] * r : 0.0f;
-              T[q] = in ? T[q] * r : T[q];  // the transmittance in front of the entry
-              aT[q] = __builtin_fmaf(alpha, T[q], aT[q]);
-              v3 = __builtin_fmaf(dLda, G, v3);  // dL/do_j
-            }
-          };
-          auto fill_park = [&](float v3, bool act, int gneg) {
-            if (__ballot(act) == 0ull) return;
-            if (n_rows + 1 > RB) {
-              flush_rows<RB>(park, ptgt, n_rows, ggrad);
-              n_rows = 0;
-            }
-            park[n_rows * RB_ROW + lane] = v3;
-            if (lane == 0) ptgt[n_rows] = make_int2(~gneg, 3);
-            n_rows = __builtin_amdgcn_readfirstlane(n_rows + 1);
-          };
-          for (; j + 1 < jend; j += 2) {
-            float va, vb;
-            bool aa, ab;
-            int ga, gb;
-            fill_eval(j, va, aa, ga);
-            fill_eval(j + 1, vb, ab, gb);
-            fill_park(va, aa, ga);
-            fill_park(vb, ab, gb);
-          }
-          if (j < jend) {
-            float va;
-            bool aa;
-            int ga;
-            fill_eval(j, va, aa, ga);
-            fill_park(va, aa, ga);
-            ++j;
-          }
-        } else {
-          // stroke Gaussians: dL/dmu (2) and dL/dsigma parked in three rows;
-          // dL/do_j summed per lane into the curve's opacity gradient, which
-          // is folded into FP64 every FLUSH entries to keep that FP32 sum short
+          if (n_rows > 0) flush_rows(park, ptgt, n_rows, ggrad);
+        } else if (cur_long) {
+          // stroke Gaussians of very long curves (LONG_TAUS): dL/dmu (2) and
+          // dL/dsigma formed per pixel and parked in three rows
+          if (n_ent > 0) flush_pending(j, n_ent);  // the rows are shared
+          n_ent = 0;
+          int n_rows = 0;
           for (; j < jend; ++j) {
             if (since >= FLUSH) {
               fold_curve<C, PPT>(false, gI, aT, accO, ctot);
@@ -1477,8 +1552,8 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             }
             ++since;
             const float4 gm = wgeo[j];
-            const float op = wop[4 * j];
             const int4 mt = wmeta[j];
+            const float op = __int_as_float(mt.z);
             const float is3 = __int_as_float(mt.w);
             float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             bool act = false;
@@ -1486,7 +1561,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             for (int q = 0; q < PPT; ++q) {
               const float dx = px[q] - gm.x, dy = py[q] - gm.y;
               const float d2 = __builtin_fmaf(dx, dx, dy * dy);
-              const bool in = (mt.z >= stop[q]) && (d2 <= gm.z);
+              const bool in = (mt.y >= stop[q]) && (d2 <= gm.z);
               act = act || in;
               const float G = __builtin_amdgcn_exp2f(gm.w * d2);
               const float oG = op * G;
@@ -1494,7 +1569,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
               const float alpha = in ? fminf(oG, amax) : 0.0f;  // = lt ? oG : amax
               const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
               const float dLda = (in && lt) ? -Wc[q] * r : 0.0f;
-              T[q] = in ? T[q] * r : T[q];
+              T[q] *= r;
               aT[q] = __builtin_fmaf(alpha, T[q], aT[q]);
               v[3] = __builtin_fmaf(dLda, G, v[3]);  // dL/do_j
               const float dG = dLda * op;
@@ -1505,7 +1580,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             }
             if (__ballot(act) == 0ull) continue;
             if (n_rows + 3 > RB) {
-              flush_rows<RB>(park, ptgt, n_rows, ggrad);
+              flush_rows(park, ptgt, n_rows, ggrad);
               n_rows = 0;
             }
             accO += v[3];
@@ -1514,15 +1589,75 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             if (lane < 3) ptgt[n_rows + lane] = make_int2(mt.x, lane);
             n_rows = __builtin_amdgcn_readfirstlane(n_rows + 3);
           }
+          if (n_rows > 0) flush_rows(park, ptgt, n_rows, ggrad);
+        } else {
+          // stroke and fill Gaussians: v = dL/dalpha G per pixel, parked (a
+          // stroke's also summed per lane into the curve's opacity gradient,
+          // which is folded into FP64 every FLUSH entries to keep that FP32
+          // sum short).  An entry that does not reach a pixel, or lies in
+          // front of its stop, composites there with G = 0: alpha 0, r exactly
+          // 1, T unchanged.
+          auto eval = [&](int jj, int ent) {
+            const float4 gm = wgeo[jj];
+            const int4 mt = wmeta[jj];
+            const float op = __int_as_float(mt.z);
+            float v[PPT];
+#pragma unroll
+            for (int q = 0; q < PPT; ++q) {
+              const float dx = px[q] - gm.x, dy = py[q] - gm.y;
+              const float d2 = __builtin_fmaf(dx, dx, dy * dy);
+              const bool in = (mt.y >= stop[q]) && (d2 <= gm.z);
+              const float G = in ? __builtin_amdgcn_exp2f(gm.w * d2) : 0.0f;
+              const float oG = op * G;
+              const bool lt = oG < amax;
+              const float alpha = fminf(oG, amax);  // lt ? oG : amax, also for a NaN oG
+              const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
+              T[q] *= r;  // the transmittance in front of the entry
+              aT[q] = __builtin_fmaf(alpha, T[q], aT[q]);
+              // dL/dalpha = (T' K - B) / (1 - alpha) = -W / (1 - alpha)
+              v[q] = (in && lt) ? -Wc[q] * r * G : 0.0f;
+            }
+            if constexpr (PPT == 1) {
+              accO += v[0];
+              park[ent * RB_ROW + lane] = v[0];
+            } else {
+              // sums over the lane's 2 x 2 pixels of v {1, ox, oy}, ox and oy
+              // the pixel's offset (0 or 1) from the first
+              const float m1 = v[1] + v[3], m2 = v[2] + v[3], m0 = (v[0] + v[1]) + (v[2] + v[3]);
+              const float dx = px[0] - gm.x, dy = py[0] - gm.y;
+              const float sx = __builtin_fmaf(dx, m0, m1), sy = __builtin_fmaf(dy, m0, m2);
+              // sum v |d + offset|^2 (ox^2 = ox, oy^2 = oy)
+              const float sr = __builtin_fmaf(dx, sx + m1, __builtin_fmaf(dy, sy + m2, m1 + m2));
+              accO += m0;
+              float* row = park + 3 * ent * RB_ROW + lane;
+              row[0] = cur_fill ? m0 : sx;
+              row[RB_ROW] = sy;
+              row[2 * RB_ROW] = sr;
+            }
+          };
+          constexpr int EPF = PPT == 1 ? RB : RB / 3;  // entries per flush
+          while (j < jend) {
+            const int m = min(jend - j, EPF - n_ent);
+            if (!cur_fill && since + m > FLUSH) {
+              fold_curve<C, PPT>(false, gI, aT, accO, ctot);
+              since = 0;
+            }
+            since += m;
+#pragma unroll 4
+            for (int i = 0; i < m; ++i) eval(j + i, n_ent + i);
+            j += m;
+            n_ent += m;
+            if (n_ent == EPF) {
+              flush_pending(j, n_ent);
+              n_ent = 0;
+            }
+          }
         }
       }
+      if (n_ent > 0) flush_pending(cnt, n_ent);
       __builtin_amdgcn_wave_barrier();
       s_lo = n_lo;
       s_hi = n_hi;
-    }
-    if (n_rows > 0) {
-      flush_rows<RB>(park, ptgt, n_rows, ggrad);
-      n_rows = 0;
     }
     close_curve();
     };
@@ -1575,7 +1710,7 @@ hipError_t bwd_t(const Launch& L, const float* dL, const float* T_final, const i
   const int64_t max_items =
       (int64_t)adj_blocks(TILE, (KIND & KIND_FILL) != 0) * ((L.bf->caps.pairs >> (L.ck_lg >= 0 ? L.ck_lg : 9)) +
                                                              L.n_tiles);
-  const size_t lds = (size_t)WPB * bwd_wave_bytes(TILE, E, KIND);
+  const size_t lds = (size_t)WPB * bwd_wave_bytes(E) + BASIS_BYTES;
   int grid = (int)((max_items + WPB - 1) / WPB);
   if (persistent) {
     grid = resident_grid(k_blend_bwd<C, TILE, E, KIND>, grid, L.n_cu, lds);

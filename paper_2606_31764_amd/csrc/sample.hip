@@ -23,6 +23,9 @@ namespace {
 
 constexpr int PREP_THREADS = 256;  // k_boundary, and k_curve_prep for many curves
 constexpr int PREP_KNOTS = 4096;  // knots held in LDS by k_curve_prep (32 KB)
+// knots up to which one thread sums the intervals: it takes about 17 ns per
+// knot, the parallel sum's extra block barriers about 2 us
+constexpr int SHORT_KNOTS = 128;
 
 __global__ void k_scene_setup(nsplat_scenes sc, nsplat_params pr, SceneTab* st, int32_t* clear_counters) {
   if (clear_counters && blockIdx.x == 0)
@@ -105,6 +108,29 @@ __device__ inline bool curve_values_ok(const nsplat_curves& cv, const CurveView&
   return !bad && pos;
 }
 
+// Exclusive prefix sum of v over the block's threads; *total their sum.
+template <int THREADS>
+__device__ inline double block_excl_scan_f64(double v, double* red, double* total) {
+  const int lane = __lane_id(), wid = threadIdx.x >> 6;
+  double incl = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const double o = __shfl_up(incl, off);
+    if (lane >= off) incl += o;
+  }
+  if (lane == 63) red[wid] = incl;
+  __syncthreads();
+  double base = 0.0, tot = 0.0;
+  for (int i = 0; i < THREADS / 64; ++i) {
+    if (i < wid) base += red[i];
+    tot += red[i];
+  }
+  __syncthreads();
+  *total = tot;
+  const double up = __shfl_up(incl, 1);
+  return base + (lane > 0 ? up : 0.0);
+}
+
 // THREADS lanes per curve: 1024 when there are few curves, so that the N_L
 // midpoints of a curve are spread over more wavefronts.
 template <int THREADS>
@@ -112,6 +138,7 @@ __global__ __launch_bounds__(THREADS) void k_curve_prep(nsplat_curves cv, nsplat
                                                         int32_t* counters, int frozen, int n_scenes) {
   __shared__ double red[THREADS / 64];
   __shared__ double Us[PREP_KNOTS];
+  __shared__ int least;
   const int c = blockIdx.x;
   const CurveView v = curve_view(cv, w.knots, c);
   int32_t* row = plan + (int64_t)P_STRIDE * c;
@@ -141,19 +168,27 @@ __global__ __launch_bounds__(THREADS) void k_curve_prep(nsplat_curves cv, nsplat
   }
   // Knot vector: U_0 = 0, U_{l+1} = U_l + delta_l with the interval list of
   // Sec. 3.1 (open: p zeros, tau, p zeros; closed: last p tau, tau, first p).
-  // The intervals are gathered in parallel into LDS, one thread sums them in
-  // order (the same additions as a plain running sum), and the block writes
-  // the knots out and evaluates the arc length from the LDS copy.
+  // The intervals are FP32 values, so in FP64 their running sums are exact,
+  // whatever the order of the additions, as long as the total stays below
+  // 2^53 units of the smallest interval's last place; then every thread sums a
+  // contiguous share and a block scan joins them.  Other curves (intervals
+  // that differ by more than about 2^15 to 2^25, by the curve's length), and
+  // short ones, are summed in order by one thread.  That was the way of every
+  // curve before and took most of the time of long ones (the plan phase of one
+  // curve of 10,240 key points at 1024^2 1.317 -> 0.047 ms, of 16 of 2,000
+  // 0.057 -> 0.029 ms).
   double* U = w.knots + v.t0 + (int64_t)c * KNOT_PAD;
   auto interval = [&](int l) {
-    if (!v.closed()) return (l < v.p || l >= v.p + v.nt) ? 0.0 : (double)cv.tau[v.t0 + l - v.p];
+    if (!v.closed()) return (l < v.p || l >= v.p + v.nt) ? 0.0f : cv.tau[v.t0 + l - v.p];
     int t = (l - v.p) % v.nt;
     if (t < 0) t += v.nt;
-    return (double)cv.tau[v.t0 + t];
+    return cv.tau[v.t0 + t];
   };
   CurveView vk = v;  // the view the quadrature evaluates: knots in LDS when they fit
-  if (v.m + 1 <= PREP_KNOTS) {
-    for (int l = threadIdx.x; l < v.m; l += THREADS) Us[l + 1] = interval(l);
+  const bool in_lds = v.m + 1 <= PREP_KNOTS;
+  double* Uw = in_lds ? Us : U;
+  if (v.m <= SHORT_KNOTS) {
+    for (int l = threadIdx.x; l < v.m; l += THREADS) Us[l + 1] = (double)interval(l);
     __syncthreads();
     if (threadIdx.x == 0) {
       double acc = 0.0;
@@ -164,18 +199,44 @@ __global__ __launch_bounds__(THREADS) void k_curve_prep(nsplat_curves cv, nsplat
       }
     }
     __syncthreads();
-    for (int l = threadIdx.x; l <= v.m; l += THREADS) U[l] = Us[l];
-    vk.U = Us;
   } else {
-    if (threadIdx.x == 0) {
-      double acc = 0.0;
-      U[0] = 0.0;
+    const int per = (v.m + THREADS - 1) / THREADS, l0 = threadIdx.x * per, l1 = min(v.m, l0 + per);
+    double sum = 0.0;
+    int ulp = 255;  // least biased exponent of the nonzero intervals (a subnormal's is that of 2^-126)
+    for (int l = l0; l < l1; ++l) {
+      const float t = interval(l);
+      sum += (double)t;
+      if (t > 0.0f) ulp = min(ulp, max(1, (int)(__float_as_uint(t) >> 23)));
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) ulp = min(ulp, __shfl_xor(ulp, off));
+    if (threadIdx.x == 0) least = 255;
+    __syncthreads();
+    if (__lane_id() == 0) atomicMin(&least, ulp);
+    double total;
+    double acc = block_excl_scan_f64<THREADS>(sum, red, &total);
+    // last place of the smallest interval: 2^(least - 127 - 23); the margin
+    // covers the rounding of a total that is not exact
+    const bool exact = total * 1.001 < ldexp(1.0, least - 150 + 53);
+    if (exact) {
+      for (int l = l0; l < l1; ++l) {
+        acc += (double)interval(l);
+        Uw[l + 1] = acc;
+      }
+      if (threadIdx.x == 0) Uw[0] = 0.0;
+    } else if (threadIdx.x == 0) {
+      acc = 0.0;
+      Uw[0] = 0.0;
       for (int l = 0; l < v.m; ++l) {
-        acc = acc + interval(l);
-        U[l + 1] = acc;
+        acc = acc + (double)interval(l);
+        Uw[l + 1] = acc;
       }
     }
     __syncthreads();
+  }
+  if (in_lds) {
+    for (int l = threadIdx.x; l <= v.m; l += THREADS) U[l] = Us[l];
+    vk.U = Us;
   }
   // Eq. 3: L = sum_j ||C'(u_j)|| du over N_L midpoints of [u_p, u_{m-p}].
   const SceneTab* st = w.scenes + s;
@@ -215,9 +276,11 @@ __global__ __launch_bounds__(THREADS) void k_curve_prep(nsplat_curves cv, nsplat
 // counters[BOUND_REQ]; which == 1: Gaussians -> P_GOFF and goff[], total to
 // counters[GAUSS_REQ], capped total to counters[GAUSS], and the number of
 // fill Gaussians, of other (stroke) Gaussians and of tangent-aligned stroke
-// Gaussians to kinds[0], kinds[1], kinds[2].
+// Gaussians to kinds[0], kinds[1], kinds[2]; with no_boundary (a batch without
+// fills, whose boundary pass is not launched) also 0 -> P_BOFF.
 __global__ __launch_bounds__(1024) void k_curve_scan(nsplat_curves cv, int32_t* plan, int32_t* goff,
-                                                     int32_t* counters, int which, int64_t cap, int32_t* kinds) {
+                                                     int32_t* counters, int which, int64_t cap, int32_t* kinds,
+                                                     int no_boundary) {
   __shared__ int64_t wsum[16];
   __shared__ int64_t fsum[16];
   __shared__ int64_t asum[16];
@@ -275,6 +338,7 @@ __global__ __launch_bounds__(1024) void k_curve_scan(nsplat_curves cv, int32_t* 
       } else {
         row[P_GOFF] = (int32_t)run;
         goff[c] = (int32_t)run;
+        if (no_boundary) row[P_BOFF] = 0;
         run += row[P_COUNT];
       }
     }
@@ -1116,15 +1180,18 @@ hipError_t launch_sample(const Launch& L, int frozen) {
   else
     hipLaunchKernelGGL(k_curve_prep<PREP_THREADS>, dim3(n), dim3(PREP_THREADS), 0, L.stream, *L.cv, *L.pr, L.w, plan,
                        cnt, frozen, L.sc->n_scenes);
+  // without fills there are no boundary points (the counters stay cleared);
   // up to 1024 curves the boundary blocks take their own offsets
+  const bool fills = (L.cv->any_flags & NSPLAT_FILLED) != 0;
   const int own = n <= 4 * PREP_THREADS;
-  if (!own)
+  if (fills && !own)
     hipLaunchKernelGGL(k_curve_scan, dim3(1), dim3(1024), 0, L.stream, *L.cv, plan, L.w.goff, cnt, 0,
-                       (int64_t)L.bf->caps.boundary, L.w.queue + Q_NFILL);
-  hipLaunchKernelGGL(k_boundary, dim3(n), dim3(PREP_THREADS), 0, L.stream, *L.cv, *L.pr, L.w, plan,
-                     (int64_t)L.bf->caps.boundary, frozen, own, cnt);
+                       (int64_t)L.bf->caps.boundary, L.w.queue + Q_NFILL, 0);
+  if (fills)
+    hipLaunchKernelGGL(k_boundary, dim3(n), dim3(PREP_THREADS), 0, L.stream, *L.cv, *L.pr, L.w, plan,
+                       (int64_t)L.bf->caps.boundary, frozen, own, cnt);
   hipLaunchKernelGGL(k_curve_scan, dim3(1), dim3(1024), 0, L.stream, *L.cv, plan, L.w.goff, cnt, 1,
-                     (int64_t)L.bf->caps.gauss, L.w.queue + Q_NFILL);
+                     (int64_t)L.bf->caps.gauss, L.w.queue + Q_NFILL, fills ? 0 : 1);
   }
   Phase ph(L, NSPLAT_T_EMIT);
   if (L.cv->any_flags & NSPLAT_FILLED)

@@ -975,36 +975,6 @@ __global__ __launch_bounds__(256, 5) void k_emit(nsplat_curves cv, nsplat_params
   }
 }
 
-// Squared distance from q to the closed polyline b[0..nb) (with its chunk
-// boxes), or `best` if that is smaller: chunks whose box lies farther than
-// the running minimum (with a relative margin of 1e-12) are not visited.
-__device__ inline double polyline_dist2(double qx, double qy, const double2* __restrict__ bp,
-                                        const double4* __restrict__ box, int nb, double best) {
-  const int K = (nb + SDF_CHUNK - 1) / SDF_CHUNK;
-  for (int k = 0; k < K; ++k) {
-    const double4 b = box[k];
-    const double ex0 = fmax(fmax(b.x - qx, qx - b.y), 0.0);
-    const double ey0 = fmax(fmax(b.z - qy, qy - b.w), 0.0);
-    if (ex0 * ex0 + ey0 * ey0 > best * (1.0 + 1e-12)) continue;
-    const int i0 = k * SDF_CHUNK;
-    const int i1 = i0 + SDF_CHUNK < nb ? i0 + SDF_CHUNK : nb;
-    double2 A = bp[i0];
-    for (int i = i0; i < i1; ++i) {
-      const double2 B = bp[i + 1 < nb ? i + 1 : 0];
-      const double ex = B.x - A.x, ey = B.y - A.y;
-      const double ee = ex * ex + ey * ey;
-      const double rx = qx - A.x, ry = qy - A.y;
-      double t = 0.0;
-      if (ee > 0.0) t = (rx * ex + ry * ey) / ee;
-      t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
-      const double px = A.x + t * ex - qx, py = A.y + t * ey - qy;
-      best = fmin(best, px * px + py * py);
-      A = B;
-    }
-  }
-  return best;
-}
-
 __global__ void k_fill_f64(double* p, double v, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
@@ -1021,68 +991,164 @@ __device__ inline int scene_of_pixel(const SceneTab* st, int n_scenes, int64_t i
   return lo;
 }
 
+// Squared distances of the wavefront's points q, inside the box [wx0, wx1] x
+// [wy0, wy1] (wavefront-uniform), to the K chunks of one curve's boundary, or
+// `best` where that is smaller.  The lanes test one chunk box each against the
+// wavefront's box, and a chunk that some lane may be nearer to than its `best`
+// (with a relative margin of 1e-12) is visited, its records read by scalar
+// loads.
+template <class P>
+__device__ inline double polyline_dist2_wave(double qx, double qy, double wx0, double wx1, double wy0, double wy1,
+                                             P boxd, P segd, int K, double lim, double best) {
+  typedef const double* gdp;
+  const gdp boxv = (gdp)boxd;
+  const int lane = __lane_id();
+  for (int k0 = 0; k0 < K; k0 += 64) {
+    const int k = k0 + lane;
+    double b0 = 0.0, b1 = 0.0, b2 = 0.0, b3 = 0.0;
+    bool near = false;
+    if (k < K) {
+      b0 = boxv[4 * (1 + k)];
+      b1 = boxv[4 * (1 + k) + 1];
+      b2 = boxv[4 * (1 + k) + 2];
+      b3 = boxv[4 * (1 + k) + 3];
+      const double ex0 = fmax(fmax(b0 - wx1, wx0 - b1), 0.0), ey0 = fmax(fmax(b2 - wy1, wy0 - b3), 0.0);
+      near = ex0 * ex0 + ey0 * ey0 <= lim * (1.0 + 1e-12);
+    }
+    uint64_t m = __ballot(near);
+    while (m) {
+      const int bit = __builtin_ctzll(m);
+      m &= m - 1;
+      const double x0 = readlane_f64(b0, bit), x1 = readlane_f64(b1, bit), y0 = readlane_f64(b2, bit),
+                   y1 = readlane_f64(b3, bit);
+      const double ex0 = fmax(fmax(x0 - qx, qx - x1), 0.0), ey0 = fmax(fmax(y0 - qy, qy - y1), 0.0);
+      if (__ballot(ex0 * ex0 + ey0 * ey0 <= best * (1.0 + 1e-12)) == 0ull) continue;
+#pragma unroll 2
+      for (int j = 0; j < SDF_CHUNK; ++j) {
+        const int64_t o = (int64_t)SEG_WORDS * ((int64_t)(k0 + bit) * SDF_CHUNK + j);
+        const double ax = segd[o], ay = segd[o + 1], ex = segd[o + 2], ey = segd[o + 3], inv = segd[o + 4];
+        const double rx = qx - ax, ry = qy - ay;
+        double t = __builtin_fma(rx, ex, ry * ey) * inv;
+        t = t < 0.0 ? 0.0 : (t > 1.0 ? 1.0 : t);
+        const double px = __builtin_fma(t, ex, -rx), py = __builtin_fma(t, ey, -ry);
+        best = fmin(best, __builtin_fma(px, px, py * py));
+      }
+    }
+  }
+  return best;
+}
+
+// 8 x 8 pixel blocks of a scene.
+__host__ __device__ inline int64_t pixel_blocks(int H, int W) { return (int64_t)((H + 7) / 8) * ((W + 7) / 8); }
+
 // Distance-weighted loss, pass 1: per pixel q, d(q) = distance to the nearest
 // boundary segment of the scene's selected filled curves, w(q) =
 // max(0, tau - d(q)) stored in the first channel plane of dL, and the per-scene
-// sums of w.
+// sums of w.  One wavefront per 8 x 8 pixel block: its lanes test one curve's
+// box each against the block, then one chunk's, so that a block visits only
+// what can lie within tau of it (no weight depends on more); every pixel on its
+// own walked all curves of its scene before (32 paths at 480^2: both passes
+// 0.147 -> 0.031 ms).
 __global__ __launch_bounds__(256) void k_udf_weight(nsplat_curves cv, Work w, const int32_t* plan, int64_t bcap,
-                                                    int n_scenes, int C, const int32_t* sel, float tau,
-                                                    float* __restrict__ dL) {
-  const int64_t npix = w.scenes[n_scenes].pix_off;
-  for (int64_t base = (int64_t)blockIdx.x * blockDim.x + threadIdx.x - __lane_id(); base < npix;
-       base += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = base + __lane_id();
-    int s = -1;
-    double wq = 0.0;
-    if (i < npix) {
-      s = scene_of_pixel(w.scenes, n_scenes, i);
-      const SceneTab st = w.scenes[s];
-      const int64_t li = i - st.pix_off;
-      const int y = (int)(li / st.W), x = (int)(li - (int64_t)y * st.W);
-      const double qx = x + 0.5, qy = y + 0.5;
-      // curves of scene s: [c0, c1)
+                                                    int n_scenes, int64_t n_blocks, int C, const int32_t* sel,
+                                                    float tau, float* __restrict__ dL) {
+  typedef const __attribute__((address_space(4))) double* cdp;
+  const int lane = __lane_id();
+  const int64_t waves = (int64_t)gridDim.x * 4, wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t per = (n_blocks + waves - 1) / waves;  // consecutive blocks of this wavefront
+  const double lim = (double)tau * (double)tau;
+  double acc = 0.0;
+  int s_open = -1;
+  auto close_scene = [&]() {  // the open scene's sum of weights over the wavefront
+    if (s_open < 0) return;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0 && acc != 0.0) unsafeAtomicAdd(&w.sacc[s_open], acc);
+    acc = 0.0;
+  };
+  const int64_t i1 = min(n_blocks, (wave + 1) * per);
+  if (wave * per >= i1) return;
+  // the scene of the first block, the lanes counting one scene's blocks each
+  int s = 0;
+  int64_t first = 0;  // the scene's first block
+  for (int s0 = 0; s0 < n_scenes; s0 += 64) {
+    int64_t n = 0;
+    if (s0 + lane < n_scenes) n = pixel_blocks(w.scenes[s0 + lane].H, w.scenes[s0 + lane].W);
+    int64_t incl = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int64_t o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    const uint64_t past = __ballot(first + incl > wave * per);
+    const int at = past ? __builtin_ctzll(past) : 63;
+    s = s0 + at;
+    first += past ? __shfl(incl - n, at) : __shfl(incl, 63);
+    if (past) break;
+  }
+  s = __builtin_amdgcn_readfirstlane(s);
+  first = first_lane_i64(first);
+  int c0 = 0, c1 = 0;  // curves of the open scene
+  for (int64_t i = wave * per; i < i1; ++i) {
+    SceneTab st = w.scenes[s];
+    while (i - first >= pixel_blocks(st.H, st.W)) {
+      first += pixel_blocks(st.H, st.W);
+      st = w.scenes[++s];
+    }
+    if (s != s_open) {
+      close_scene();
+      s_open = s;
       int lo = 0, hi = cv.n_curves;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
         if (cv.scene[mid] < s) lo = mid + 1;
         else hi = mid;
       }
-      const int c0 = lo;
+      c0 = lo;
       hi = cv.n_curves;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
         if (cv.scene[mid] <= s) lo = mid + 1;
         else hi = mid;
       }
-      double best = INFINITY;
-      for (int c = c0; c < lo; ++c) {
-        if (!(cv.flags[c] & NSPLAT_FILLED) || (sel && !sel[c])) continue;
+      c1 = lo;
+    }
+    const int cols = (st.W + 7) / 8, b = (int)(i - first);
+    const int bx = 8 * (b % cols), by = 8 * (b / cols);
+    const int x = bx + (lane & 7), y = by + (lane >> 3);
+    const bool in = x < st.W && y < st.H;
+    const double wx0 = bx + 0.5, wx1 = wx0 + 7.0, wy0 = by + 0.5, wy1 = wy0 + 7.0;
+    const double qx = x + 0.5, qy = y + 0.5;
+    double best = lim;  // a boundary farther than tau gives no weight
+    for (int cb = c0; cb < c1; cb += 64) {
+      const int c = cb + lane;
+      bool near = false;
+      if (c < c1 && (cv.flags[c] & NSPLAT_FILLED) && !(sel && !sel[c])) {
         const int32_t* row = plan + (int64_t)P_STRIDE * c;
-        const int nb = row[P_NSAMP];
+        const int nb = row[P_NSAMP];  // (0 for a curve with invalid data or values)
         const int64_t boff = row[P_BOFF];
-        if (nb <= 0 || boff + nb > bcap || !curve_valid(curve_view(cv, w.knots, c))) continue;
-        const double4* box = w.cbox + cbox_base(boff, c);
-        const double4 hb = box[0];
-        const double ex0 = fmax(fmax(hb.x - qx, qx - hb.y), 0.0);
-        const double ey0 = fmax(fmax(hb.z - qy, qy - hb.w), 0.0);
-        if (ex0 * ex0 + ey0 * ey0 > best * (1.0 + 1e-12)) continue;
-        best = polyline_dist2(qx, qy, w.bpts + boff, box + 1, nb, best);
+        if (nb > 0 && boff + nb <= bcap) {
+          const double4 hb = w.cbox[cbox_base(boff, c)];
+          const double ex0 = fmax(fmax(hb.x - wx1, wx0 - hb.y), 0.0), ey0 = fmax(fmax(hb.z - wy1, wy0 - hb.w), 0.0);
+          near = ex0 * ex0 + ey0 * ey0 <= lim * (1.0 + 1e-12);
+        }
       }
-      wq = fmax(0.0, (double)tau - sqrt(best));
-      dL[st.pix_off * C + li] = (float)wq;
+      uint64_t m = __ballot(near);
+      while (m) {
+        const int cu = __builtin_amdgcn_readfirstlane(cb + __builtin_ctzll(m));
+        m &= m - 1;
+        const int32_t* row = plan + (int64_t)P_STRIDE * cu;
+        const int nb = __builtin_amdgcn_readfirstlane(row[P_NSAMP]), boff = __builtin_amdgcn_readfirstlane(row[P_BOFF]);
+        best = polyline_dist2_wave(qx, qy, wx0, wx1, wy0, wy1, (cdp)(w.cbox + cbox_base(boff, cu)),
+                                   (cdp)(w.segs + SEG_WORDS * seg_base(boff, cu)), (nb + SDF_CHUNK - 1) / SDF_CHUNK,
+                                   lim, best);
+      }
     }
-    // per-scene sums: one atomic per wavefront when its pixels share a scene
-    const int s0 = __builtin_amdgcn_readfirstlane(s);
-    const bool same = __ballot(i < npix && s != s0) == 0ull;
-    if (same) {
-      double t = wq;
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off);
-      if (__lane_id() == 0 && s0 >= 0 && t != 0.0) unsafeAtomicAdd(&w.sacc[s0], t);
-    } else if (s >= 0 && wq != 0.0) {
-      unsafeAtomicAdd(&w.sacc[s], wq);
-    }
+    const double wq = in ? fmax(0.0, (double)tau - sqrt(best)) : 0.0;
+    if (in) dL[(int64_t)st.pix_off * C + (int64_t)y * st.W + x] = (float)wq;
+    acc += wq;
   }
+  close_scene();
 }
 
 // Pass 2: dL/dI_c(q) = 2 w(q) / W_s (I_c - I*_c) / C with W_s the scene's sum
@@ -1120,14 +1186,19 @@ __global__ __launch_bounds__(256) void k_udf_grad(Work w, int n_scenes, int C, c
 hipError_t launch_udf(const Launch& L, const int32_t* sel, float tau, const float* image, const float* target,
                       float* dL, float* loss, double* sacc) {
   const int S = L.sc->n_scenes, C = L.cv->channels;
-  int64_t npix = 0;
-  for (int s = 0; s < S; ++s) npix += (int64_t)L.sc->hw_host[2 * s] * L.sc->hw_host[2 * s + 1];
+  int64_t npix = 0, blocks = 0;
+  for (int s = 0; s < S; ++s) {
+    npix += (int64_t)L.sc->hw_host[2 * s] * L.sc->hw_host[2 * s + 1];
+    blocks += pixel_blocks(L.sc->hw_host[2 * s], L.sc->hw_host[2 * s + 1]);
+  }
   Work w = L.w;
   if (sacc) w.sacc = sacc;  // per-scene weight sums somewhere else than the workspace
   hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(256), 0, L.stream, w.sacc, 0.0, (int64_t)(S + 1));
   if (npix <= 0) return hipGetLastError();
-  hipLaunchKernelGGL(k_udf_weight, dim3(grid_for(npix, 256, 8192)), dim3(256), 0, L.stream, *L.cv, w,
-                     L.bf->plan, (int64_t)L.bf->caps.boundary, S, C, sel, tau, dL);
+  // enough wavefronts to fill the GPU, few enough that their per-scene sums do
+  // not queue up
+  hipLaunchKernelGGL(k_udf_weight, dim3(grid_for(blocks, 4, 1024)), dim3(256), 0, L.stream, *L.cv, w, L.bf->plan,
+                     (int64_t)L.bf->caps.boundary, S, blocks, C, sel, tau, dL);
   hipLaunchKernelGGL(k_udf_grad, dim3(grid_for(npix, 256, 2048)), dim3(256), 0, L.stream, w, S, C, image, target,
                      dL, loss);
   return hipGetLastError();

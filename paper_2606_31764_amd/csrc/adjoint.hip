@@ -16,8 +16,8 @@
 //   (Colour gradients, and the opacity gradient of stroke curves, are
 //   accumulated per curve by the compositing adjoint.)
 //   k_adj_boundary  one lane per boundary point: the same point adjoint.
-//   Both reduce within the wavefront by (curve, span) segment before the FP64
-//   global atomics.
+//   Both sum within the wavefront by (curve, span) run before the FP64 global
+//   atomics (accumulate_points).
 //   k_reg_stroke,   the geometric regularisers of Sec. 3.5 at stroke samples
 //   k_reg_boundary  and fill boundary points: bounding-box penalty (Eq. 12)
 //                   into the centre / boundary-point adjoints, derivative
@@ -44,106 +44,130 @@ struct PtAdj {
   double ubar;
 };
 
-// Reverse-mode adjoint of the rational point (x, y, s) at u on `span` for the
-// upstream gradient ab[3].
-template <int PD>
-__device__ inline void point_adjoint(const nsplat_curves& cv, const CurveView& v, double u, int span,
-                                     const double (&ab)[3], PtAdj<PD>& out) {
-  const double* U = v.U;
-  const int p = v.p;
-  double tri[tri_n(PD)];
-  double N[PD + 1], left[PD + 1], right[PD + 1];
-  N[0] = 1.0;
+// Reciprocals of the Cox-de Boor denominators: inv[d (d - 1) / 2 + r] =
+// 1 / (U[span + r + 1] - U[span - d + r + 1]), r < d (each stands in two terms
+// of the triangle and in four of its reverse, as a division each time before:
+// point adjoints of 1.8M samples 0.248 -> 0.098 ms with the sums below).
+constexpr int inv_n(int d) { return d * (d + 1) / 2; }
+
+// Basis triangle at u on `span`: left[k] = u - U[span + 1 - k], right[k] =
+// U[span + k] - u, the reciprocals, and level d's functions at tri[d (d + 1) / 2].
+template <int P>
+__device__ inline void basis_triangle(const double* U, int span, double u, double (&left)[P + 1],
+                                      double (&right)[P + 1], double (&inv)[inv_n(P)], double (&tri)[tri_n(P)]) {
   tri[0] = 1.0;
 #pragma unroll
-  for (int d = 1; d <= PD; ++d) {
-    if (d > p) break;
-    left[d] = u - U[span + 1 - d];
-    right[d] = U[span + d] - u;
+  for (int d = 1; d <= P; ++d) {
+    const double lo = U[span + 1 - d], hi = U[span + d];
+    left[d] = u - lo;
+    right[d] = hi - u;
     double saved = 0.0;
 #pragma unroll
     for (int r = 0; r < d; ++r) {
-      const double temp = N[r] / (right[r + 1] + left[d - r]);
-      N[r] = saved + right[r + 1] * temp;
+      inv[d * (d - 1) / 2 + r] = 1.0 / (right[r + 1] + left[d - r]);
+      const double temp = tri[(d - 1) * d / 2 + r] * inv[d * (d - 1) / 2 + r];
+      tri[d * (d + 1) / 2 + r] = saved + right[r + 1] * temp;
       saved = left[d - r] * temp;
     }
-    N[d] = saved;
-#pragma unroll
-    for (int r = 0; r <= d; ++r) tri[d * (d + 1) / 2 + r] = N[r];
+    tri[d * (d + 1) / 2 + d] = saved;
   }
+}
+
+// Reverse of the triangle: given the adjoints Nb of the degree-d functions,
+// through N_{i,d} = (u - U_i) / (U_{i+d} - U_i) N_{i,d-1}
+//                 + (U_{i+d+1} - u) / (U_{i+d+1} - U_{i+1}) N_{i+1,d-1},
+// adds the adjoints of u and of the knots (slot k <-> knot index
+// span - PD + 1 + k) and leaves those of the degree d - 1 functions in Nb.
+template <int PD, int P>
+__device__ inline void triangle_reverse(int d, const double (&left)[P + 1], const double (&right)[P + 1],
+                                        const double (&inv)[inv_n(P)], const double (&tri)[tri_n(P)],
+                                        double (&Nb)[P + 1], double& ub, double (&knot)[2 * PD]) {
+  double Np[P + 1];
+#pragma unroll
+  for (int r = 0; r <= P; ++r) Np[r] = 0.0;
+#pragma unroll
+  for (int r = 0; r <= d; ++r) {
+    const double nb = Nb[r];
+    if (r >= 1) {
+      const double iv = inv[d * (d - 1) / 2 + r - 1], al = left[d + 1 - r] * iv;
+      Np[r - 1] += nb * al;
+      const double g = nb * tri[(d - 1) * d / 2 + r - 1] * iv;
+      ub += g;
+      knot[PD - 1 - d + r] -= g * (right[r] * iv);
+      knot[PD - 1 + r] -= g * al;
+    }
+    if (r <= d - 1) {
+      const double iv = inv[d * (d - 1) / 2 + r], be = right[r + 1] * iv;
+      Np[r] += nb * be;
+      const double g = nb * tri[(d - 1) * d / 2 + r] * iv;
+      ub -= g;
+      knot[PD + r] += g * (left[d - r] * iv);
+      knot[PD - d + r] += g * be;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r <= P; ++r) Nb[r] = Np[r];
+}
+
+// Reverse-mode adjoint of the rational point (x, y, s) at u on `span` for the
+// upstream gradient ab[3], for a curve of degree P <= PD.
+template <int PD, int P>
+__device__ inline void point_adjoint_deg(const nsplat_curves& cv, const CurveView& v, double u, int span,
+                                         const double (&ab)[3], PtAdj<PD>& out) {
+  double tri[tri_n(P)], left[P + 1], right[P + 1], inv[inv_n(P)];
+  basis_triangle<P>(v.U, span, u, left, right, inv, tri);
+  constexpr int TP = P * (P + 1) / 2;  // the degree-P functions
   // C = S / W over the span's control points
-  double P[PD + 1][3], wt[PD + 1];
+  double Q[P + 1][3], wt[P + 1];
   double S[3] = {0.0, 0.0, 0.0}, W = 0.0;
 #pragma unroll
-  for (int r = 0; r <= PD; ++r) {
-    if (r > p) break;
-    const int k = v.k0 + v.key_of_cp(span - p + r);
+  for (int r = 0; r <= P; ++r) {
+    const int k = v.k0 + v.key_of_cp(span - P + r);
     wt[r] = (double)cv.key_w[k];
-    P[r][0] = (double)cv.key_xy[2 * k];
-    P[r][1] = (double)cv.key_xy[2 * k + 1];
-    P[r][2] = (double)cv.key_s[k];
-    const double nw = N[r] * wt[r];
+    Q[r][0] = (double)cv.key_xy[2 * k];
+    Q[r][1] = (double)cv.key_xy[2 * k + 1];
+    Q[r][2] = (double)cv.key_s[k];
+    const double nw = tri[TP + r] * wt[r];
     W += nw;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) S[q] += nw * P[r][q];
+    for (int q = 0; q < 3; ++q) S[q] += nw * Q[r][q];
   }
   const double invW = 1.0 / W;
   const double Cp[3] = {S[0] * invW, S[1] * invW, S[2] * invW};
-  double Nb[PD + 1];
+  double Nb[P + 1];
 #pragma unroll
   for (int r = 0; r <= PD; ++r) {
-    Nb[r] = 0.0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) out.cp[r][q] = 0.0;
-    if (r > p) continue;
-    const double gdot = ab[0] * (P[r][0] - Cp[0]) + ab[1] * (P[r][1] - Cp[1]) + ab[2] * (P[r][2] - Cp[2]);
-    const double nwW = N[r] * wt[r] * invW;
-    out.cp[r][0] = ab[0] * nwW;            // dC/dP = N w / W
+    if (r > P) continue;
+    const double gdot = ab[0] * (Q[r][0] - Cp[0]) + ab[1] * (Q[r][1] - Cp[1]) + ab[2] * (Q[r][2] - Cp[2]);
+    const double nwW = tri[TP + r] * wt[r] * invW;
+    out.cp[r][0] = ab[0] * nwW;                // dC/dP = N w / W
     out.cp[r][1] = ab[1] * nwW;
-    out.cp[r][2] = N[r] * gdot * invW;     // dC/dw = N (P - C) / W
+    out.cp[r][2] = tri[TP + r] * gdot * invW;  // dC/dw = N (P - C) / W
     out.cp[r][3] = ab[2] * nwW;
-    Nb[r] = wt[r] * gdot * invW;           // dC/dN = w (P - C) / W
+    Nb[r] = wt[r] * gdot * invW;               // dC/dN = w (P - C) / W
   }
-  // Reverse through N_{i,d} = (u - U_i)/(U_{i+d} - U_i) N_{i,d-1}
-  //                          + (U_{i+d+1} - u)/(U_{i+d+1} - U_{i+1}) N_{i+1,d-1}
   double ub = 0.0;
 #pragma unroll
   for (int k = 0; k < 2 * PD; ++k) out.knot[k] = 0.0;
 #pragma unroll
-  for (int d = PD; d >= 1; --d) {
-    if (d > p) continue;
-    double Np[PD + 1];
-#pragma unroll
-    for (int r = 0; r <= PD; ++r) Np[r] = 0.0;
-#pragma unroll
-    for (int r = 0; r <= d; ++r) {
-      const double nb = Nb[r];
-      const int i = span - d + r;
-      if (r >= 1) {
-        const double Ui = U[i], Uid = U[i + d];
-        const double D = Uid - Ui;
-        const double al = (u - Ui) / D;
-        Np[r - 1] += nb * al;
-        const double g = nb * tri[(d - 1) * d / 2 + r - 1];
-        ub += g / D;
-        out.knot[PD - 1 - d + r] -= g * (Uid - u) / (D * D);
-        out.knot[PD - 1 + r] -= g * (u - Ui) / (D * D);
-      }
-      if (r <= d - 1) {
-        const double Ui1 = U[i + 1], Uid1 = U[i + d + 1];
-        const double D = Uid1 - Ui1;
-        const double be = (Uid1 - u) / D;
-        Np[r] += nb * be;
-        const double g = nb * tri[(d - 1) * d / 2 + r];
-        ub -= g / D;
-        out.knot[PD + r] += g * (u - Ui1) / (D * D);
-        out.knot[PD - d + r] += g * (Uid1 - u) / (D * D);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r <= PD; ++r) Nb[r] = Np[r];
-  }
+  for (int d = P; d >= 1; --d) triangle_reverse<PD, P>(d, left, right, inv, tri, Nb, ub, out.knot);
   out.ubar = ub;
+}
+
+// The adjoints for the degree of the lane's curve: bodies with the degree
+// fixed need no tests of it and fewer registers.
+template <int PD>
+__device__ inline void point_adjoint(const nsplat_curves& cv, const CurveView& v, double u, int span,
+                                     const double (&ab)[3], PtAdj<PD>& out) {
+  if constexpr (PD >= 5) {
+    if (v.p == 5) return point_adjoint_deg<PD, 5>(cv, v, u, span, ab, out);
+    if (v.p == 4) return point_adjoint_deg<PD, 4>(cv, v, u, span, ab, out);
+  }
+  if (v.p == 3) return point_adjoint_deg<PD, 3>(cv, v, u, span, ab, out);
+  if (v.p == 2) return point_adjoint_deg<PD, 2>(cv, v, u, span, ab, out);
+  point_adjoint_deg<PD, 1>(cv, v, u, span, ab, out);
 }
 
 // Segmented suffix sum across the wavefront.  A run is a maximal group of
@@ -174,68 +198,175 @@ __device__ inline bool seg_head(int64_t key) {
   return key >= 0 && (lane == 0 || prev != key);
 }
 
-// Wave-cooperative accumulation of point adjoints into the FP64 control-point
-// and knot buffers.  Every lane of the wavefront must call it.
+// Sums of point adjoints over the wavefront into the FP64 control-point and
+// knot buffers.  The lanes' values go through LDS, one row of 64 samples per
+// value; lane (i, part) = (l & 31, l >> 5) then adds up value i over half of
+// the samples, 32 at most, and sends the sum of each run of samples with one
+// (curve, span) out with one atomic (a run that crosses the middle is joined
+// there).  Shuffling every value through six rounds of a segmented scan took
+// 264 LDS permutes and as many selects per wavefront before, this 22 writes and
+// 32 reads (adjoint of 1.8M samples: 0.248 -> 0.098 ms with the reciprocals
+// above; 16 closed strokes at 512^2 0.022 -> 0.012).  At degree 4 or 5 the values go in two rounds.
 template <int PD>
-__device__ inline void accumulate_points(const Work& w, int64_t key, int c, const CurveView& v, int span,
-                                         PtAdj<PD>& pa, bool any) {
-  if (!any) return;
-  constexpr int NCP = 4 * (PD + 1);
-  double buf[NCP + 2 * PD];
+struct PointSums {
+  static constexpr int NCP = 4 * (PD + 1), NV = NCP + 2 * PD, ROUNDS = NV > 32 ? 2 : 1, NR = NV / ROUNDS;
+  static_assert(NR * ROUNDS == NV && NR <= 32, "values per round");
+  double v[NR][65];     // padded rows
+  int64_t cp[64], kn[64];  // by a run's first sample: its first control-point and knot element
+};
+
+template <int PD>
+__device__ inline void accumulate_points(const Work& w, PointSums<PD>* st, bool act, int64_t key, int c,
+                                         const CurveView& v, int span, PtAdj<PD>& pa) {
+  using S = PointSums<PD>;
+  const uint64_t am = __ballot(act);
+  if (am == 0ull) return;
+  const int lane = __lane_id();
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  // a run begins at an active lane whose key differs from the active lane's
+  // before it; inactive lanes (values 0) go on with the run
+  const int pl = (am & below) ? 63 - __builtin_clzll(am & below) : -1;
+  const int64_t pk = __shfl(key, pl < 0 ? 0 : pl);
+  const bool head = act && (pl < 0 || pk != key);
+  const uint64_t hm = __ballot(head);
+  const int i = lane & 31, part = lane >> 5;
+  const uint32_t mine = (uint32_t)(part ? hm >> 32 : hm);
 #pragma unroll
-  for (int r = 0; r <= PD; ++r)
+  for (int rd = 0; rd < S::ROUNDS; ++rd) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-    for (int q = 0; q < 4; ++q) buf[4 * r + q] = pa.cp[r][q];
-#pragma unroll
-  for (int k = 0; k < 2 * PD; ++k) buf[NCP + k] = pa.knot[k];
-  seg_reduce(key, buf);
-  if (seg_head(key)) {
-    double* gcp = w.gcp + 4 * ((int64_t)v.k0 + (int64_t)c * CP_PAD);
-    double* gk = w.gknot + (int64_t)v.t0 + (int64_t)c * KNOT_PAD;
-#pragma unroll
-    for (int r = 0; r <= PD; ++r) {
-      if (r > v.p) break;
-      const int j = span - v.p + r;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (buf[4 * r + q] != 0.0) unsafeAtomicAdd(gcp + 4 * j + q, buf[4 * r + q]);
+    for (int k = 0; k < S::NR; ++k) {
+      const int q = rd * S::NR + k;
+      st->v[k][lane] = q < S::NCP ? pa.cp[q / 4][q & 3] : pa.knot[q - S::NCP < 2 * PD ? q - S::NCP : 0];
     }
-#pragma unroll
-    for (int k = 0; k < 2 * PD; ++k) {
-      if (k < PD - v.p || k > PD + v.p - 1) continue;
-      if (buf[NCP + k] != 0.0) unsafeAtomicAdd(gk + span - PD + 1 + k, buf[NCP + k]);
+    if (head && rd == 0) {
+      st->cp[lane] = 4 * ((int64_t)v.k0 + (int64_t)c * CP_PAD + span - v.p);
+      st->kn[lane] = (int64_t)v.t0 + (int64_t)c * KNOT_PAD + span - PD + 1;
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int q = rd * S::NR + i;
+    const bool valid = i < S::NR;
+    auto emit = [&](int at, double x) {  // the run that begins at sample `at`
+      if (!valid || x == 0.0) return;
+      double* o = q < S::NCP ? w.gcp + st->cp[at] + q : w.gknot + st->kn[at] + (q - S::NCP);
+      unsafeAtomicAdd(o, x);
+    };
+    const double* row = st->v[valid ? i : 0] + 32 * part;
+    double sum = 0.0, first = 0.0;  // first: the upper half's samples before its first run
+    int at = -1;                    // where the open run begins (-1: none in this half yet)
+#pragma unroll 8
+    for (int k = 0; k < 32; ++k) {
+      const double x = row[k];
+      if ((mine >> k) & 1u) {
+        if (at >= 0) emit(at, sum);
+        else first = sum;
+        at = 32 * part + k;
+        sum = 0.0;
+      }
+      sum += x;
+    }
+    if (at < 0) {
+      first = sum;
+      sum = 0.0;
+    }
+    // the lower half's last run goes on with the upper half's first samples
+    const double up = __shfl(first, i + 32);
+    const bool lower = part == 0;
+    if (at >= 0) emit(at, lower ? sum + up : sum);
+    else if (lower && up != 0.0) emit(0, up);  // (no run in the lower half: up is 0)
   }
 }
 
-// Curve-level sums (opacity, colour, domain ends), reduced by curve.
-__device__ inline void accumulate_curve(const Work& w, int64_t key, int c, const CurveView& v, double (&cur)[6]) {
-  seg_reduce(key, cur);
-  if (seg_head(key)) {
-    double* gc = w.gcurve + 4 * (int64_t)c;
+// Curve-level sums dL/du_p, dL/du_{m-p} (the samples' dependence on the domain
+// ends), kept per lane over consecutive groups of samples of one curve and
+// sent out where the curve changes: all samples of a curve add to the same two
+// addresses, where an atomic per wavefront queues up.
+struct DomainSums {
+  int c = -1;            // the curve of a and b (wavefront-uniform)
+  int64_t ia = 0, ib = 0;
+  double a = 0.0, b = 0.0;
+  __device__ void flush(const Work& w) {
+    if (c < 0) return;
+    double x = a, y = b;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (cur[i] != 0.0) unsafeAtomicAdd(gc + i, cur[i]);
-    double* gk = w.gknot + (int64_t)v.t0 + (int64_t)c * KNOT_PAD;
-    if (cur[4] != 0.0) unsafeAtomicAdd(gk + v.p, cur[4]);
-    if (cur[5] != 0.0) unsafeAtomicAdd(gk + v.m - v.p, cur[5]);
+    for (int off = 32; off >= 1; off >>= 1) {
+      x += __shfl_xor(x, off);
+      y += __shfl_xor(y, off);
+    }
+    if (__lane_id() == 0) {
+      if (x != 0.0) unsafeAtomicAdd(w.gknot + ia, x);
+      if (y != 0.0) unsafeAtomicAdd(w.gknot + ib, y);
+    }
+    c = -1;
+    a = b = 0.0;
   }
-}
+  // every lane of the wavefront calls it; act lanes add (xa, xb) to curve cc
+  __device__ void add(const Work& w, bool act, int cc, const CurveView& v, double xa, double xb) {
+    const uint64_t am = __ballot(act);
+    if (am == 0ull) return;
+    const int l0 = __builtin_ctzll(am);
+    const int cu = __builtin_amdgcn_readlane(cc, l0);
+    const int64_t base = (int64_t)v.t0 + (int64_t)cc * KNOT_PAD, pa = base + v.p, pb = base + v.m - v.p;
+    if (__ballot(act && cc != cu) == 0ull) {
+      if (cu != c) {
+        flush(w);
+        c = cu;
+        ia = __shfl(pa, l0);
+        ib = __shfl(pb, l0);
+      }
+      a += act ? xa : 0.0;
+      b += act ? xb : 0.0;
+      return;
+    }
+    double x[2] = {act ? xa : 0.0, act ? xb : 0.0};
+    const int64_t key = act ? (int64_t)cc : -1 - (int64_t)__lane_id();
+    seg_reduce(key, x);
+    if (seg_head(key)) {
+      if (x[0] != 0.0) unsafeAtomicAdd(w.gknot + pa, x[0]);
+      if (x[1] != 0.0) unsafeAtomicAdd(w.gknot + pb, x[1]);
+    }
+  }
+};
 
-// Stroke Gaussians: dL/d(mu, sigma) -> the curve point adjoint at u_j.
+// First group of 64 samples of this wavefront and its stride over the groups
+// (in samples): wavefronts take `run` consecutive groups at a time.
+struct GroupWalk {
+  int64_t base, jump;
+  int run, k = 0;
+  __device__ GroupWalk(int run_) : run(run_) {
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    base = wave * run * 64;
+    jump = (((int64_t)gridDim.x * blockDim.x) >> 6) * run * 64 - (int64_t)(run - 1) * 64;
+  }
+  __device__ void next() {
+    if (++k < run) base += 64;
+    else {
+      k = 0;
+      base += jump;
+    }
+  }
+};
+
+// Stroke Gaussians: dL/d(mu, sigma) -> the curve point adjoint at u_j.  Held to
+// three wavefronts per SIMD at degree 3 (168 VGPRs, 8 spilled): with 170 and two
+// wavefronts 1.8M samples took 0.118 ms, with three 0.098.
 template <int PD>
-__global__ __launch_bounds__(256) void k_adj_stroke(nsplat_curves cv, nsplat_params pr, Work w,
+__global__ __launch_bounds__(256, PD <= 3 ? 3 : 2) void k_adj_stroke(nsplat_curves cv, nsplat_params pr, Work w,
                                                     const int32_t* plan, const int32_t* counters,
-                                                    const Gauss* __restrict__ gs) {
+                                                    const Gauss* __restrict__ gs, int run) {
+  __shared__ PointSums<PD> sums[4];
   if (w.queue[Q_NSTROKE] == 0) return;  // no Gaussians of this kind
   const int64_t G = counters[NSPLAT_CNT_GAUSS];
   const int lane = __lane_id();
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) - lane;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t base = wave0; base < G; base += stride) {
-    const int64_t g = base + lane;
-    int64_t kspan = -1 - lane, kcur = -1 - lane;
-    double cur[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  DomainSums dom;
+  for (GroupWalk gw(run); gw.base < G; gw.next()) {
+    const int64_t g = gw.base + lane;
+    int64_t kspan = 0;
+    double da = 0.0, db = 0.0;
     PtAdj<PD> pa;
     int c = 0, span = 0;
     CurveView v;
@@ -260,10 +391,9 @@ __global__ __launch_bounds__(256) void k_adj_stroke(nsplat_curves cv, nsplat_par
         const double u = sample_u(v.U[v.p], v.U[v.m - v.p], j, M, v.closed(), &dt);
         span = find_span(v.U, v.p, v.m, u);
         point_adjoint(cv, v, u, span, ab, pa);
-        cur[4] = pa.ubar * (1.0 - dt);  // u_j = u_p + t_j (u_{m-p} - u_p)
-        cur[5] = pa.ubar * dt;
+        da = pa.ubar * (1.0 - dt);  // u_j = u_p + t_j (u_{m-p} - u_p)
+        db = pa.ubar * dt;
         kspan = (int64_t)v.t0 + (int64_t)c * KNOT_PAD + span;
-        kcur = c;
       }
     }
     if (!stroke) {
@@ -274,10 +404,10 @@ __global__ __launch_bounds__(256) void k_adj_stroke(nsplat_curves cv, nsplat_par
 #pragma unroll
       for (int k = 0; k < 2 * PD; ++k) pa.knot[k] = 0.0;
     }
-    const bool any = __ballot(stroke) != 0ull;
-    accumulate_points(w, kspan, c, v, span, pa, any);
-    if (any) accumulate_curve(w, kcur, c, v, cur);
+    accumulate_points(w, &sums[threadIdx.x >> 6], stroke, kspan, c, v, span, pa);
+    dom.add(w, stroke, c, v, da, db);
   }
+  dom.flush(w);
 }
 
 // Fill Gaussians: o_j = o sigmoid(z), z = gamma / h * sgn * d(q) with the
@@ -374,17 +504,17 @@ __global__ __launch_bounds__(256) void k_adj_fill(nsplat_curves cv, nsplat_param
 }
 
 template <int PD>
-__global__ __launch_bounds__(256) void k_adj_boundary(nsplat_curves cv, Work w, const int32_t* plan,
+__global__ __launch_bounds__(256, PD <= 3 ? 3 : 2) void k_adj_boundary(nsplat_curves cv, Work w, const int32_t* plan,
                                                       const int32_t* counters) {
+  __shared__ PointSums<PD> sums[4];
   const int64_t NB = counters[NSPLAT_CNT_BOUND];
   const int lane = __lane_id();
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) - lane;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int n = cv.n_curves;
-  for (int64_t base = wave0; base < NB; base += stride) {
-    const int64_t b = base + lane;
+  DomainSums dom;
+  for (GroupWalk gw(1); gw.base < NB; gw.next()) {
+    const int64_t b = gw.base + lane;
     bool act = false;
-    int64_t kspan = -1 - lane, kcur = -1 - lane;
+    int64_t kspan = 0;
     PtAdj<PD> pa;
 #pragma unroll
     for (int r = 0; r <= PD; ++r)
@@ -393,7 +523,7 @@ __global__ __launch_bounds__(256) void k_adj_boundary(nsplat_curves cv, Work w, 
 #pragma unroll
     for (int k = 0; k < 2 * PD; ++k) pa.knot[k] = 0.0;
     pa.ubar = 0.0;
-    double cur[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    double da = 0.0, db = 0.0;
     int c = 0, span = 0;
     CurveView v;
     v.p = 0;
@@ -411,16 +541,15 @@ __global__ __launch_bounds__(256) void k_adj_boundary(nsplat_curves cv, Work w, 
         const double u = sample_u(v.U[v.p], v.U[v.m - v.p], j, nb, true, &dt);
         span = find_span(v.U, v.p, v.m, u);
         point_adjoint(cv, v, u, span, ab, pa);
-        cur[4] = pa.ubar * (1.0 - dt);
-        cur[5] = pa.ubar * dt;
+        da = pa.ubar * (1.0 - dt);
+        db = pa.ubar * dt;
         kspan = (int64_t)v.t0 + (int64_t)c * KNOT_PAD + span;
-        kcur = c;
       }
     }
-    const bool any = __ballot(act) != 0ull;
-    accumulate_points(w, kspan, c, v, span, pa, any);
-    if (any) accumulate_curve(w, kcur, c, v, cur);
+    accumulate_points(w, &sums[threadIdx.x >> 6], act, kspan, c, v, span, pa);
+    dom.add(w, act, c, v, da, db);
   }
+  dom.flush(w);
 }
 
 // One block per curve: colour / opacity sums to FP32, control-point adjoints
@@ -548,39 +677,20 @@ constexpr int MAXR = 3;  // highest derivative order of the derivative loss
 // basis functions entering the Cox-de Boor triangle at its level p - k.  With
 // `up` set, the reverse pass starts from the given adjoint up[0..1] of
 // C^(r)(u) instead of that of the value (whose scale is then unused).
-template <int PD>
-__device__ inline double deriv_adjoint(const nsplat_curves& cv, const CurveView& v, double u, int span, int r,
-                                       double scale, PtAdj<PD>& out, const double* up = nullptr) {
-  const double* U = v.U;
-  const int p = v.p;
-  const int R = r < p ? r : p;
-  double tri[tri_n(PD)];
-  double N[PD + 1], left[PD + 1], right[PD + 1];
-  N[0] = 1.0;
-  tri[0] = 1.0;
+template <int PD, int P>
+__device__ inline double deriv_adjoint_deg(const nsplat_curves& cv, const CurveView& v, double u, int span, int r,
+                                           double scale, PtAdj<PD>& out, const double* up) {
+  constexpr int RM = MAXR < P ? MAXR : P;  // derivatives above the degree vanish
+  double tri[tri_n(P)], left[P + 1], right[P + 1], inv[inv_n(P)];
+  basis_triangle<P>(v.U, span, u, left, right, inv, tri);
+  // PK_k[j]'s denominator U[span + j + 1] - U[span - P + j + k] is entry j of
+  // level P - k + 1 of the triangle
+  constexpr auto lvl = [](int k) { return (P - k + 1) * (P - k) / 2; };
+  double X[P + 1], Y[P + 1], Wt[P + 1];
+  double PK[RM + 1][P + 1][3];
 #pragma unroll
-  for (int d = 1; d <= PD; ++d) {
-    if (d > p) break;
-    left[d] = u - U[span + 1 - d];
-    right[d] = U[span + d] - u;
-    double saved = 0.0;
-#pragma unroll
-    for (int q = 0; q < d; ++q) {
-      const double temp = N[q] / (right[q + 1] + left[d - q]);
-      N[q] = saved + right[q + 1] * temp;
-      saved = left[d - q] * temp;
-    }
-    N[d] = saved;
-#pragma unroll
-    for (int q = 0; q <= d; ++q) tri[d * (d + 1) / 2 + q] = N[q];
-  }
-  double X[PD + 1], Y[PD + 1], Wt[PD + 1];
-  double PK[MAXR + 1][PD + 1][3];
-#pragma unroll
-  for (int j = 0; j <= PD; ++j) {
-    X[j] = Y[j] = Wt[j] = 0.0;
-    if (j > p) continue;
-    const int k = v.k0 + v.key_of_cp(span - p + j);
+  for (int j = 0; j <= P; ++j) {
+    const int k = v.k0 + v.key_of_cp(span - P + j);
     Wt[j] = (double)cv.key_w[k];
     X[j] = (double)cv.key_xy[2 * k];
     Y[j] = (double)cv.key_xy[2 * k + 1];
@@ -589,65 +699,62 @@ __device__ inline double deriv_adjoint(const nsplat_curves& cv, const CurveView&
     PK[0][j][2] = Wt[j];
   }
 #pragma unroll
-  for (int k = 1; k <= MAXR; ++k) {
-    if (k > R) break;
+  for (int k = 1; k <= RM; ++k)
 #pragma unroll
-    for (int j = 0; j < PD; ++j) {
-      if (j > p - k) break;
-      const double c = (double)(p - k + 1) / (U[span + j + 1] - U[span - p + j + k]);
+    for (int j = 0; j <= P - k; ++j) {
+      const double c = (double)(P - k + 1) * inv[lvl(k) + j];
 #pragma unroll
       for (int q = 0; q < 3; ++q) PK[k][j][q] = c * (PK[k - 1][j + 1][q] - PK[k - 1][j][q]);
     }
-  }
-  // (register arrays are indexed with compile-time indices only: the degree
-  // d = p - k is matched by an unrolled loop instead of computed)
   double S[MAXR + 1][3];
 #pragma unroll
   for (int k = 0; k <= MAXR; ++k) {
     S[k][0] = S[k][1] = S[k][2] = 0.0;
-    if (k > R) continue;
+    if (k > RM) continue;
 #pragma unroll
-    for (int d = 0; d <= PD; ++d) {
-      if (d != p - k) continue;
+    for (int j = 0; j <= P - k; ++j) {
+      const double n = tri[(P - k) * (P - k + 1) / 2 + j];
 #pragma unroll
-      for (int j = 0; j <= d; ++j) {
-        const double n = tri[d * (d + 1) / 2 + j];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) S[k][q] += n * PK[k][j][q];
-      }
+      for (int q = 0; q < 3; ++q) S[k][q] += n * PK[k][j][q];
     }
   }
   const double binom[MAXR + 1][MAXR + 1] = {{1, 0, 0, 0}, {1, 1, 0, 0}, {1, 2, 1, 0}, {1, 3, 3, 1}};
-  const double W0 = S[0][2];
+  const double iW0 = 1.0 / S[0][2];
   double Cx[MAXR + 1], Cy[MAXR + 1];
 #pragma unroll
   for (int k = 0; k <= MAXR; ++k) {
     Cx[k] = Cy[k] = 0.0;
     if (k > r) continue;
-    double ax = S[k][0], ay = S[k][1];  // zero for k > R
+    double ax = S[k][0], ay = S[k][1];  // zero above the degree
 #pragma unroll
     for (int i = 1; i <= MAXR; ++i) {
       if (i > k) break;
       ax -= binom[k][i] * S[i][2] * Cx[k - i];
       ay -= binom[k][i] * S[i][2] * Cy[k - i];
     }
-    Cx[k] = ax / W0;
-    Cy[k] = ay / W0;
+    Cx[k] = ax * iW0;
+    Cy[k] = ay * iW0;
   }
-  const double value = scale * (Cx[r] * Cx[r] + Cy[r] * Cy[r]);
+  // (register arrays are indexed with compile-time indices only)
+  double crx = Cx[0], cry = Cy[0];
+#pragma unroll
+  for (int k = 1; k <= MAXR; ++k) {
+    crx = k == r ? Cx[k] : crx;
+    cry = k == r ? Cy[k] : cry;
+  }
+  const double value = scale * (crx * crx + cry * cry);
   // reverse: Leibniz rule
   double dCx[MAXR + 1], dCy[MAXR + 1], dS[MAXR + 1][3];
 #pragma unroll
   for (int k = 0; k <= MAXR; ++k) {
-    dCx[k] = dCy[k] = 0.0;
+    dCx[k] = k == r ? (up ? up[0] : 2.0 * scale * crx) : 0.0;
+    dCy[k] = k == r ? (up ? up[1] : 2.0 * scale * cry) : 0.0;
     dS[k][0] = dS[k][1] = dS[k][2] = 0.0;
   }
-  dCx[r] = up ? up[0] : 2.0 * scale * Cx[r];
-  dCy[r] = up ? up[1] : 2.0 * scale * Cy[r];
 #pragma unroll
   for (int k = MAXR; k >= 0; --k) {
     if (k > r) continue;
-    const double gx = dCx[k] / W0, gy = dCy[k] / W0;
+    const double gx = dCx[k] * iW0, gy = dCy[k] * iW0;
     dS[k][0] += gx;
     dS[k][1] += gy;
 #pragma unroll
@@ -659,111 +766,81 @@ __device__ inline double deriv_adjoint(const nsplat_curves& cv, const CurveView&
     }
     dS[0][2] -= gx * Cx[k] + gy * Cy[k];
   }
-  // reverse: S^(k) = sum_j N_{p-k}[j] PK_k[j]
-  double dPK[MAXR + 1][PD + 1][3], dN[MAXR + 1][PD + 1];
-#pragma unroll
-  for (int k = 0; k <= MAXR; ++k)
-#pragma unroll
-    for (int j = 0; j <= PD; ++j) {
-      dN[k][j] = 0.0;
-      dPK[k][j][0] = dPK[k][j][1] = dPK[k][j][2] = 0.0;
-    }
-#pragma unroll
-  for (int k = 0; k <= MAXR; ++k) {
-    if (k > R) continue;
-#pragma unroll
-    for (int d = 0; d <= PD; ++d) {
-      if (d != p - k) continue;
-#pragma unroll
-      for (int j = 0; j <= d; ++j) {
-        const double n = tri[d * (d + 1) / 2 + j];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) dPK[k][j][q] = n * dS[k][q];
-        dN[k][j] = dS[k][0] * PK[k][j][0] + dS[k][1] * PK[k][j][1] + dS[k][2] * PK[k][j][2];
-      }
-    }
-  }
-  // reverse: derivative control points; knot slot s <-> knot index span - PD + 1 + s
+  // reverse, level by level from the highest derivative: S^(k) =
+  // sum_j N_{P-k}[j] PK_k[j] gives the adjoint of PK_k (A, joined by what the
+  // level above sends down) and of the degree P - k functions (dN); knot slot
+  // s <-> knot index span - PD + 1 + s
 #pragma unroll
   for (int k = 0; k < 2 * PD; ++k) out.knot[k] = 0.0;
+  double A[P + 1][3], dN[RM + 1][P + 1];
 #pragma unroll
-  for (int k = MAXR; k >= 1; --k) {
-    if (k > R) continue;
+  for (int k = RM; k >= 0; --k) {
+    double B[P + 1][3];
 #pragma unroll
-    for (int j = 0; j < PD; ++j) {
-      if (j > p - k) break;
-      const int hi = span + j + 1, lo = span - p + j + k;
-      const double D = U[hi] - U[lo];
-      const double c = (double)(p - k + 1) / D;
-      double dD = 0.0;
+    for (int j = 0; j <= P - k; ++j) {
+      const double n = tri[(P - k) * (P - k + 1) / 2 + j];
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        dPK[k - 1][j + 1][q] += c * dPK[k][j][q];
-        dPK[k - 1][j][q] -= c * dPK[k][j][q];
-        dD -= dPK[k][j][q] * PK[k][j][q];
-      }
-      dD /= D;
-      out.knot[j + PD] += dD;  // slot of knot hi = span + j + 1
-#pragma unroll
-      for (int sl = 0; sl < 2 * PD; ++sl)
-        if (sl == lo - span + PD - 1) out.knot[sl] -= dD;
+      for (int q = 0; q < 3; ++q) B[j][q] = n * dS[k][q];
+      dN[k][j] = dS[k][0] * PK[k][j][0] + dS[k][1] * PK[k][j][1] + dS[k][2] * PK[k][j][2];
     }
+    if (k < RM) {
+#pragma unroll
+      for (int j = 0; j <= P - k - 1; ++j) {
+        const double iD = inv[lvl(k + 1) + j], c = (double)(P - k) * iD;
+        double dD = 0.0;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          B[j + 1][q] += c * A[j][q];
+          B[j][q] -= c * A[j][q];
+          dD -= A[j][q] * PK[k + 1][j][q];
+        }
+        dD *= iD;
+        out.knot[j + PD] += dD;              // knot span + j + 1
+        out.knot[j + k + PD - P] -= dD;      // knot span - P + j + k + 1
+      }
+    }
+#pragma unroll
+    for (int j = 0; j <= P - k; ++j)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) A[j][q] = B[j][q];
   }
   // homogeneous control points -> (x, y, w); the width does not enter
 #pragma unroll
   for (int j = 0; j <= PD; ++j) {
     out.cp[j][0] = out.cp[j][1] = out.cp[j][2] = out.cp[j][3] = 0.0;
-    if (j > p) continue;
-    out.cp[j][0] = Wt[j] * dPK[0][j][0];
-    out.cp[j][1] = Wt[j] * dPK[0][j][1];
-    out.cp[j][2] = X[j] * dPK[0][j][0] + Y[j] * dPK[0][j][1] + dPK[0][j][2];
+    if (j > P) continue;
+    out.cp[j][0] = Wt[j] * A[j][0];
+    out.cp[j][1] = Wt[j] * A[j][1];
+    out.cp[j][2] = X[j] * A[j][0] + Y[j] * A[j][1] + A[j][2];
   }
-  // reverse through the Cox-de Boor triangle (as point_adjoint), the degree
-  // p - k adjoint dN[k] joining at level p - k
-  double Nb[PD + 1];
+  // reverse through the Cox-de Boor triangle, the degree P - k adjoint dN[k]
+  // joining at level P - k (zero above min(r, P))
+  double Nb[P + 1];
 #pragma unroll
-  for (int q = 0; q <= PD; ++q) Nb[q] = dN[0][q];
+  for (int q = 0; q <= P; ++q) Nb[q] = dN[0][q];
   double ub = 0.0;
 #pragma unroll
-  for (int d = PD; d >= 1; --d) {
-    if (d > p) continue;
+  for (int d = P; d >= 1; --d) {
+    if (P - d >= 1 && P - d <= RM) {
 #pragma unroll
-    for (int k = 1; k <= MAXR; ++k)
-      if (k <= R && d == p - k) {
-#pragma unroll
-        for (int q = 0; q <= PD; ++q) Nb[q] += dN[k][q];
-      }
-    double Np[PD + 1];
-#pragma unroll
-    for (int q = 0; q <= PD; ++q) Np[q] = 0.0;
-#pragma unroll
-    for (int q = 0; q <= d; ++q) {
-      const double nb = Nb[q];
-      const int i = span - d + q;
-      if (q >= 1) {
-        const double Ui = U[i], Uid = U[i + d];
-        const double D = Uid - Ui;
-        Np[q - 1] += nb * (u - Ui) / D;
-        const double g = nb * tri[(d - 1) * d / 2 + q - 1];
-        ub += g / D;
-        out.knot[PD - 1 - d + q] -= g * (Uid - u) / (D * D);
-        out.knot[PD - 1 + q] -= g * (u - Ui) / (D * D);
-      }
-      if (q <= d - 1) {
-        const double Ui1 = U[i + 1], Uid1 = U[i + d + 1];
-        const double D = Uid1 - Ui1;
-        Np[q] += nb * (Uid1 - u) / D;
-        const double g = nb * tri[(d - 1) * d / 2 + q];
-        ub -= g / D;
-        out.knot[PD + q] += g * (u - Ui1) / (D * D);
-        out.knot[PD - d + q] += g * (Uid1 - u) / (D * D);
-      }
+      for (int q = 0; q <= d; ++q) Nb[q] += dN[P - d][q];
     }
-#pragma unroll
-    for (int q = 0; q <= PD; ++q) Nb[q] = Np[q];
+    triangle_reverse<PD, P>(d, left, right, inv, tri, Nb, ub, out.knot);
   }
   out.ubar = ub;
   return value;
+}
+
+template <int PD>
+__device__ inline double deriv_adjoint(const nsplat_curves& cv, const CurveView& v, double u, int span, int r,
+                                       double scale, PtAdj<PD>& out, const double* up = nullptr) {
+  if constexpr (PD >= 5) {
+    if (v.p == 5) return deriv_adjoint_deg<PD, 5>(cv, v, u, span, r, scale, out, up);
+    if (v.p == 4) return deriv_adjoint_deg<PD, 4>(cv, v, u, span, r, scale, out, up);
+  }
+  if (v.p == 3) return deriv_adjoint_deg<PD, 3>(cv, v, u, span, r, scale, out, up);
+  if (v.p == 2) return deriv_adjoint_deg<PD, 2>(cv, v, u, span, r, scale, out, up);
+  return deriv_adjoint_deg<PD, 1>(cv, v, u, span, r, scale, out, up);
 }
 
 // Penalty of Eq. 12 and its derivative: ReLU (kind 0) or softplus (kind 1).
@@ -852,23 +929,26 @@ __device__ inline void block_loss(double a, double b, float* loss) {
   }
 }
 
+// Registers for one wavefront per SIMD: held to two (256 VGPRs) the derivative
+// adjoint spills about 110 to scratch (1.8M samples: 0.261 ms against 0.254;
+// 0.375 before the fixed degrees, the reciprocals and the LDS sums).
 // Stroke samples (one lane per stroke Gaussian; endpoint copies skipped): the
 // box gradient joins the Gaussian's centre adjoint, the derivative loss goes
 // straight to the control points, knots and domain ends.
 template <int PD>
-__global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_stroke(nsplat_curves cv, Work w, RegArgs ra, const int32_t* plan,
+__global__ __launch_bounds__(256, 1) void k_reg_stroke(nsplat_curves cv, Work w, RegArgs ra, const int32_t* plan,
                                                     const int32_t* counters, const Gauss* __restrict__ gs,
-                                                    int kappa) {
+                                                    int kappa, int run) {
+  __shared__ PointSums<PD> sums[4];
   if (w.queue[Q_NSTROKE] == 0) return;  // no Gaussians of this kind
   const int64_t G = counters[NSPLAT_CNT_GAUSS];
   const int lane = __lane_id();
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) - lane;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   double lb = 0.0, ld = 0.0;
-  for (int64_t base = wave0; base < G; base += stride) {
-    const int64_t g = base + lane;
-    int64_t kspan = -1 - lane, kcur = -1 - lane;
-    double cur[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  DomainSums dom;
+  for (GroupWalk gw(run); gw.base < G; gw.next()) {
+    const int64_t g = gw.base + lane;
+    int64_t kspan = 0;
+    double da = 0.0, db = 0.0;
     PtAdj<PD> pa;
     int c = 0, span = 0;
     CurveView v;
@@ -898,10 +978,9 @@ __global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_stroke(nsplat_curv
           const double sc = ra.deriv_weight / (double)curves_in_scene(cv, cv.scene[c]) *
                             quad_weight(j, M, v.closed());
           ld += deriv_adjoint(cv, v, u, span, ra.deriv_order, sc, pa);
-          cur[4] = pa.ubar * (1.0 - dt);
-          cur[5] = pa.ubar * dt;
+          da = pa.ubar * (1.0 - dt);
+          db = pa.ubar * dt;
           kspan = (int64_t)v.t0 + (int64_t)c * KNOT_PAD + span;
-          kcur = c;
         }
       }
     }
@@ -913,28 +992,28 @@ __global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_stroke(nsplat_curv
 #pragma unroll
       for (int k = 0; k < 2 * PD; ++k) pa.knot[k] = 0.0;
     }
-    const bool any = __ballot(act) != 0ull;
-    accumulate_points(w, kspan, c, v, span, pa, any);
-    if (any) accumulate_curve(w, kcur, c, v, cur);
+    accumulate_points(w, &sums[threadIdx.x >> 6], act, kspan, c, v, span, pa);
+    dom.add(w, act, c, v, da, db);
   }
+  dom.flush(w);
   block_loss(lb, ld, ra.loss);
 }
 
 // Fill boundary samples (one lane per boundary point): the box gradient joins
 // the boundary-point adjoint, the derivative loss goes straight to the curve.
 template <int PD>
-__global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_boundary(nsplat_curves cv, Work w, RegArgs ra, const int32_t* plan,
+__global__ __launch_bounds__(256, 1) void k_reg_boundary(nsplat_curves cv, Work w, RegArgs ra, const int32_t* plan,
                                                       const int32_t* counters) {
+  __shared__ PointSums<PD> sums[4];
   const int64_t NB = counters[NSPLAT_CNT_BOUND];
   const int lane = __lane_id();
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) - lane;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int n = cv.n_curves;
   double lb = 0.0, ld = 0.0;
-  for (int64_t base = wave0; base < NB; base += stride) {
-    const int64_t bi = base + lane;
-    int64_t kspan = -1 - lane, kcur = -1 - lane;
-    double cur[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  DomainSums dom;
+  for (GroupWalk gw(1); gw.base < NB; gw.next()) {
+    const int64_t bi = gw.base + lane;
+    int64_t kspan = 0;
+    double da = 0.0, db = 0.0;
     PtAdj<PD> pa;
     int c = 0, span = 0;
     CurveView v;
@@ -962,10 +1041,9 @@ __global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_boundary(nsplat_cu
           span = find_span(v.U, v.p, v.m, u);
           const double sc = ra.deriv_weight / (double)curves_in_scene(cv, cv.scene[c]) * quad_weight(j, nb, true);
           ld += deriv_adjoint(cv, v, u, span, ra.deriv_order, sc, pa);
-          cur[4] = pa.ubar * (1.0 - dt);
-          cur[5] = pa.ubar * dt;
+          da = pa.ubar * (1.0 - dt);
+          db = pa.ubar * dt;
           kspan = (int64_t)v.t0 + (int64_t)c * KNOT_PAD + span;
-          kcur = c;
         }
       }
     }
@@ -977,10 +1055,10 @@ __global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_boundary(nsplat_cu
 #pragma unroll
       for (int k = 0; k < 2 * PD; ++k) pa.knot[k] = 0.0;
     }
-    const bool any = __ballot(act) != 0ull;
-    accumulate_points(w, kspan, c, v, span, pa, any);
-    if (any) accumulate_curve(w, kcur, c, v, cur);
+    accumulate_points(w, &sums[threadIdx.x >> 6], act, kspan, c, v, span, pa);
+    dom.add(w, act, c, v, da, db);
   }
+  dom.flush(w);
   block_loss(lb, ld, ra.loss);
 }
 
@@ -994,19 +1072,19 @@ __global__ __launch_bounds__(256, PD <= 3 ? 2 : 1) void k_reg_boundary(nsplat_cu
 // the derivative loss; dL/d du = dL/dsigma |C'| / rho goes to the domain
 // ends (du = (u_{m-p} - u_p) / (M - 1), or / M closed).
 template <int PD>
-__global__ __launch_bounds__(256) void k_adj_aniso(nsplat_curves cv, nsplat_params pr, Work w,
+__global__ __launch_bounds__(256, 1) void k_adj_aniso(nsplat_curves cv, nsplat_params pr, Work w,
                                                    const int32_t* plan, const int32_t* counters,
                                                    const Gauss* __restrict__ gs) {
+  __shared__ PointSums<PD> sums[4];
   if (w.queue[Q_NANISO] == 0) return;  // no Gaussians of this kind
   const int64_t G = counters[NSPLAT_CNT_GAUSS];
   const int lane = __lane_id();
-  const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) - lane;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const double rho = (double)pr.rho;
-  for (int64_t base = wave0; base < G; base += stride) {
-    const int64_t g = base + lane;
-    int64_t kspan = -1 - lane, kcur = -1 - lane;
-    double cur[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  DomainSums dom;
+  for (GroupWalk gw(1); gw.base < G; gw.next()) {
+    const int64_t g = gw.base + lane;
+    int64_t kspan = 0;
+    double da = 0.0, db = 0.0;
     PtAdj<PD> pa;
     int c = 0, span = 0;
     CurveView v;
@@ -1055,10 +1133,9 @@ __global__ __launch_bounds__(256) void k_adj_aniso(nsplat_curves cv, nsplat_para
           for (int k = 0; k < 2 * PD; ++k) pa.knot[k] += pd.knot[k];
           pa.ubar += pd.ubar;
         }
-        cur[4] = pa.ubar * (1.0 - dt) - ddu / den;  // u_j = u_p + t_j (u_{m-p} - u_p)
-        cur[5] = pa.ubar * dt + ddu / den;
+        da = pa.ubar * (1.0 - dt) - ddu / den;  // u_j = u_p + t_j (u_{m-p} - u_p)
+        db = pa.ubar * dt + ddu / den;
         kspan = (int64_t)v.t0 + (int64_t)c * KNOT_PAD + span;
-        kcur = c;
       }
     }
     if (!act) {
@@ -1069,10 +1146,10 @@ __global__ __launch_bounds__(256) void k_adj_aniso(nsplat_curves cv, nsplat_para
 #pragma unroll
       for (int k = 0; k < 2 * PD; ++k) pa.knot[k] = 0.0;
     }
-    const bool any = __ballot(act) != 0ull;
-    accumulate_points(w, kspan, c, v, span, pa, any);
-    if (any) accumulate_curve(w, kcur, c, v, cur);
+    accumulate_points(w, &sums[threadIdx.x >> 6], act, kspan, c, v, span, pa);
+    dom.add(w, act, c, v, da, db);
   }
+  dom.flush(w);
 }
 
 }  // namespace
@@ -1102,10 +1179,15 @@ hipError_t launch_zero_grads(const Launch& L) {
 // no degree above 3 (curve_valid rejects any curve above the bound).
 inline bool low_degree(const Launch& L) { return L.cv->max_degree >= 1 && L.cv->max_degree <= 3; }
 
+// Groups of 64 samples that a wavefront of the stroke adjoints takes in a row
+// (see DomainSums): four where that still leaves two wavefronts per SIMD, one
+// below, where the launch would lose wavefronts it needs.
+inline int sample_run(const Launch& L) { return L.bf->caps.gauss >= (int64_t)4 * 64 * 8 * L.n_cu ? 4 : 1; }
+
 template <int PD>
 void launch_reg_d(const Launch& L, const RegArgs& ra) {
-  hipLaunchKernelGGL(k_reg_stroke<PD>, dim3(grid_for(L.bf->caps.gauss, 256, 4096)), dim3(256), 0, L.stream, *L.cv,
-                     L.w, ra, L.bf->plan, L.bf->counters, (const Gauss*)L.bf->gauss, L.pr->kappa);
+  hipLaunchKernelGGL(k_reg_stroke<PD>, dim3(grid_for(L.bf->caps.gauss, 256 * sample_run(L), 4096)), dim3(256), 0, L.stream, *L.cv,
+                     L.w, ra, L.bf->plan, L.bf->counters, (const Gauss*)L.bf->gauss, L.pr->kappa, sample_run(L));
   if (L.bf->caps.boundary > 0)
     hipLaunchKernelGGL(k_reg_boundary<PD>, dim3(grid_for(L.bf->caps.boundary, 256, 4096)), dim3(256), 0, L.stream,
                        *L.cv, L.w, ra, L.bf->plan, L.bf->counters);
@@ -1113,8 +1195,8 @@ void launch_reg_d(const Launch& L, const RegArgs& ra) {
 
 template <int PD>
 void launch_adj_stroke_d(const Launch& L) {
-  hipLaunchKernelGGL(k_adj_stroke<PD>, dim3(grid_for(L.bf->caps.gauss, 256, 8192)), dim3(256), 0, L.stream, *L.cv,
-                     *L.pr, L.w, L.bf->plan, L.bf->counters, (const Gauss*)L.bf->gauss);
+  hipLaunchKernelGGL(k_adj_stroke<PD>, dim3(grid_for(L.bf->caps.gauss, 256 * sample_run(L), 8192)), dim3(256), 0, L.stream, *L.cv,
+                     *L.pr, L.w, L.bf->plan, L.bf->counters, (const Gauss*)L.bf->gauss, sample_run(L));
 }
 
 template <int PD>

@@ -161,9 +161,8 @@ struct CurveView {
   // Closed curves wrap the last ceil(p/2) key points in front (Sec. 3.1).
   __device__ int key_of_cp(int j) const {
     if (!closed()) return j;
-    int k = j - (p + 1) / 2;
-    k %= nk;
-    return k < 0 ? k + nk : k;
+    const int k = j - (p + 1) / 2;  // 0 <= j < nk + p and nk > p: one turn at most either way
+    return k < 0 ? k + nk : (k >= nk ? k - nk : k);
   }
 };
 

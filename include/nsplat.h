@@ -200,6 +200,8 @@ typedef struct {
                        else chosen by nsplat_bin on the device from the pair
                        count (about pairs x quadrants per tile / (8 x compute
                        units), rounded to a power of two in [512, 8192]).
+                       At 0 the forward may also take a long list with
+                       several wavefronts, depending on the pair count.
                        It only changes FP32 rounding.                        */
   const float* h_dev; /* (dev, optional) if non-NULL the grid step is read
                          from here, so a captured graph can anneal it        */

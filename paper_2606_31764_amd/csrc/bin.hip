@@ -548,7 +548,7 @@ __global__ __launch_bounds__(256) void k_order_count(const int32_t* __restrict__
   if (threadIdx.x < 32 && h[threadIdx.x] > 0) atomicAdd(&obin[threadIdx.x], h[threadIdx.x]);
 }
 
-__global__ void k_order_scan(int32_t* obin) {
+__global__ void k_order_scan(int32_t* obin, int32_t* queue, const int32_t* counters, int split, int quads, int n_cu) {
   const int l = threadIdx.x;
   const int v = l < 32 ? obin[l] : 0;
   int incl = v;
@@ -558,6 +558,7 @@ __global__ void k_order_scan(int32_t* obin) {
     if (l >= off) incl += o;
   }
   if (l < 32) obin[32 + l] = incl - v;
+  if (l == long_class(counters[NSPLAT_CNT_PAIRS], quads, n_cu)) queue[Q_NLONG] = split ? incl : 0;
 }
 
 __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict__ ranges, int n_tiles,
@@ -650,7 +651,8 @@ __device__ inline uint32_t plan_wave_scan(uint32_t v) {
 // starts (or at the pair count); empty tiles get [0, 0).
 __global__ __launch_bounds__(PLAN_THREADS) void k_tile_plan(int32_t* __restrict__ ranges, int n_tiles, int quads,
                                                             int blocks, const SceneTab* st, int n_scenes,
-                                                            int ck_arg, int n_cu, int32_t* __restrict__ queue,
+                                                            int ck_arg, int split, int n_cu,
+                                                            int32_t* __restrict__ queue,
                                                             int32_t* __restrict__ order, int32_t* __restrict__ ck_off,
                                                             int32_t* __restrict__ item_off,
                                                             const uint32_t* __restrict__ hist, int sb, int nd,
@@ -688,6 +690,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_tile_plan(int32_t* __restrict_
     if (tid < 32) {
       base[tid] = incl - v;
       h[tid] = 0;
+      if (tid == long_class(counters[NSPLAT_CNT_PAIRS], quads, n_cu)) queue[Q_NLONG] = split ? incl : 0;
     }
   }
   __syncthreads();
@@ -755,6 +758,7 @@ hipError_t launch_bin(const Launch& L) {
   int32_t* cnt = L.bf->counters;
   const Gauss* gs = (const Gauss*)L.bf->gauss;
   const int gg = grid_for(gcap, 256, 8192);
+  const int split = split_long(*L.pr);
   // number of key bits and radix passes (up to RADIX_BITS_MAX bits each)
   int key_bits = 0;
   while (key_bits < 31 && ((int64_t)1 << key_bits) < L.n_tiles) ++key_bits;
@@ -799,7 +803,7 @@ hipError_t launch_bin(const Launch& L) {
       Phase ph(L, NSPLAT_T_RANGES);
       hipLaunchKernelGGL(k_tile_plan, dim3(1), dim3(PLAN_THREADS), 0, L.stream, L.bf->ranges, (int)L.n_tiles,
                          L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, L.ck_lg,
-                         L.n_cu, L.w.queue, L.w.order, L.w.ck_off, L.w.item_off,
+                         split, L.n_cu, L.w.queue, L.w.order, L.w.ck_off, L.w.item_off,
                          (const uint32_t*)L.w.hist, nbk, nd, cnt, 1);
       return hipGetLastError();
     }
@@ -849,12 +853,13 @@ hipError_t launch_bin(const Launch& L) {
     if (nt > 0 && nt <= SMALL_TILES) {
       hipLaunchKernelGGL(k_tile_plan, dim3(1), dim3(PLAN_THREADS), 0, L.stream, L.bf->ranges, nt,
                          L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, L.ck_lg,
-                         L.n_cu, L.w.queue, L.w.order, L.w.ck_off, L.w.item_off,
+                         split, L.n_cu, L.w.queue, L.w.order, L.w.ck_off, L.w.item_off,
                          from_hist ? (const uint32_t*)L.w.hist : nullptr, sb, 1 << key_bits, cnt, 0);
     } else if (nt > 0) {
       hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, L.stream, L.w.obin, 0, (int64_t)64);
       hipLaunchKernelGGL(k_order_count, dim3(ob), dim3(256), 0, L.stream, L.bf->ranges, nt, L.w.obin);
-      hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, L.stream, L.w.obin);
+      hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, L.stream, L.w.obin, L.w.queue, cnt, split,
+                         L.pr->tile == 8 ? 1 : 4, L.n_cu);
       hipLaunchKernelGGL(k_order_scatter, dim3(ob), dim3(256), 0, L.stream, L.bf->ranges, nt, L.w.obin, L.w.order);
       const int cb = grid_for(nt, 256, 4096);
       hipLaunchKernelGGL(k_chunk_counts, dim3(cb), dim3(256), 0, L.stream, L.bf->ranges, nt, L.ck_lg, cnt,

@@ -1,8 +1,9 @@
 // nsplat_forward / the first half of nsplat_backward: per-tile alpha
 // compositing (Sec. 3.4, Eq. 8-9) and its adjoint.
 //
-// The forward's unit of work is one wavefront per (tile, quadrant): see
-// TileCfg below.  Centres become exact tile-local FP32 coordinates when an
+// The forward's unit of work is one wavefront per (tile, quadrant), or, for
+// the long lists of small launches, one block (fwd_serial, fwd_block).
+// Centres become exact tile-local FP32 coordinates when an
 // entry is loaded (FP64 centre minus the tile origin, rounded once).  The
 // forward stops a pixel once T < eps_T and a wavefront once all its pixels
 // have stopped, and stores each pixel's state at every chunk boundary (a
@@ -21,9 +22,9 @@ namespace {
 // Work decomposition: one wavefront per (tile, quadrant) item.  8x8 tiles are
 // one quadrant; 16x16 and 32x32 tiles have four (8x8 or 16x16 pixels), and
 // each lane owns a BLK x BLK block of its quadrant.  A wavefront walks the
-// tile's list in steps of up to 64 E entries: every lane loads E entries (the
-// next step's loads are issued before the current step is processed),
-// entries whose support disc misses the quadrant are dropped, the rest are
+// tile's list in steps of up to 64 entries (64 E in the adjoint): every lane
+// loads one (E; the next step's loads are issued before the current step is
+// processed), entries whose support disc misses the quadrant are dropped, the rest are
 // compacted in order into the wavefront's own LDS arrays and then composited
 // one after another.  Wavefronts never wait for each other.
 template <int TILE>
@@ -368,139 +369,103 @@ __device__ inline int step_floor(int h, int start, int depth, int end, int ck_lg
   return max(max(start, h - depth), end - ((k + 1) << ck_lg));
 }
 
-template <int C, int TILE, int E, int KIND>
-__global__ __launch_bounds__(BLOCK, E == 1 ? 4 : 1) void k_blend_fwd(
-    nsplat_curves cv, nsplat_params pr, Work w, int n_scenes, int n_items, const Gauss* __restrict__ gs,
-    const int32_t* __restrict__ ranges, const int32_t* __restrict__ idx, const float* __restrict__ bg,
-    float* __restrict__ image, float* __restrict__ Tfin, int32_t* __restrict__ nlast, const int32_t* __restrict__ plan,
-    int64_t gcap, int persistent, int ck_arg) {
+// A (tile, quadrant) of the forward.
+struct FwdItem {
+  SceneTab st;
+  int s, tile, quad, lt, x0, y0, start, end;
+};
+
+// A staged tangent-aligned entry takes its axis u and ratio r.
+__device__ inline void convert_aniso(const float4* __restrict__ gaux, FwdRec& rec) {
+  const float4 ax = gaux[rec.g];
+  float ux, uy, rq;
+  aniso_axes(ax, rec.geo.w, &ux, &uy, &rq);
+  rec.geo.z = ux;
+  rec.geo.w = uy;
+  rec.g = __float_as_int(rq);
+}
+
+// One (tile, quadrant) on one wavefront, with its own LDS slice (64 entries).
+// Bound by vector instructions, a dozen per entry and pixel: where the GPU is
+// full, at 4.5 cycles each per SIMD; the longest list alone, at 38 to 47 ns an
+// entry (fwd_block is for those).  A pixel's stopping position is taken from
+// its last composited entry at the end of a step rather than selected at every
+// entry, one compare and one LDS word less: 16 x 2000 key points at 1024^2
+// 0.322 -> 0.305 ms, 200 mixed curves at 777 x 1003 0.190 -> 0.182, 16 mixed
+// scenes in 32 x 32 tiles 0.763 -> 0.704.  Steps are never longer than 64
+// (params.batch above 64 is the adjoint's): two or four entries per lane only
+// took registers and LDS from other wavefronts.
+template <int C, int TILE, int KIND>
+__device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& w, const FwdItem& im,
+                                           const Gauss* __restrict__ gs, const int32_t* __restrict__ idx,
+                                           const float* __restrict__ bg, float* __restrict__ image,
+                                           float* __restrict__ Tfin, int32_t* __restrict__ nlast,
+                                           const int32_t* __restrict__ plan, int64_t gcap, int ck_lg,
+                                           bool fill_lattice, char* mine_lds) {
   using Cfg = TileCfg<TILE>;
   constexpr int PPT = Cfg::PPT;
-  extern __shared__ __align__(16) char smem[];
-  typedef const __attribute__((address_space(4))) int32_t* const_i32;
-  // the chunk length: the caller's, or the one the binning chose
-  const int ck_lg = ck_arg >= 0 ? ck_arg : ((const_i32)w.queue)[Q_CKLG];
-  const int depth = min(pr.batch, 64 * E);   // entries per step (E per lane; fewer lanes below 64)
-  const float amax = pr.alpha_max, eps = pr.eps_T, ks = pr.k_sigma;
-  const int lane = __lane_id(), wv = threadIdx.x >> 6;
-  char* mine_lds = smem + (size_t)wv * (64 * E) * FWD_ENTRY_BYTES;
-  FwdRec* wrec = (FwdRec*)mine_lds;
-  float4* wcol = (float4*)(wrec + 64 * E);  // colour
-  const uint64_t below = lanes_below();
   constexpr bool ANI = (KIND & KIND_ANI) != 0;
-  // fill runs at h = 1 walk each pixel's lattice neighbours (see FillRun);
-  // the support radius must be the 4.5 the offsets are laid out for
-  const bool fill_lattice = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
+  const float amax = pr.alpha_max, eps = pr.eps_T, ks = pr.k_sigma;
   const float inv_tile = 1.0f / (float)TILE;
-  for (int it = 0;; ++it) {
-    const int item = next_item(it, persistent, w.queue);
-    if (item >= n_items) break;
-    const int tq = item / Cfg::QUADS, quad = item - tq * Cfg::QUADS;
-    const int tile = w.order[tq];
-    const int s = scene_of_tile(w.scenes, n_scenes, tile);
-    const SceneTab st = w.scenes[s];
-    const int lt = tile - st.tile_off;
-    const int x0 = (lt % st.tiles_x) * TILE, y0 = (lt / st.tiles_x) * TILE;
-    // The colour is accumulated per run of entries of one curve (one
-    // colour): over a run, sum alpha_j T_j = T at its start - T now
-    // (alpha_j T_j = T_j - T_{j+1}), so each pixel keeps Tst, its T where the
-    // run began, and adds col (Tst - T) where the run ends.  Runs end where
-    // the curve changes between consecutive composited entries, at chunk
-    // boundaries and at the end, all fixed by the list, so the result does not
-    // depend on the batch depth.
-    float px[PPT], py[PPT], T[PPT], Tst[PPT], acc[PPT][3];
-    int stop[PPT];
-    int run_curve = -1, run_kind = 0;
-    float rc0 = 0.0f, rc1 = 0.0f, rc2 = 0.0f;  // the run's colour
-    const int start = ranges[2 * tile], end = ranges[2 * tile + 1];
+  const int depth = min(pr.batch, 64);  // entries per step
+  const int lane = __lane_id();
+  const uint64_t below = lanes_below();
+  FwdRec* wrec = (FwdRec*)mine_lds;
+  float4* wcol = (float4*)(wrec + 64);  // colour
+  const int s = im.s, tile = im.tile, quad = im.quad, lt = im.lt, x0 = im.x0, y0 = im.y0, start = im.start,
+            end = im.end;
+  const SceneTab st = im.st;
+  // The colour is accumulated per run of entries of one curve (one
+  // colour): over a run, sum alpha_j T_j = T at its start - T now
+  // (alpha_j T_j = T_j - T_{j+1}), so each pixel keeps Tst, its T where the
+  // run began, and adds col (Tst - T) where the run ends.  Runs end where
+  // the curve changes between consecutive composited entries, at chunk
+  // boundaries and at the end, all fixed by the list, so the result does not
+  // depend on the batch depth.
+  float px[PPT], py[PPT], T[PPT], Tst[PPT], acc[PPT][3];
+  int stop[PPT];
+  int run_curve = -1, run_kind = 0;
+  float rc0 = 0.0f, rc1 = 0.0f, rc2 = 0.0f;  // the run's colour
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      int lx, ly;
-      pixel_of<TILE>(quad, lane, q, &lx, &ly);
-      px[q] = (float)lx;
-      py[q] = (float)ly;
-      // a pixel is live while T >= eps_T (0 <= eps_T <= 1): T only falls,
-      // and it falls below eps_T exactly at the entry where the pixel stops;
-      // pixels outside the image start at T = 0
-      T[q] = (x0 + lx < st.W && y0 + ly < st.H) ? 1.0f : 0.0f;
-      Tst[q] = T[q];
+  for (int q = 0; q < PPT; ++q) {
+    int lx, ly;
+    pixel_of<TILE>(quad, lane, q, &lx, &ly);
+    px[q] = (float)lx;
+    py[q] = (float)ly;
+    // a pixel is live while T >= eps_T (0 <= eps_T <= 1): T only falls,
+    // and it falls below eps_T exactly at the entry where the pixel stops;
+    // pixels outside the image start at T = 0
+    T[q] = (x0 + lx < st.W && y0 + ly < st.H) ? 1.0f : 0.0f;
+    Tst[q] = T[q];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) acc[q][c] = 0.0f;
-      stop[q] = start;
-    }
-    const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
-    const Box qbox = quad_box<TILE>(quad);
-    // front to back: list positions end-1 down to start, at most `depth` per
-    // step and never across a chunk boundary, where the state is stored
-    const int ck0 = w.ck_off[tile];
-    int n_ck = 0;  // chunk boundaries passed (state stored)
-    // loads run two steps ahead for the list indices and one step ahead for
-    // the records, so a step waits for one round trip, issued a step earlier
-    Entry e[E];
-    int gnext[E];  // Gaussian indices of the next step
-    int hi = end, lo_s = step_floor(hi, start, depth, end, ck_lg);
-    int nhi = lo_s, nlo = step_floor(nhi, start, depth, end, ck_lg);
+    for (int c = 0; c < 3; ++c) acc[q][c] = 0.0f;
+    stop[q] = start;
+  }
+  const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
+  const Box qbox = quad_box<TILE>(quad);
+  // front to back: list positions end-1 down to start, at most `depth` per
+  // step and never across a chunk boundary, where the state is stored
+  const int ck0 = w.ck_off[tile];
+  int n_ck = 0;  // chunk boundaries passed (state stored)
+  // loads run two steps ahead for the list indices and one step ahead for
+  // the records, so a step waits for one round trip, issued a step earlier
+  Entry e;
+  int gnext;  // Gaussian indices of the next step
+  int hi = end, lo_s = step_floor(hi, start, depth, end, ck_lg);
+  int nhi = lo_s, nlo = step_floor(nhi, start, depth, end, ck_lg);
+  load_entry(idx, gs, w.gcol, hi - 1 - lane, lane < hi - lo_s, &e);
+  gnext = lane < nhi - nlo ? idx[nhi - 1 - lane] : 0;
+  // One fill run's positions fr.p_lo .. top at h = 1, front to back for each
+  // pixel: the colour run, the chunk boundaries and the per-pixel
+  // arithmetic are those of the entry-by-entry path, entry for entry.
+  constexpr int FNB = Cfg::SUB + 2 * FR_R;  // lattice neighbourhood of the quadrant, per axis
+  constexpr int FNIT = (FNB * FNB + 63) / 64;
+  auto fill_run_fwd = [&](const FillRun& fr, int top, const float (&og)[FNIT]) {
+    constexpr int NB = FNB;
+    float* ol = (float*)mine_lds;            // [NB][NB] opacities (0: no Gaussian of the run waits there)
+    if (run_curve != fr.c) {                 // a run of this curve already open goes on
 #pragma unroll
-    for (int u = 0; u < E; ++u) {
-      const int k = u * 64 + lane;
-      load_entry(idx, gs, w.gcol, hi - 1 - k, k < hi - lo_s, &e[u]);
-      gnext[u] = k < nhi - nlo ? idx[nhi - 1 - k] : 0;
-    }
-    // One fill run's positions fr.p_lo .. top at h = 1, front to back for each
-    // pixel: the colour run, the chunk boundaries and the per-pixel
-    // arithmetic are those of the entry-by-entry path, entry for entry.
-    constexpr int FNB = Cfg::SUB + 2 * FR_R;  // lattice neighbourhood of the quadrant, per axis
-    constexpr int FNIT = (FNB * FNB + 63) / 64;
-    auto fill_run_fwd = [&](const FillRun& fr, int top, const float (&og)[FNIT]) {
-      constexpr int NB = FNB;
-      float* ol = (float*)mine_lds;            // [NB][NB] opacities (0: no Gaussian of the run waits there)
-      if (run_curve != fr.c) {                 // a run of this curve already open goes on
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-          const float a = Tst[q] - T[q];
-          acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-          if (C == 3) {
-            acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-            acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-          }
-          Tst[q] = T[q];
-        }
-        const float4 pc = w.gcol[fr.g_top];
-        rc0 = pc.x;
-        rc1 = pc.y;
-        rc2 = pc.z;
-        run_curve = fr.c;
-      }
-      const int qx = (quad & 1) * Cfg::SUB, qy = (quad >> 1) * Cfg::SUB;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-      for (int it = 0; it < FNIT; ++it)
-        if (it * 64 + lane < NB * NB) ol[it * 64 + lane] = og[it];
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const double sgd = (double)fr.sigma;
-      const float coef = (float)(-0.5 * LOG2E / (sgd * sgd));  // as entry_geometry
-      // lane k holds G at squared lattice distance k, as the entry path forms it
-      const int gtab = __float_as_int(__builtin_amdgcn_exp2f(coef * (float)lane));
-      bool neg = false;
-#pragma unroll
-      for (int it = 0; it < FNIT; ++it) neg = neg || !(og[it] >= 0.0f);
-      const bool nonneg = __ballot(neg) == 0ull;  // no negative (or NaN) opacity in the run
-      int nb[PPT];
-      const int nb0 = end - ((n_ck + 1) << ck_lg);  // the next chunk boundary still to store
-#pragma unroll
-      for (int q = 0; q < PPT; ++q) nb[q] = nb0;
-      // pixel q's LDS cell and the list position of its own lattice point:
-      // those of the lane's first pixel plus q's offset in the lane's block
-      int lx0, ly0;
-      pixel_of<TILE>(quad, lane, 0, &lx0, &ly0);
-      const int cell0 = (ly0 - qy + FR_R) * NB + (lx0 - qx + FR_R);
-      const int pb0 = fr.p_lo + (y0 + ly0 - fr.iy0 - fr.j0) * fr.w + (x0 + lx0 - fr.ix0 - fr.i0);
-      // the state of pixel q at chunk boundary nb[q] (all positions >= it done)
-      auto store_boundary = [&](int q) {
+      for (int q = 0; q < PPT; ++q) {
         const float a = Tst[q] - T[q];
         acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
         if (C == 3) {
@@ -508,262 +473,212 @@ __global__ __launch_bounds__(BLOCK, E == 1 ? 4 : 1) void k_blend_fwd(
           acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
         }
         Tst[q] = T[q];
-        float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - nb[q]) >> ck_lg) - 1) * (4 * TILE * TILE);
-        const int slot = (quad * PPT + q) * 64 + lane;
-        ckp[slot] = T[q];
+      }
+      const float4 pc = w.gcol[fr.g_top];
+      rc0 = pc.x;
+      rc1 = pc.y;
+      rc2 = pc.z;
+      run_curve = fr.c;
+    }
+    const int qx = (quad & 1) * Cfg::SUB, qy = (quad >> 1) * Cfg::SUB;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch) {
-          ckp[(1 + ch) * TILE * TILE + slot] = acc[q][ch];
-          acc[q][ch] = 0.0f;
-        }
-        nb[q] -= 1 << ck_lg;
-      };
-      // pixels are independent here: one pixel's whole walk at a time
+    for (int it = 0; it < FNIT; ++it)
+      if (it * 64 + lane < NB * NB) ol[it * 64 + lane] = og[it];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const double sgd = (double)fr.sigma;
+    const float coef = (float)(-0.5 * LOG2E / (sgd * sgd));  // as entry_geometry
+    // lane k holds G at squared lattice distance k, as the entry path forms it
+    const int gtab = __float_as_int(__builtin_amdgcn_exp2f(coef * (float)lane));
+    bool neg = false;
 #pragma unroll
-      for (int q = 0; q < PPT; ++q) {
+    for (int it = 0; it < FNIT; ++it) neg = neg || !(og[it] >= 0.0f);
+    const bool nonneg = __ballot(neg) == 0ull;  // no negative (or NaN) opacity in the run
+    int nb[PPT];
+    const int nb0 = end - ((n_ck + 1) << ck_lg);  // the next chunk boundary still to store
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) nb[q] = nb0;
+    // pixel q's LDS cell and the list position of its own lattice point:
+    // those of the lane's first pixel plus q's offset in the lane's block
+    int lx0, ly0;
+    pixel_of<TILE>(quad, lane, 0, &lx0, &ly0);
+    const int cell0 = (ly0 - qy + FR_R) * NB + (lx0 - qx + FR_R);
+    const int pb0 = fr.p_lo + (y0 + ly0 - fr.iy0 - fr.j0) * fr.w + (x0 + lx0 - fr.ix0 - fr.i0);
+    // the state of pixel q at chunk boundary nb[q] (all positions >= it done)
+    auto store_boundary = [&](int q) {
+      const float a = Tst[q] - T[q];
+      acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
+      if (C == 3) {
+        acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
+        acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
+      }
+      Tst[q] = T[q];
+      float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - nb[q]) >> ck_lg) - 1) * (4 * TILE * TILE);
+      const int slot = (quad * PPT + q) * 64 + lane;
+      ckp[slot] = T[q];
+#pragma unroll
+      for (int ch = 0; ch < C; ++ch) {
+        ckp[(1 + ch) * TILE * TILE + slot] = acc[q][ch];
+        acc[q][ch] = 0.0f;
+      }
+      nb[q] -= 1 << ck_lg;
+    };
+    // pixels are independent here: one pixel's whole walk at a time
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) {
 #pragma unroll 1
-        for (int dy = FR_R; dy >= -FR_R; --dy) {
-          const int dxm = dy * dy <= 4 ? 4 : (dy * dy == 9 ? 3 : 2);  // dx^2 + dy^2 <= FR_R2
-          const int roff = cell0 + (q / Cfg::BLK + dy) * NB + q % Cfg::BLK;
-          const int rpos = pb0 + (q / Cfg::BLK + dy) * fr.w + q % Cfg::BLK;
-          {
-            // a row with no Gaussian still to composite for any live pixel
-            // changes nothing (chunk boundaries it crosses are stored with
-            // the unchanged state at the end)
-            const int jr = y0 + ly0 + q / Cfg::BLK + dy - fr.iy0, ir = x0 + lx0 + q % Cfg::BLK - fr.ix0;
-            const bool any = T[q] >= eps && jr >= fr.j0 && jr <= fr.j1 && ir + dxm >= fr.i0 && ir - dxm <= fr.i1 &&
-                             rpos - dxm <= top;
-            if (__ballot(any) == 0ull) continue;
-          }
-          // the row's opacities first, one LDS wait per row, and its five
-          // Gaussian factors (|dx| = 0 .. 4) from the table
-          float orow[2 * FR_R + 1], Gr[FR_R + 1];
+      for (int dy = FR_R; dy >= -FR_R; --dy) {
+        const int dxm = dy * dy <= 4 ? 4 : (dy * dy == 9 ? 3 : 2);  // dx^2 + dy^2 <= FR_R2
+        const int roff = cell0 + (q / Cfg::BLK + dy) * NB + q % Cfg::BLK;
+        const int rpos = pb0 + (q / Cfg::BLK + dy) * fr.w + q % Cfg::BLK;
+        {
+          // a row with no Gaussian still to composite for any live pixel
+          // changes nothing (chunk boundaries it crosses are stored with
+          // the unchanged state at the end)
+          const int jr = y0 + ly0 + q / Cfg::BLK + dy - fr.iy0, ir = x0 + lx0 + q % Cfg::BLK - fr.ix0;
+          const bool any = T[q] >= eps && jr >= fr.j0 && jr <= fr.j1 && ir + dxm >= fr.i0 && ir - dxm <= fr.i1 &&
+                           rpos - dxm <= top;
+          if (__ballot(any) == 0ull) continue;
+        }
+        // the row's opacities first, one LDS wait per row, and its five
+        // Gaussian factors (|dx| = 0 .. 4) from the table
+        float orow[2 * FR_R + 1], Gr[FR_R + 1];
 #pragma unroll
-          for (int dx = -FR_R; dx <= FR_R; ++dx) orow[dx + FR_R] = ol[roff + dx];
+        for (int dx = -FR_R; dx <= FR_R; ++dx) orow[dx + FR_R] = ol[roff + dx];
 #pragma unroll
-          for (int a = 0; a <= FR_R; ++a) Gr[a] = __int_as_float(__builtin_amdgcn_readlane(gtab, a * a + dy * dy));
-          auto cell = [&](int dx, bool check) {
-            const float G = Gr[dx < 0 ? -dx : dx];
-            const float o = orow[dx + FR_R];
-            const int pos = rpos + dx;
-            if (check && o != 0.0f)
-              while (pos < nb[q]) store_boundary(q);
-            const float Tn = T[q] * (1.0f - fminf(amax, o * G));
-            const bool live = T[q] >= eps;
-            stop[q] = (live && Tn < eps) ? pos : stop[q];
-            T[q] = live ? Tn : T[q];
-          };
-          // a chunk boundary falls in the row of some lane only now and then
-          if (__ballot(rpos - dxm < nb[q]) == 0ull) {
-            // With no negative opacity in the run T does not grow along the
-            // row, so a pixel live at its start whose T ends it at or above
-            // eps_T was live at every cell: the row's product, with no stop
-            // test, is then the cell-by-cell result.  Only where some pixel
-            // stops inside the row is the row taken cell by cell.
-            float Tr = T[q];
+        for (int a = 0; a <= FR_R; ++a) Gr[a] = __int_as_float(__builtin_amdgcn_readlane(gtab, a * a + dy * dy));
+        auto cell = [&](int dx, bool check) {
+          const float G = Gr[dx < 0 ? -dx : dx];
+          const float o = orow[dx + FR_R];
+          const int pos = rpos + dx;
+          if (check && o != 0.0f)
+            while (pos < nb[q]) store_boundary(q);
+          const float Tn = T[q] * (1.0f - fminf(amax, o * G));
+          const bool live = T[q] >= eps;
+          stop[q] = (live && Tn < eps) ? pos : stop[q];
+          T[q] = live ? Tn : T[q];
+        };
+        // a chunk boundary falls in the row of some lane only now and then
+        if (__ballot(rpos - dxm < nb[q]) == 0ull) {
+          // With no negative opacity in the run T does not grow along the
+          // row, so a pixel live at its start whose T ends it at or above
+          // eps_T was live at every cell: the row's product, with no stop
+          // test, is then the cell-by-cell result.  Only where some pixel
+          // stops inside the row is the row taken cell by cell.
+          float Tr = T[q];
 #pragma unroll
-            for (int dx = FR_R; dx >= -FR_R; --dx)
-              if (dx <= dxm && dx >= -dxm) Tr = Tr * (1.0f - fminf(amax, orow[dx + FR_R] * Gr[dx < 0 ? -dx : dx]));
-            const bool live = T[q] >= eps;
-            if (nonneg && __ballot(live && !(Tr >= eps)) == 0ull) {
-              T[q] = live ? Tr : T[q];
-            } else {
-#pragma unroll
-              for (int dx = FR_R; dx >= -FR_R; --dx)
-                if (dx <= dxm && dx >= -dxm) cell(dx, false);
-            }
+          for (int dx = FR_R; dx >= -FR_R; --dx)
+            if (dx <= dxm && dx >= -dxm) Tr = Tr * (1.0f - fminf(amax, orow[dx + FR_R] * Gr[dx < 0 ? -dx : dx]));
+          const bool live = T[q] >= eps;
+          if (nonneg && __ballot(live && !(Tr >= eps)) == 0ull) {
+            T[q] = live ? Tr : T[q];
           } else {
 #pragma unroll
             for (int dx = FR_R; dx >= -FR_R; --dx)
-              if (dx <= dxm && dx >= -dxm) cell(dx, true);
+              if (dx <= dxm && dx >= -dxm) cell(dx, false);
           }
+        } else {
+#pragma unroll
+          for (int dx = FR_R; dx >= -FR_R; --dx)
+            if (dx <= dxm && dx >= -dxm) cell(dx, true);
         }
       }
-      // boundaries at or above the run's bottom (none at or below start)
-      const int bl = max(fr.p_lo, start + 1);
+    }
+    // boundaries at or above the run's bottom (none at or below start)
+    const int bl = max(fr.p_lo, start + 1);
 #pragma unroll
-      for (int q = 0; q < PPT; ++q)
-        while (nb[q] >= bl) store_boundary(q);
-      n_ck = (end - bl) >> ck_lg;
-    };
-    while (hi > start) {
-      if (fill_lattice && __builtin_amdgcn_readfirstlane(e[0].kind) == 1) {
-        // the next entry (position hi - 1, lane 0's first) is a fill
-        // Gaussian: take its run's remaining positions pixel by pixel
-        FillRun fr;
-        const int c = __builtin_amdgcn_readfirstlane(e[0].r.curve);
-        const float sg = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, e[0].r.sigma)));
-        const float rr = ks * sg;
-        float og[FNIT];
-        bool take = false;
-        if (rr * rr >= (float)FR_R2 && rr * rr < (float)(FR_R2 + 5) &&
-            fill_run_at(plan, c, __builtin_amdgcn_readfirstlane(e[0].g), __builtin_amdgcn_readfirstlane(e[0].r.local),
-                        sg, hi - 1, start, end, 1.0, ks, inv_tile, st, lt, TILE, &fr)) {
-          // the opacities and the corner check in flight together
-          const int ib = x0 + (quad & 1) * Cfg::SUB - fr.ix0 - FR_R, jb = y0 + (quad >> 1) * Cfg::SUB - fr.iy0 - FR_R;
-          fill_gather<FNB, FNIT>(w.gop, gcap, fr, ib, jb, fr.p_lo, hi - 1, 0.0f, og);
-          take = fill_corners_ok(idx, fr);
-        }
-        if (take) {
-          const int top = hi - 1;
-          hi = fr.p_lo;
-          // the next step's loads (as at the start of the list), in flight
-          // during the walk
-          lo_s = step_floor(hi, start, depth, end, ck_lg);
-          nhi = lo_s;
-          nlo = step_floor(nhi, start, depth, end, ck_lg);
-#pragma unroll
-          for (int u = 0; u < E; ++u) {
-            const int k = u * 64 + lane;
-            load_entry(idx, gs, w.gcol, hi - 1 - k, k < hi - lo_s, &e[u]);
-            gnext[u] = k < nhi - nlo ? idx[nhi - 1 - k] : 0;
-          }
-          fill_run_fwd(fr, top, og);
-          bool done = true;
-#pragma unroll
-          for (int q = 0; q < PPT; ++q) done = done && !(T[q] >= eps);
-          if (__ballot(!done) == 0ull) break;  // every pixel of the quadrant has stopped
-          continue;
-        }
+    for (int q = 0; q < PPT; ++q)
+      while (nb[q] >= bl) store_boundary(q);
+    n_ck = (end - bl) >> ck_lg;
+  };
+  while (hi > start) {
+    if (fill_lattice && __builtin_amdgcn_readfirstlane(e.kind) == 1) {
+      // the next entry (position hi - 1, lane 0's first) is a fill
+      // Gaussian: take its run's remaining positions pixel by pixel
+      FillRun fr;
+      const int c = __builtin_amdgcn_readfirstlane(e.r.curve);
+      const float sg = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, e.r.sigma)));
+      const float rr = ks * sg;
+      float og[FNIT];
+      bool take = false;
+      if (rr * rr >= (float)FR_R2 && rr * rr < (float)(FR_R2 + 5) &&
+          fill_run_at(plan, c, __builtin_amdgcn_readfirstlane(e.g), __builtin_amdgcn_readfirstlane(e.r.local),
+                      sg, hi - 1, start, end, 1.0, ks, inv_tile, st, lt, TILE, &fr)) {
+        // the opacities and the corner check in flight together
+        const int ib = x0 + (quad & 1) * Cfg::SUB - fr.ix0 - FR_R, jb = y0 + (quad >> 1) * Cfg::SUB - fr.iy0 - FR_R;
+        fill_gather<FNB, FNIT>(w.gop, gcap, fr, ib, jb, fr.p_lo, hi - 1, 0.0f, og);
+        take = fill_corners_ok(idx, fr);
       }
-      int cnt = 0;
-      bool step_aniso = false;
+      if (take) {
+        const int top = hi - 1;
+        hi = fr.p_lo;
+        // the next step's loads (as at the start of the list), in flight
+        // during the walk
+        lo_s = step_floor(hi, start, depth, end, ck_lg);
+        nhi = lo_s;
+        nlo = step_floor(nhi, start, depth, end, ck_lg);
+        load_entry(idx, gs, w.gcol, hi - 1 - lane, lane < hi - lo_s, &e);
+        gnext = lane < nhi - nlo ? idx[nhi - 1 - lane] : 0;
+        fill_run_fwd(fr, top, og);
+        bool done = true;
 #pragma unroll
-      for (int u = 0; u < E; ++u) {
-        const int k = u * 64 + lane;
-        const int mypos = hi - 1 - k;
-        const bool ok = k < hi - lo_s;
-        float4 geo;
-        const bool keep = ok && entry_geometry(e[u].r, ox, oy, ks, qbox, &geo);
-        const uint64_t m = __ballot(keep);
-        if (ANI) step_aniso = step_aniso || __ballot(keep && e[u].kind == 2) != 0ull;
-        if (keep) {
-          const int dst = cnt + __popcll(m & below);
-          FwdRec rec;
-          rec.geo = geo;
-          rec.op = e[u].r.opacity;
-          rec.pos = mypos;
-          rec.curve = e[u].r.curve;
-          rec.g = e[u].g;
-          wrec[dst] = rec;
-          wcol[dst] = make_float4(e[u].c0, e[u].c1, e[u].c2, ANI ? (float)e[u].kind : 0.0f);
-        }
-        cnt += __popcll(m);
+        for (int q = 0; q < PPT; ++q) done = done && !(T[q] >= eps);
+        if (__ballot(!done) == 0ull) break;  // every pixel of the quadrant has stopped
+        continue;
       }
-      // next step's records (their indices arrived during this step's
-      // predecessor) and the indices of the step after, in flight while
-      // this step is composited
-      const int n2hi = nlo, n2lo = step_floor(n2hi, start, depth, end, ck_lg);
-#pragma unroll
-      for (int u = 0; u < E; ++u) {
-        const int k = u * 64 + lane;
-        if (k < nhi - nlo) load_rec(gs, w.gcol, gnext[u], &e[u]);
-        gnext[u] = k < n2hi - n2lo ? idx[n2hi - 1 - k] : 0;
-      }
+    }
+    float4 geo;
+    const bool keep = lane < hi - lo_s && entry_geometry(e.r, ox, oy, ks, qbox, &geo);
+    const uint64_t m = __ballot(keep);
+    const int cnt = __popcll(m);
+    const bool step_aniso = ANI && __ballot(keep && e.kind == 2) != 0ull;
+    if (keep) {
+      const int dst = __popcll(m & below);
+      FwdRec rec;
+      rec.geo = geo;
+      rec.op = e.r.opacity;
+      rec.pos = hi - 1 - lane;
+      rec.curve = e.r.curve;
+      rec.g = e.g;
+      wrec[dst] = rec;
+      wcol[dst] = make_float4(e.c0, e.c1, e.c2, ANI ? (float)e.kind : 0.0f);
+    }
+    // next step's records (their indices arrived during this step's
+    // predecessor) and the indices of the step after, in flight while
+    // this step is composited
+    const int n2hi = nlo, n2lo = step_floor(n2hi, start, depth, end, ck_lg);
+    if (lane < nhi - nlo) load_rec(gs, w.gcol, gnext, &e);
+    gnext = lane < n2hi - n2lo ? idx[n2hi - 1 - lane] : 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (ANI && step_aniso) {
+      // tangent-aligned entries of the step take their axis u and ratio r
+      if (lane < cnt && wcol[lane].w == 2.0f) convert_aniso(w.gaux, wrec[lane]);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      if (ANI && step_aniso) {
-        // tangent-aligned entries of the step take their axis u and ratio r
-        for (int i = lane; i < cnt; i += 64) {
-          if (wcol[i].w != 2.0f) continue;
-          const float4 ax = w.gaux[wrec[i].g];
-          float ux, uy, rq;
-          aniso_axes(ax, wrec[i].geo.w, &ux, &uy, &rq);
-          wrec[i].geo.z = ux;
-          wrec[i].geo.w = uy;
-          wrec[i].g = __float_as_int(rq);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      }
-      // composited entries that begin a run (their curve differs from the
-      // entry before, the first one compared with the previous step's run)
-      uint64_t rs[E];
+    }
+    // composited entries that begin a run (their curve differs from the
+    // entry before, the first one compared with the previous step's run)
+    const int prev = lane == 0 ? run_curve : wrec[lane > 0 ? lane - 1 : 0].curve;
+    const uint64_t rs = __ballot(lane < cnt && wrec[lane].curve != prev);
+    int last[PPT];   // the pixel's last composited entry of the step
+    bool was[PPT];  // live in front of it
 #pragma unroll
-      for (int g = 0; g < E; ++g) {
-        const int i = 64 * g + lane;
-        const int prev = i == 0 ? run_curve : wrec[i > 0 ? i - 1 : 0].curve;
-        rs[g] = __ballot(i < cnt && wrec[i < cnt ? i : 0].curve != prev);
-      }
-      for (int j = 0; j < cnt;) {
-        // this segment: j up to the next run start (or the step's end)
-        int jend = cnt;
-#pragma unroll
-        for (int g = E - 1; g >= 0; --g) {
-          const int b = j + 1 - 64 * g;  // first bit of group g after j
-          const uint64_t m = b <= 0 ? rs[g] : (b < 64 ? rs[g] & (~0ull << b) : 0ull);
-          if (m) jend = 64 * g + __builtin_ctzll(m);
-        }
-        if ((rs[j >> 6] >> (j & 63)) & 1ull) {  // a new run: close the previous one
-#pragma unroll
-          for (int q = 0; q < PPT; ++q) {
-            const float a = Tst[q] - T[q];
-            acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-            if (C == 3) {
-              acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-              acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-            }
-            Tst[q] = T[q];
-          }
-          const float4 pc = wcol[j];
-          rc0 = pc.x;
-          rc1 = pc.y;
-          rc2 = pc.z;
-          run_curve = wrec[j].curve;
-          if (ANI) run_kind = __builtin_amdgcn_readfirstlane((int)pc.w);
-        }
-        if (ANI && run_kind == 2) {
-          // tangent-aligned strokes (elliptical Eq. 9)
-          const float lim = ANI_CK * ks * ks;
-          for (; j < jend; ++j) {
-            const float4 gm = wrec[j].geo;
-            const float op = wrec[j].op, rq = __int_as_float(wrec[j].g);
-            const int pos = wrec[j].pos;
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-              const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-              const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
-              const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
-              const float m = __builtin_fmaf(a, a, b * b);
-              const float G = __builtin_amdgcn_exp2f(-m);
-              const bool in = (m <= lim) && (T[q] >= eps);
-              const float Tn = T[q] * (1.0f - fminf(amax, op * G));
-              stop[q] = (in && Tn < eps) ? pos : stop[q];
-              T[q] = in ? Tn : T[q];
-            }
-          }
-        }
-#pragma unroll 8
-        for (; j < jend; ++j) {
-          const float4 gm = wrec[j].geo;
-          const float op = wrec[j].op;
-          const int pos = wrec[j].pos;
-#pragma unroll
-          for (int q = 0; q < PPT; ++q) {
-            const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-            const float d2 = __builtin_fmaf(dx, dx, dy * dy);
-            const float G = __builtin_amdgcn_exp2f(gm.w * d2);
-            const bool in = (d2 <= gm.z) && (T[q] >= eps);
-            const float Tn = T[q] * (1.0f - fminf(amax, op * G));
-            stop[q] = (in && Tn < eps) ? pos : stop[q];  // the pixel's last composited position
-            T[q] = in ? Tn : T[q];
-          }
-        }
-      }
-      bool mine = true;
-#pragma unroll
-      for (int q = 0; q < PPT; ++q) mine = mine && !(T[q] >= eps);
-      hi = nhi;
-      lo_s = nlo;
-      nhi = n2hi;
-      nlo = n2lo;
-      if (hi > start && ((end - hi) & ((1 << ck_lg) - 1)) == 0) {
-        // at the front of chunk k = (end - hi) / CK: T, and the colour the
-        // chunk just finished contributed (the current run closed at the
-        // boundary; the sum restarts for the next chunk)
-        float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - hi) >> ck_lg) - 1) * (4 * TILE * TILE);
+    for (int q = 0; q < PPT; ++q) {
+      last[q] = 0;
+      was[q] = T[q] >= eps;
+    }
+    for (int j = 0; j < cnt;) {
+      // this segment: j up to the next run start (or the step's end)
+      const uint64_t after = j < 63 ? rs & (~0ull << (j + 1)) : 0ull;
+      const int jend = after ? __builtin_ctzll(after) : cnt;
+      if ((rs >> j) & 1ull) {  // a new run: close the previous one
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
           const float a = Tst[q] - T[q];
@@ -774,65 +689,133 @@ __global__ __launch_bounds__(BLOCK, E == 1 ? 4 : 1) void k_blend_fwd(
           }
           Tst[q] = T[q];
         }
+        const float4 pc = wcol[j];
+        rc0 = pc.x;
+        rc1 = pc.y;
+        rc2 = pc.z;
+        run_curve = wrec[j].curve;
+        if (ANI) run_kind = __builtin_amdgcn_readfirstlane((int)pc.w);
+      }
+      if (ANI && run_kind == 2) {
+        // tangent-aligned strokes (elliptical Eq. 9)
+        const float lim = ANI_CK * ks * ks;
+        for (; j < jend; ++j) {
+          const float4 gm = wrec[j].geo;
+          const float op = wrec[j].op, rq = __int_as_float(wrec[j].g);
 #pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-          const int slot = (quad * PPT + q) * 64 + lane;
-          ckp[slot] = T[q];
-#pragma unroll
-          for (int c = 0; c < C; ++c) {
-            ckp[(1 + c) * TILE * TILE + slot] = acc[q][c];
-            acc[q][c] = 0.0f;
+          for (int q = 0; q < PPT; ++q) {
+            const float dx = px[q] - gm.x, dy = py[q] - gm.y;
+            const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
+            const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
+            const float m = __builtin_fmaf(a, a, b * b);
+            const float G = __builtin_amdgcn_exp2f(-m);
+            const bool in = (m <= lim) && (T[q] >= eps);
+            const float Tn = T[q] * (1.0f - fminf(amax, op * G));
+            last[q] = in ? j : last[q];
+            T[q] = in ? Tn : T[q];
           }
         }
-        ++n_ck;
       }
-      __builtin_amdgcn_wave_barrier();
-      if (__ballot(!mine) == 0ull) break;  // every pixel of the quadrant has stopped
-    }
+#pragma unroll 8
+      for (; j < jend; ++j) {
+        const float4 gm = wrec[j].geo;
+        const float op = wrec[j].op;
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {  // close the last run
-      const float a = Tst[q] - T[q];
-      acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-      if (C == 3) {
-        acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-        acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
+        for (int q = 0; q < PPT; ++q) {
+          const float dx = px[q] - gm.x, dy = py[q] - gm.y;
+          const float d2 = __builtin_fmaf(dx, dx, dy * dy);
+          const float G = __builtin_amdgcn_exp2f(gm.w * d2);
+          const bool in = (d2 <= gm.z) && (T[q] >= eps);
+          const float Tn = T[q] * (1.0f - fminf(amax, op * G));
+          last[q] = in ? j : last[q];
+          T[q] = in ? Tn : T[q];
+        }
       }
     }
-    // Suffix sums over the chunks, back to front: each boundary's slot
-    // receives the colour of everything behind it (the chunks after it; the
-    // background is added by the adjoint), a sum of the chunks' own
-    // contributions with no cancellation, and the total is the pixel's
-    // colour.  Each lane rereads only the slots it wrote itself.
-    const int64_t ck_first = (int64_t)ck0 * (4 * TILE * TILE);
-    for (int k = n_ck; k >= 1; --k) {
-      float* ckp = w.ckbuf + ck_first + (int64_t)(k - 1) * (4 * TILE * TILE);
+    bool mine = true;
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) {
+      mine = mine && !(T[q] >= eps);
+      // a pixel that stopped in this step did so at the last entry it took
+      if (was[q] && T[q] < eps) stop[q] = wrec[last[q]].pos;
+    }
+    hi = nhi;
+    lo_s = nlo;
+    nhi = n2hi;
+    nlo = n2lo;
+    if (hi > start && ((end - hi) & ((1 << ck_lg) - 1)) == 0) {
+      // at the front of chunk k = (end - hi) / CK: T, and the colour the
+      // chunk just finished contributed (the current run closed at the
+      // boundary; the sum restarts for the next chunk)
+      float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - hi) >> ck_lg) - 1) * (4 * TILE * TILE);
+#pragma unroll
+      for (int q = 0; q < PPT; ++q) {
+        const float a = Tst[q] - T[q];
+        acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
+        if (C == 3) {
+          acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
+          acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
+        }
+        Tst[q] = T[q];
+      }
 #pragma unroll
       for (int q = 0; q < PPT; ++q) {
         const int slot = (quad * PPT + q) * 64 + lane;
+        ckp[slot] = T[q];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-          const float ch = ckp[(1 + c) * TILE * TILE + slot];
           ckp[(1 + c) * TILE * TILE + slot] = acc[q][c];
-          acc[q][c] += ch;
+          acc[q][c] = 0.0f;
         }
       }
+      ++n_ck;
     }
+    __builtin_amdgcn_wave_barrier();
+    if (__ballot(!mine) == 0ull) break;  // every pixel of the quadrant has stopped
+  }
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {  // close the last run
+    const float a = Tst[q] - T[q];
+    acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
+    if (C == 3) {
+      acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
+      acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
+    }
+  }
+  // Suffix sums over the chunks, back to front: each boundary's slot
+  // receives the colour of everything behind it (the chunks after it; the
+  // background is added by the adjoint), a sum of the chunks' own
+  // contributions with no cancellation, and the total is the pixel's
+  // colour.  Each lane rereads only the slots it wrote itself.
+  const int64_t ck_first = (int64_t)ck0 * (4 * TILE * TILE);
+  for (int k = n_ck; k >= 1; --k) {
+    float* ckp = w.ckbuf + ck_first + (int64_t)(k - 1) * (4 * TILE * TILE);
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
-      int lx, ly;
-      pixel_of<TILE>(quad, lane, q, &lx, &ly);
-      const int x = x0 + lx, y = y0 + ly;
-      if (x < st.W && y < st.H) {
-        const int64_t pix = (int64_t)st.pix_off + (int64_t)y * st.W + x;
-        const int64_t plane = (int64_t)st.H * st.W;
+      const int slot = (quad * PPT + q) * 64 + lane;
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)y * st.W + x;
-          image[o] = __builtin_fmaf(T[q], bg[s * C + c], acc[q][c]);
-        }
-        Tfin[pix] = T[q];
-        nlast[pix] = stop[q];
+      for (int c = 0; c < C; ++c) {
+        const float ch = ckp[(1 + c) * TILE * TILE + slot];
+        ckp[(1 + c) * TILE * TILE + slot] = acc[q][c];
+        acc[q][c] += ch;
       }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    int lx, ly;
+    pixel_of<TILE>(quad, lane, q, &lx, &ly);
+    const int x = x0 + lx, y = y0 + ly;
+    if (x < st.W && y < st.H) {
+      const int64_t pix = (int64_t)st.pix_off + (int64_t)y * st.W + x;
+      const int64_t plane = (int64_t)st.H * st.W;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)y * st.W + x;
+        image[o] = __builtin_fmaf(T[q], bg[s * C + c], acc[q][c]);
+      }
+      Tfin[pix] = T[q];
+      nlast[pix] = stop[q];
     }
   }
 }
@@ -867,6 +850,431 @@ __device__ inline float wave_totals_to_lanes(const float (&v)[N]) {
     out = lane == i ? t : out;
   }
   return out;
+}
+
+// Inclusive products over the lanes: lane l gets x_0 x_1 ... x_l.
+__device__ inline float wave_scan_product(float x) {
+#define NSP_DPP_MUL(ctrl, rmask)                                                                            \
+  x *= __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(1.0f), __float_as_int(x), ctrl, rmask, 0xf, \
+                                                  false));
+  NSP_DPP_MUL(0x111, 0xf)
+  NSP_DPP_MUL(0x112, 0xf)
+  NSP_DPP_MUL(0x114, 0xf)
+  NSP_DPP_MUL(0x118, 0xf)
+  NSP_DPP_MUL(0x142, 0xa)
+  NSP_DPP_MUL(0x143, 0xc)
+#undef NSP_DPP_MUL
+  return x;
+}
+
+// ---------------------------------------------------------------------------
+// A long list on the eight wavefronts of a block.  The list is taken from its
+// end in windows of 512 positions: every wavefront culls and stages 64 of them,
+// the kept entries are compacted into one array, and each wavefront composites
+// an eighth of it (a share) on its own: per pixel the product of the factors
+// 1 - alpha, starting from T = 1, and the colours on that scale.  The products
+// go through LDS, every wavefront multiplies them up in list order, and T at
+// the front of its share scales its colours.  Where a pixel goes below eps_T
+// inside a share, that share's wavefront finds the entry with one scan over the
+// lanes, an entry each (fwd_stop), or, for many pixels at once, by compositing
+// the share again entry by entry.  In a window with a negative (or NaN)
+// opacity, where T may grow, the shares are composited one after another.
+//
+// On one wavefront (fwd_serial) an entry takes 38 ns, a dozen vector
+// instructions at the 11 cycles between two of a single wavefront, so that
+// launches with a few long lists waited for the longest one.  With eight, a
+// window takes about 17,000 cycles, 6,000 of them in the composited shares,
+// 900 per pixel that stops and 5,000 in staging, exchange and the chunk's
+// state: 12 quintic strokes at 512^2 (longest list 9,736) 0.376 -> 0.228 ms,
+// 16 closed ones at 512^2 (1,667) 0.067 -> 0.040, 32 strokes at 256^2 (1,537)
+// 0.057 -> 0.028, 32 tangent-aligned ones (265) 0.031 -> 0.022.  Built for six
+// wavefronts per SIMD, so that three blocks share a CU: at four (two blocks)
+// the same took 0.265, 0.048, 0.037 ms.
+// ---------------------------------------------------------------------------
+constexpr int FW = 8;  // wavefronts per block of the forward
+constexpr int FWD_BLOCK = 64 * FW;
+constexpr int FWD_WINDOW = 64 * FW;
+static_assert(FWD_WINDOW <= CK_MIN, "a window lies inside one chunk");
+constexpr int STOP_SCANS = 12;  // more stopping pixels than this: composite the share again
+
+struct FwdLds {
+  FwdRec rec[FWD_WINDOW];  // the window's entries (colour sums when exchanged; fwd_serial: 64 per wavefront)
+  float4 col[FWD_WINDOW];
+  float prod[FW][64];      // the shares' products
+  float stopT[64];         // T and list position where a pixel stopped
+  int stopP[64];
+  int cnt[FW], neg[FW];  // entries kept per wavefront, and whether one has a negative opacity
+  int next;
+};
+
+template <int C, int TILE, int KIND>
+__device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w, const FwdItem& im,
+                                          const Gauss* __restrict__ gs, const int32_t* __restrict__ idx,
+                                          const float* __restrict__ bg, float* __restrict__ image,
+                                          float* __restrict__ Tfin, int32_t* __restrict__ nlast, int ck_lg,
+                                          FwdLds& L) {
+  static_assert(TileCfg<TILE>::PPT == 1, "one pixel per lane");
+  constexpr bool ANI = (KIND & KIND_ANI) != 0;
+  static_assert(sizeof(L.rec) + sizeof(L.col) >= sizeof(float) * FW * 64 * C, "colour sums fit");
+  const float amax = pr.alpha_max, eps = pr.eps_T, ks = pr.k_sigma;
+  const float lim = ANI_CK * ks * ks;  // (tangent-aligned entries)
+  const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t below = lanes_below();
+  const int quad = im.quad, x0 = im.x0, y0 = im.y0, start = im.start, end = im.end;
+  // T: the pixels' transmittance in front of the window, in every wavefront.
+  // A pixel is live while T >= eps_T (0 <= eps_T <= 1); -1 stands for a
+  // stopped one (stopT, stopP) and for pixels outside the image.
+  int lx, ly;
+  pixel_of<TILE>(quad, lane, 0, &lx, &ly);
+  const float px = (float)lx, py = (float)ly;
+  float T = (x0 + lx < im.st.W && y0 + ly < im.st.H) ? 1.0f : -1.0f;
+  float acc[3] = {0.0f, 0.0f, 0.0f};
+  const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
+  const Box qbox = quad_box<TILE>(quad);
+  const int ck0 = w.ck_off[im.tile];
+  int n_ck = 0;  // chunk boundaries passed (state stored)
+  float* sums = (float*)L.rec;  // [FW][C][64], between windows
+  auto put_sums = [&]() {
+    __syncthreads();  // every wavefront is done with the window's entries
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      sums[(wv * C + c) * 64 + lane] = acc[c];
+      acc[c] = 0.0f;
+    }
+    __syncthreads();
+  };
+  auto get_sum = [&](int c) {
+    float a = 0.0f;
+#pragma unroll
+    for (int k = 0; k < FW; ++k) a += sums[(k * C + c) * 64 + lane];
+    return a;
+  };
+  // list indices are loaded two windows ahead and records one window ahead
+  Entry e;
+  int gnext = 0;
+  e.kind = 0;
+  {
+    const int p = end - 1 - 64 * wv - lane;
+    load_entry(idx, gs, w.gcol, p, p >= start, &e);
+    if (p - FWD_WINDOW >= start) gnext = idx[p - FWD_WINDOW];
+  }
+  for (int whi = end; whi > start; whi -= FWD_WINDOW) {
+    const int pos = whi - 1 - 64 * wv - lane;
+    float4 geo;
+    const bool keep = pos >= start && entry_geometry(e.r, ox, oy, ks, qbox, &geo);
+    const uint64_t m = __ballot(keep);
+    const bool neg = __ballot(keep && !(e.r.opacity >= 0.0f)) != 0ull;
+    if (lane == 0) {
+      L.cnt[wv] = __popcll(m);
+      L.neg[wv] = neg;
+    }
+    __syncthreads();
+    int base = 0, K = 0;
+    bool any_neg = false;
+#pragma unroll
+    for (int k = 0; k < FW; ++k) {
+      const int n = L.cnt[k];
+      base += k < wv ? n : 0;
+      K += n;
+      any_neg = any_neg || L.neg[k] != 0;
+    }
+    if (keep) {
+      const int dst = base + __popcll(m & below);
+      FwdRec rec;
+      rec.geo = geo;
+      rec.op = e.r.opacity;
+      rec.pos = pos;
+      rec.curve = e.r.curve;
+      rec.g = e.g;
+      if (ANI && e.kind == 2) convert_aniso(w.gaux, rec);
+      L.rec[dst] = rec;
+      L.col[dst] = make_float4(e.c0, e.c1, e.c2, (float)e.kind);
+    }
+    // the next window's records, and the indices of the one after, in flight
+    // during this window
+    if (pos - FWD_WINDOW >= start) {
+      load_rec(gs, w.gcol, gnext, &e);
+      if (pos - 2 * FWD_WINDOW >= start) gnext = idx[pos - 2 * FWD_WINDOW];
+    }
+    __syncthreads();
+    // this wavefront's share: n (at most 64) entries of the window's K
+    K = __builtin_amdgcn_readfirstlane(K);
+    const int ja = K * wv / FW, n = K * (wv + 1) / FW - ja;
+    const FwdRec* rec = L.rec + ja;
+    const float4* col = L.col + ja;
+    // entries whose curve differs from the entry before
+    const uint64_t rs = __ballot(lane < n && (lane == 0 || rec[lane].curve != rec[lane > 0 ? lane - 1 : 0].curve));
+    // Composites the share into t (from the given start) and ca, the colour
+    // per run of entries of one curve as in fwd_serial.  STOP: pixels with
+    // t >= eps stop where t falls below it, at position sp; lp is the last
+    // position that they composited.
+    float t, ca[3];
+    int sp = -1, lp = start;
+    auto composite = [&](auto stop_tag) {
+      constexpr bool STOP = decltype(stop_tag)::value;
+      float tst = t, rc0 = 0.0f, rc1 = 0.0f, rc2 = 0.0f;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) ca[c] = 0.0f;
+      auto close_run = [&]() {
+        const float a = tst - t;
+        ca[0] = __builtin_fmaf(rc0, a, ca[0]);
+        if (C == 3) {
+          ca[1] = __builtin_fmaf(rc1, a, ca[1]);
+          ca[2] = __builtin_fmaf(rc2, a, ca[2]);
+        }
+        tst = t;
+      };
+      auto take = [&](bool in, float f, int at) {
+        const float tn = t * f;
+        if (STOP) {
+          in = in && t >= eps;
+          sp = (in && tn < eps) ? at : sp;
+          lp = in ? at : lp;
+        }
+        t = in ? tn : t;
+      };
+      auto disc = [&](const FwdRec& r) {
+        const float4 gm = r.geo;
+        const float op = r.op;
+        const int at = STOP ? r.pos : 0;
+        const float dx = px - gm.x, dy = py - gm.y;
+        const float d2 = __builtin_fmaf(dx, dx, dy * dy);
+        const float G = __builtin_amdgcn_exp2f(gm.w * d2);
+        take(d2 <= gm.z, 1.0f - fminf(amax, op * G), at);
+      };
+      for (int j = 0; j < n;) {
+        const uint64_t after = j < 63 ? rs & (~0ull << (j + 1)) : 0ull;
+        const int jend = after ? __builtin_ctzll(after) : n;  // up to the next run
+        close_run();
+        const float4 pc = col[j];
+        rc0 = pc.x;
+        rc1 = pc.y;
+        rc2 = pc.z;
+        if (ANI && __builtin_amdgcn_readfirstlane((int)pc.w) == 2) {
+          // tangent-aligned strokes (elliptical Eq. 9)
+          for (; j < jend; ++j) {
+            const float4 gm = rec[j].geo;
+            const float op = rec[j].op, rq = __int_as_float(rec[j].g);
+            const int at = STOP ? rec[j].pos : 0;
+            const float dx = px - gm.x, dy = py - gm.y;
+            const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
+            const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
+            const float mm = __builtin_fmaf(a, a, b * b);
+            const float G = __builtin_amdgcn_exp2f(-mm);
+            take(mm <= lim, 1.0f - fminf(amax, op * G), at);
+          }
+        }
+        if constexpr (STOP) {
+#pragma unroll 2
+          for (; j < jend; ++j) disc(rec[j]);
+        } else {
+#pragma unroll 8
+          for (; j < jend; ++j) disc(rec[j]);
+        }
+      }
+      close_run();
+    };
+    if (!any_neg) {
+      t = 1.0f;
+      composite(std::false_type{});
+      L.prod[wv][lane] = t;
+      __syncthreads();
+      // T through the window, and at the front of this share
+      float Tw = T;
+      bool flag = false;
+#pragma unroll
+      for (int k = 0; k < FW; ++k) {
+        const float Tn = T * L.prod[k][lane];
+        const bool live = T >= eps, goes = live && !(Tn >= eps);
+        if (k == wv) {
+          Tw = T;
+          flag = goes;
+        }
+        T = goes ? -1.0f : (live ? Tn : T);
+      }
+      uint64_t left = __ballot(flag);
+      if (Tw >= eps && !flag) {
+        acc[0] = __builtin_fmaf(Tw, ca[0], acc[0]);
+        if (C == 3) {
+          acc[1] = __builtin_fmaf(Tw, ca[1], acc[1]);
+          acc[2] = __builtin_fmaf(Tw, ca[2], acc[2]);
+        }
+      }
+      // where the products say that a pixel stops in this share but its
+      // factors one by one do not, it stops at its last entry of the share
+      const float under = __int_as_float(__float_as_int(eps) - 1);
+      if (__popcll(left) > STOP_SCANS) {
+        t = flag ? Tw : -1.0f;
+        composite(std::true_type{});
+        if (flag) {
+          L.stopT[lane] = fminf(t, under);
+          L.stopP[lane] = sp >= 0 ? sp : lp;
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc[c] += ca[c];
+        }
+      } else if (left) {
+        const FwdRec r = rec[lane < n ? lane : 0];
+        const float4 pc = col[lane < n ? lane : 0];
+        while (left) {
+          // the pixel of lane l: an entry per lane
+          const int l = __builtin_ctzll(left);
+          left &= left - 1;
+          const float dx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(px), l)) - r.geo.x;
+          const float dy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(py), l)) - r.geo.y;
+          const float T0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(Tw), l));
+          float d2 = __builtin_fmaf(dx, dx, dy * dy), x = r.geo.w * d2, l2 = r.geo.z;
+          if (ANI && pc.w == 2.0f) {
+            const float a = __builtin_fmaf(dx, r.geo.z, dy * r.geo.w);
+            const float b = __int_as_float(r.g) * __builtin_fmaf(dy, r.geo.z, -(dx * r.geo.w));
+            d2 = __builtin_fmaf(a, a, b * b);
+            x = -d2;
+            l2 = lim;
+          }
+          const bool in = lane < n && d2 <= l2;
+          const float f = 1.0f - fminf(amax, r.op * __builtin_amdgcn_exp2f(x));
+          const float Tn = T0 * wave_scan_product(in ? f : 1.0f);
+          const uint64_t dead = __ballot(in && Tn < eps), some = __ballot(in);
+          const int at = dead ? __builtin_ctzll(dead) : (some ? 63 - __builtin_clzll(some) : 0);
+          const float Tp =
+              __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(T0), __float_as_int(Tn), 0x138, 0xf, 0xf, false));
+          const float d = lane <= at ? Tp - Tn : 0.0f;
+          float tot;
+          if constexpr (C == 3) {
+            const float v[3] = {pc.x * d, pc.y * d, pc.z * d};
+            tot = wave_totals_to_lanes<3>(v);
+          } else {
+            const float v[1] = {pc.x * d};
+            tot = wave_totals_to_lanes<1>(v);
+          }
+          if (lane == at) {
+            L.stopT[l] = fminf(Tn, under);
+            L.stopP[l] = r.pos;
+          }
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tot), c));
+            acc[c] += lane == l ? a : 0.0f;
+          }
+        }
+      }
+    } else {
+      // one share after another
+      for (int k = 0; k < FW; ++k) {
+        if (k == wv) {
+          t = T;
+          composite(std::true_type{});
+#pragma unroll
+          for (int c = 0; c < C; ++c) acc[c] += ca[c];
+          if (sp >= 0) {
+            L.stopT[lane] = t;
+            L.stopP[lane] = sp;
+          }
+          L.prod[0][lane] = sp >= 0 ? -1.0f : t;
+        }
+        __syncthreads();
+        T = L.prod[0][lane];
+        __syncthreads();
+      }
+    }
+    const int lo = whi - FWD_WINDOW;
+    if (lo > start && ((end - lo) & ((1 << ck_lg) - 1)) == 0) {
+      // at the front of chunk k = (end - lo) / CK: T, and the colour the chunk
+      // just finished contributed (the sum restarts for the next)
+      float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - lo) >> ck_lg) - 1) * (4 * TILE * TILE);
+      put_sums();
+      const int slot = quad * 64 + lane;
+      if (wv < C) ckp[(1 + wv) * TILE * TILE + slot] = get_sum(wv);
+      if (wv == FW - 1) ckp[slot] = T;
+      ++n_ck;
+    }
+    if (__ballot(T >= eps) == 0ull) break;  // every pixel of the quadrant has stopped
+  }
+  // The pixels' colours: the shares' sums, then suffix sums over the chunks,
+  // back to front, as in fwd_serial.  Wavefront c takes channel c and rereads
+  // only the slots that it wrote; the last one writes T and the positions.
+  put_sums();
+  const int64_t plane = (int64_t)im.st.H * im.st.W;
+  const int x = x0 + lx, y = y0 + ly;
+  const bool inside = x < im.st.W && y < im.st.H;
+  const int64_t at = (int64_t)y * im.st.W + x;
+  const int slot = quad * 64 + lane;
+  float Tq = T;
+  int stop = start;
+  if (inside && !(Tq >= eps)) {
+    Tq = L.stopT[lane];
+    stop = L.stopP[lane];
+  }
+  if (wv < C) {
+    float a = get_sum(wv);
+    for (int k = n_ck; k >= 1; --k) {
+      float* ckp = w.ckbuf + (int64_t)(ck0 + k - 1) * (4 * TILE * TILE) + (1 + wv) * TILE * TILE;
+      const float ch = ckp[slot];
+      ckp[slot] = a;
+      a += ch;
+    }
+    if (inside) image[(int64_t)im.st.pix_off * C + wv * plane + at] = __builtin_fmaf(Tq, bg[im.s * C + wv], a);
+  }
+  if (wv == FW - 1 && inside) {
+    Tfin[(int64_t)im.st.pix_off + at] = Tq;
+    nlast[(int64_t)im.st.pix_off + at] = stop;
+  }
+}
+
+// The first n_long tiles of the blend order (the binning's choice) take a
+// block per quadrant, the others a wavefront per quadrant, eight to a block.
+template <int C, int TILE, int KIND>
+__global__ __launch_bounds__(FWD_BLOCK, TileCfg<TILE>::PPT == 1 && !(KIND & KIND_FILL) ? 6 : 4) void k_blend_fwd(
+    nsplat_params pr, Work w, int n_scenes, int n_tiles, const Gauss* __restrict__ gs,
+    const int32_t* __restrict__ ranges, const int32_t* __restrict__ idx, const float* __restrict__ bg,
+    float* __restrict__ image, float* __restrict__ Tfin, int32_t* __restrict__ nlast, const int32_t* __restrict__ plan,
+    int64_t gcap, int persistent, int ck_arg) {
+  using Cfg = TileCfg<TILE>;
+  __shared__ __align__(16) FwdLds L;
+  typedef const __attribute__((address_space(4))) int32_t* const_i32;
+  // the chunk length: the caller's, or the one the binning chose
+  const int ck_lg = ck_arg >= 0 ? ck_arg : ((const_i32)w.queue)[Q_CKLG];
+  // fill runs at h = 1 walk each pixel's lattice neighbours (see FillRun);
+  // the support radius must be the 4.5 the offsets are laid out for
+  const bool fill_lattice = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_items = n_tiles * Cfg::QUADS;
+  // (launches that cannot hold a long list come in blocks of WPB wavefronts)
+  const int wpb = blockDim.x >> 6;
+  const int n_long =
+      wpb < FW || fill_lattice ? 0 : min(max(((const_i32)w.queue)[Q_NLONG], 0), n_tiles) * Cfg::QUADS;
+  for (int it = 0;; ++it) {
+    int b = blockIdx.x;
+    if (persistent) {
+      __syncthreads();
+      if (threadIdx.x == 0) L.next = atomicAdd(w.queue, 1);
+      __syncthreads();
+      b = __builtin_amdgcn_readfirstlane(L.next);
+    } else if (it > 0) {
+      break;
+    }
+    const bool whole = b < n_long;
+    if (!whole && n_long + (int64_t)(b - n_long) * wpb >= n_items) break;
+    const int item = whole ? b : n_long + (b - n_long) * wpb + wv;
+    if (item >= n_items) continue;
+    FwdItem im;
+    const int tq = item / Cfg::QUADS;
+    im.quad = item - tq * Cfg::QUADS;
+    im.tile = w.order[tq];
+    im.s = scene_of_tile(w.scenes, n_scenes, im.tile);
+    im.st = w.scenes[im.s];
+    im.lt = im.tile - im.st.tile_off;
+    im.x0 = (im.lt % im.st.tiles_x) * TILE;
+    im.y0 = (im.lt / im.st.tiles_x) * TILE;
+    im.start = ranges[2 * im.tile];
+    im.end = ranges[2 * im.tile + 1];
+    if constexpr (Cfg::PPT == 1)
+      if (whole) {
+        fwd_block<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, ck_lg, L);
+        continue;
+      }
+    fwd_serial<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, plan, gcap, ck_lg, fill_lattice,
+                              (char*)L.rec + wv * (64 * FWD_ENTRY_BYTES));
+  }
 }
 
 // Minimum over the wavefront: running minima inside each row of 16 lanes by
@@ -1675,9 +2083,9 @@ __global__ void k_reset_queue(int32_t* q) {
 }
 
 template <class K>
-int resident_grid(K kernel, int n_blocks, int n_cu, size_t lds) {
+int resident_grid(K kernel, int n_blocks, int n_cu, size_t lds, int block = BLOCK) {
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, BLOCK, lds) != hipSuccess || per_cu < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, block, lds) != hipSuccess || per_cu < 1)
     per_cu = 1;
   const int g = per_cu * n_cu;
   return g < n_blocks ? g : n_blocks;
@@ -1685,20 +2093,27 @@ int resident_grid(K kernel, int n_blocks, int n_cu, size_t lds) {
 
 inline int depth_factor(int batch) { return batch <= 64 ? 1 : (batch <= 128 ? 2 : 4); }
 
-template <int C, int TILE, int E, int KIND>
+template <int C, int TILE, int KIND>
 hipError_t fwd_t(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
-  const int n_items = (int)L.n_tiles * TileCfg<TILE>::QUADS;
+  constexpr int QUADS = TileCfg<TILE>::QUADS;
+  const int64_t n_items = L.n_tiles * QUADS;
   if (n_items <= 0) return hipSuccess;
-  const size_t lds = (size_t)WPB * 64 * E * FWD_ENTRY_BYTES;
-  int grid = (n_items + WPB - 1) / WPB;
-  if (persistent) {
-    grid = resident_grid(k_blend_fwd<C, TILE, E, KIND>, grid, L.n_cu, lds);
+  // blocks: one per item of a long list (at least LONG_LEAST positions each;
+  // their number is on the device), one per wpb others
+  const bool split = split_long(*L.pr) && !((KIND & KIND_FILL) && !L.pr->h_dev && L.pr->h == 1.0f);
+  const int wpb = split ? FW : WPB;
+  const int64_t n_long = split ? std::min(L.n_tiles, (int64_t)L.bf->caps.pairs / LONG_LEAST) * QUADS : 0;
+  int64_t blocks = std::min(n_items, n_long + (n_items + wpb - 1) / wpb);
+  // (a launch counts its threads in 32 bits)
+  if (persistent || blocks * 64 * wpb > 0x7fffffffLL) {
+    persistent = 1;
+    blocks = resident_grid(k_blend_fwd<C, TILE, KIND>, (int)std::min<int64_t>(blocks, 0x7fffffff), L.n_cu, 0, 64 * wpb);
     hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, L.stream, L.w.queue);
   }
   Phase ph(L, NSPLAT_T_BLEND_FWD);
-  hipLaunchKernelGGL((k_blend_fwd<C, TILE, E, KIND>), dim3(grid), dim3(BLOCK), lds, L.stream, *L.cv, *L.pr, L.w,
-                     L.sc->n_scenes, n_items, (const Gauss*)L.bf->gauss, L.bf->ranges, L.bf->idx, L.sc->bg, image,
-                     T_final, n_last, L.bf->plan, (int64_t)L.bf->caps.gauss, persistent, L.ck_lg);
+  hipLaunchKernelGGL((k_blend_fwd<C, TILE, KIND>), dim3((int)blocks), dim3(64 * wpb), 0, L.stream, *L.pr, L.w,
+                     L.sc->n_scenes, (int)L.n_tiles, (const Gauss*)L.bf->gauss, L.bf->ranges, L.bf->idx, L.sc->bg,
+                     image, T_final, n_last, L.bf->plan, (int64_t)L.bf->caps.gauss, persistent, L.ck_lg);
   return hipGetLastError();
 }
 
@@ -1730,22 +2145,13 @@ inline int kinds_of(const Launch& L) {
   return ((L.cv->any_flags & NSPLAT_ANISO) ? KIND_ANI : 0) | ((L.cv->any_flags & NSPLAT_FILLED) ? KIND_FILL : 0);
 }
 
-template <int C, int TILE, int E>
-hipError_t fwd_k(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
-  switch (kinds_of(L)) {
-    case 0: return fwd_t<C, TILE, E, 0>(L, image, T_final, n_last, persistent);
-    case KIND_ANI: return fwd_t<C, TILE, E, KIND_ANI>(L, image, T_final, n_last, persistent);
-    case KIND_FILL: return fwd_t<C, TILE, E, KIND_FILL>(L, image, T_final, n_last, persistent);
-    default: return fwd_t<C, TILE, E, KIND_ANI | KIND_FILL>(L, image, T_final, n_last, persistent);
-  }
-}
-
 template <int C, int TILE>
 hipError_t fwd_d(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
-  switch (depth_factor(L.pr->batch)) {
-    case 1: return fwd_k<C, TILE, 1>(L, image, T_final, n_last, persistent);
-    case 2: return fwd_k<C, TILE, 2>(L, image, T_final, n_last, persistent);
-    default: return fwd_k<C, TILE, 4>(L, image, T_final, n_last, persistent);
+  switch (kinds_of(L)) {
+    case 0: return fwd_t<C, TILE, 0>(L, image, T_final, n_last, persistent);
+    case KIND_ANI: return fwd_t<C, TILE, KIND_ANI>(L, image, T_final, n_last, persistent);
+    case KIND_FILL: return fwd_t<C, TILE, KIND_FILL>(L, image, T_final, n_last, persistent);
+    default: return fwd_t<C, TILE, KIND_ANI | KIND_FILL>(L, image, T_final, n_last, persistent);
   }
 }
 

@@ -136,6 +136,29 @@ constexpr int Q_NFILL = 8, Q_NSTROKE = 9, Q_NANISO = 10;
 // Work::queue slot with the log2 chunk length that the binning chose for the
 // launch's lists when params.chunk is 0 (read by the blend kernels).
 constexpr int Q_CKLG = 11;
+// Work::queue slot with the number of long lists, the first so many tiles of
+// the blend order, which the forward takes with a block per quadrant.
+constexpr int Q_NLONG = 12;
+// Lists are long from this length class (__clz of the length) on: those whose
+// length is at least the positions of all quadrants / (LONG_SHARE x compute
+// units), rounded down to a power of two, and at least LONG_LEAST.  A list
+// below the first bound ends, on one wavefront, before the rest of the launch
+// does, and a block composites it with about half more instructions; one above
+// it would be waited for.  Measured at 1/3, 1, 2 and 16 times the share: 12
+// quintic strokes at 512^2 0.410, 0.228, 0.179, 0.175 ms; one curve of 10,240
+// key points at 1024^2 0.162, 0.140, 0.157, 0.250; 16 x 2000 key points at
+// 1024^2 0.307, 0.307, 0.313, 0.48 (0.139 and 0.322 on one wavefront each).
+// LONG_LEAST 512, 256, 128: 32 strokes at 256^2 0.038, 0.028, 0.028 ms, 32
+// tangent-aligned ones (longest list 265) 0.029, 0.028, 0.022.
+constexpr int LONG_SHARE = 9, LONG_LEAST = 128;
+// Whether a launch may take long lists so: at one pixel per lane, and where
+// the chunk length is left to choose as well (both move the rounding with the
+// size of the launch).
+inline bool split_long(const nsplat_params& pr) { return pr.chunk == 0 && pr.tile <= 16; }
+__device__ inline int long_class(int64_t pairs, int quads, int n_cu) {
+  const int64_t len = pairs * quads / ((int64_t)LONG_SHARE * (n_cu > 0 ? n_cu : 1));
+  return __builtin_clz((unsigned)(len < LONG_LEAST ? LONG_LEAST : len));
+}
 
 struct Layout {
   size_t off[N_WS];

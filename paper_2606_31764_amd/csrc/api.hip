@@ -244,13 +244,13 @@ int check_params(nsplat_ctx* ctx, const nsplat_params* pr) {
   return NSPLAT_OK;
 }
 
-// log2 of params.chunk; when it is 0, 512 for batches without fills and -1
-// (the binning chooses on the device, auto_chunk_log2) for batches with them:
-// the fill-run walks cost mostly per run and per item set-up, which longer
-// chunks save, while entry-by-entry stroke compositing gains more from
-// splitting long lists across wavefronts.
+// log2 of params.chunk; when it is 0, the binning chooses on the device: for
+// batches with fills by auto_chunk_log2, for others 512 or, at up to 16 x 16
+// tiles, less (small_chunk_log2): the fill-run walks cost mostly per run and
+// per item set-up, which longer chunks save, while entry-by-entry stroke
+// compositing gains more from splitting long lists across wavefronts.
 int chunk_log2(const nsplat_curves* cv, const nsplat_params* pr) {
-  if (pr->chunk == 0) return (cv->any_flags & NSPLAT_FILLED) ? -1 : 9;
+  if (pr->chunk == 0) return (cv->any_flags & NSPLAT_FILLED) ? CK_ARG_AUTO : (pr->tile <= 16 ? CK_ARG_SMALL : 9);
   int lg = 0;
   while ((1 << lg) < pr->chunk) ++lg;
   return lg;

@@ -582,7 +582,9 @@ __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict
 // The launch's log2 chunk length: the caller's (ck_arg >= 0), or chosen from
 // the pair count.
 __device__ inline int launch_chunk_log2(int ck_arg, const int32_t* counters, int quads, int n_cu) {
-  return ck_arg >= 0 ? ck_arg : auto_chunk_log2(counters[NSPLAT_CNT_PAIRS], quads, n_cu);
+  if (ck_arg >= 0) return ck_arg;
+  const int64_t pairs = counters[NSPLAT_CNT_PAIRS];
+  return ck_arg == CK_ARG_SMALL ? small_chunk_log2(pairs, quads, n_cu) : auto_chunk_log2(pairs, quads, n_cu);
 }
 
 __global__ void k_chunk_counts(const int32_t* __restrict__ ranges, int n_tiles, int ck_arg, const int32_t* counters,

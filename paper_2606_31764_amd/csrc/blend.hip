@@ -421,8 +421,13 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
   // run began, and adds col (Tst - T) where the run ends.  Runs end where
   // the curve changes between consecutive composited entries, at chunk
   // boundaries and at the end, all fixed by the list, so the result does not
-  // depend on the batch depth.
+  // depend on the batch depth.  At one pixel per lane the image's sums (tot,
+  // runs from Trun) are kept apart from the chunks' and don't end at their
+  // boundaries, so that an image does not depend on the chunk length either,
+  // which a small launch takes shorter.
+  constexpr bool TOT = PPT == 1;
   float px[PPT], py[PPT], T[PPT], Tst[PPT], acc[PPT][3];
+  float tot[3] = {0.0f, 0.0f, 0.0f}, Trun = 0.0f;
   int stop[PPT];
   int run_curve = -1, run_kind = 0;
   float rc0 = 0.0f, rc1 = 0.0f, rc2 = 0.0f;  // the run's colour
@@ -441,6 +446,31 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     for (int c = 0; c < 3; ++c) acc[q][c] = 0.0f;
     stop[q] = start;
   }
+  Trun = T[0];
+  // pixel q's share of the chunk's colour from the current run so far
+  auto close_chunk = [&](int q) {
+    const float a = Tst[q] - T[q];
+    acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
+    if (C == 3) {
+      acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
+      acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
+    }
+    Tst[q] = T[q];
+  };
+  // the end of a run
+  auto close_run = [&]() {
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) close_chunk(q);
+    if (TOT) {
+      const float a = Trun - T[0];
+      tot[0] = __builtin_fmaf(rc0, a, tot[0]);
+      if (C == 3) {
+        tot[1] = __builtin_fmaf(rc1, a, tot[1]);
+        tot[2] = __builtin_fmaf(rc2, a, tot[2]);
+      }
+      Trun = T[0];
+    }
+  };
   const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
   const Box qbox = quad_box<TILE>(quad);
   // front to back: list positions end-1 down to start, at most `depth` per
@@ -464,16 +494,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     constexpr int NB = FNB;
     float* ol = (float*)mine_lds;            // [NB][NB] opacities (0: no Gaussian of the run waits there)
     if (run_curve != fr.c) {                 // a run of this curve already open goes on
-#pragma unroll
-      for (int q = 0; q < PPT; ++q) {
-        const float a = Tst[q] - T[q];
-        acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-        if (C == 3) {
-          acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-          acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-        }
-        Tst[q] = T[q];
-      }
+      close_run();
       const float4 pc = w.gcol[fr.g_top];
       rc0 = pc.x;
       rc1 = pc.y;
@@ -510,13 +531,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     const int pb0 = fr.p_lo + (y0 + ly0 - fr.iy0 - fr.j0) * fr.w + (x0 + lx0 - fr.ix0 - fr.i0);
     // the state of pixel q at chunk boundary nb[q] (all positions >= it done)
     auto store_boundary = [&](int q) {
-      const float a = Tst[q] - T[q];
-      acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-      if (C == 3) {
-        acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-        acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-      }
-      Tst[q] = T[q];
+      close_chunk(q);
       float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - nb[q]) >> ck_lg) - 1) * (4 * TILE * TILE);
       const int slot = (quad * PPT + q) * 64 + lane;
       ckp[slot] = T[q];
@@ -679,16 +694,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
       const uint64_t after = j < 63 ? rs & (~0ull << (j + 1)) : 0ull;
       const int jend = after ? __builtin_ctzll(after) : cnt;
       if ((rs >> j) & 1ull) {  // a new run: close the previous one
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-          const float a = Tst[q] - T[q];
-          acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-          if (C == 3) {
-            acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-            acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-          }
-          Tst[q] = T[q];
-        }
+        close_run();
         const float4 pc = wcol[j];
         rc0 = pc.x;
         rc1 = pc.y;
@@ -749,15 +755,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
       // boundary; the sum restarts for the next chunk)
       float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - hi) >> ck_lg) - 1) * (4 * TILE * TILE);
 #pragma unroll
-      for (int q = 0; q < PPT; ++q) {
-        const float a = Tst[q] - T[q];
-        acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-        if (C == 3) {
-          acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-          acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-        }
-        Tst[q] = T[q];
-      }
+      for (int q = 0; q < PPT; ++q) close_chunk(q);
 #pragma unroll
       for (int q = 0; q < PPT; ++q) {
         const int slot = (quad * PPT + q) * 64 + lane;
@@ -773,20 +771,12 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     __builtin_amdgcn_wave_barrier();
     if (__ballot(!mine) == 0ull) break;  // every pixel of the quadrant has stopped
   }
-#pragma unroll
-  for (int q = 0; q < PPT; ++q) {  // close the last run
-    const float a = Tst[q] - T[q];
-    acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
-    if (C == 3) {
-      acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-      acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
-    }
-  }
+  close_run();
   // Suffix sums over the chunks, back to front: each boundary's slot
   // receives the colour of everything behind it (the chunks after it; the
   // background is added by the adjoint), a sum of the chunks' own
   // contributions with no cancellation, and the total is the pixel's
-  // colour.  Each lane rereads only the slots it wrote itself.
+  // colour (to the rounding of tot).  Each lane rereads only the slots it wrote itself.
   const int64_t ck_first = (int64_t)ck0 * (4 * TILE * TILE);
   for (int k = n_ck; k >= 1; --k) {
     float* ckp = w.ckbuf + ck_first + (int64_t)(k - 1) * (4 * TILE * TILE);
@@ -812,7 +802,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
 #pragma unroll
       for (int c = 0; c < C; ++c) {
         const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)y * st.W + x;
-        image[o] = __builtin_fmaf(T[q], bg[s * C + c], acc[q][c]);
+        image[o] = __builtin_fmaf(T[q], bg[s * C + c], TOT ? tot[c] : acc[q][c]);
       }
       Tfin[pix] = T[q];
       nlast[pix] = stop[q];
@@ -871,30 +861,33 @@ __device__ inline float wave_scan_product(float x) {
 // A long list on the eight wavefronts of a block.  The list is taken from its
 // end in windows of 512 positions: every wavefront culls and stages 64 of them,
 // the kept entries are compacted into one array, and each wavefront composites
-// an eighth of it (a share) on its own: per pixel the product of the factors
-// 1 - alpha, starting from T = 1, and the colours on that scale.  The products
-// go through LDS, every wavefront multiplies them up in list order, and T at
-// the front of its share scales its colours.  Where a pixel goes below eps_T
-// inside a share, that share's wavefront finds the entry with one scan over the
-// lanes, an entry each (fwd_stop), or, for many pixels at once, by compositing
-// the share again entry by entry.  In a window with a negative (or NaN)
-// opacity, where T may grow, the shares are composited one after another.
+// a share, half of what two wavefronts kept, on its own: per pixel the product
+// of the factors 1 - alpha, starting from T = 1, and the colours on that
+// scale.  The products go through LDS, every wavefront multiplies them up in
+// list order, and T at the front of its share scales its colours.  Where a
+// pixel goes below eps_T inside a share, that share's wavefront finds the entry
+// with one scan over the lanes, an entry each, or, for many pixels at once, by
+// compositing the share again entry by entry.  In a window with a negative (or
+// NaN) opacity, where T may grow, the shares are composited one after another.
 //
 // On one wavefront (fwd_serial) an entry takes 38 ns, a dozen vector
 // instructions at the 11 cycles between two of a single wavefront, so that
 // launches with a few long lists waited for the longest one.  With eight, a
 // window takes about 17,000 cycles, 6,000 of them in the composited shares,
 // 900 per pixel that stops and 5,000 in staging, exchange and the chunk's
-// state: 12 quintic strokes at 512^2 (longest list 9,736) 0.376 -> 0.228 ms,
-// 16 closed ones at 512^2 (1,667) 0.067 -> 0.040, 32 strokes at 256^2 (1,537)
-// 0.057 -> 0.028, 32 tangent-aligned ones (265) 0.031 -> 0.022.  Built for six
-// wavefronts per SIMD, so that three blocks share a CU: at four (two blocks)
-// the same took 0.265, 0.048, 0.037 ms.
+// state: 12 quintic strokes at 512^2 (longest list 9,736) 0.376 -> 0.240 ms,
+// 16 closed ones at 512^2 (1,667) 0.067 -> 0.047, 32 strokes at 256^2 (1,537)
+// 0.057 -> 0.036, 32 tangent-aligned ones (265) 0.031 -> 0.023.  Shares of all
+// eight wavefronts' entries together were more even (0.228, 0.040, 0.028,
+// 0.022 ms), but then a chunk could not end inside a window, which the adjoint
+// gains more from (small_chunk_log2).  Built for six wavefronts per SIMD, so
+// that three blocks share a CU: at four (two blocks) it was a quarter slower.
 // ---------------------------------------------------------------------------
 constexpr int FW = 8;  // wavefronts per block of the forward
 constexpr int FWD_BLOCK = 64 * FW;
 constexpr int FWD_WINDOW = 64 * FW;
-static_assert(FWD_WINDOW <= CK_MIN, "a window lies inside one chunk");
+static_assert(CK_SMALL >= 64 && FWD_WINDOW % CK_SMALL == 0 && FWD_WINDOW <= CK_MIN,
+              "a window lies inside one chunk or holds whole ones");
 constexpr int STOP_SCANS = 12;  // more stopping pixels than this: composite the share again
 
 struct FwdLds {
@@ -928,27 +921,27 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
   pixel_of<TILE>(quad, lane, 0, &lx, &ly);
   const float px = (float)lx, py = (float)ly;
   float T = (x0 + lx < im.st.W && y0 + ly < im.st.H) ? 1.0f : -1.0f;
-  float acc[3] = {0.0f, 0.0f, 0.0f};
   const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
   const Box qbox = quad_box<TILE>(quad);
+  // A share is taken from a group's positions, those of two wavefronts: a
+  // chunk holds whole groups whatever its length, so that the image does not
+  // depend on it.
+  constexpr int group = CK_SMALL / 64;
   const int ck0 = w.ck_off[im.tile];
   int n_ck = 0;  // chunk boundaries passed (state stored)
-  float* sums = (float*)L.rec;  // [FW][C][64], between windows
-  auto put_sums = [&]() {
-    __syncthreads();  // every wavefront is done with the window's entries
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      sums[(wv * C + c) * 64 + lane] = acc[c];
-      acc[c] = 0.0f;
-    }
-    __syncthreads();
+  const int slot = quad * 64 + lane;
+  // T at the front of share k of the window at whi, if a chunk ends there
+  // (chunk number (end - lo) / CK counts from 1)
+  auto boundary = [&](int lo) { return lo > start && ((end - lo) & ((1 << ck_lg) - 1)) == 0; };
+  auto ck_at = [&](int lo) {
+    return w.ckbuf + (int64_t)(ck0 + ((end - lo) >> ck_lg) - 1) * (4 * TILE * TILE) + slot;
   };
-  auto get_sum = [&](int c) {
-    float a = 0.0f;
-#pragma unroll
-    for (int k = 0; k < FW; ++k) a += sums[(k * C + c) * 64 + lane];
-    return a;
+  auto put_T = [&](int whi, int k, float t) {
+    const int lo = whi - 64 * (k + 1);
+    if (wv == FW - 1 && boundary(lo)) *ck_at(lo) = t;
   };
+  float tail = 0.0f, tot = 0.0f;  // channel wv's colour since the last boundary, and the image's
+  float* sums = (float*)L.rec;  // [FW][C][64], at the end of a window
   // list indices are loaded two windows ahead and records one window ahead
   Entry e;
   int gnext = 0;
@@ -969,13 +962,14 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
       L.neg[wv] = neg;
     }
     __syncthreads();
-    int base = 0, K = 0;
+    int base = 0, g0 = 0, K = 0;
     bool any_neg = false;
 #pragma unroll
     for (int k = 0; k < FW; ++k) {
       const int n = L.cnt[k];
       base += k < wv ? n : 0;
-      K += n;
+      g0 += k < (wv & -group) ? n : 0;
+      K += (k & -group) == (wv & -group) ? n : 0;
       any_neg = any_neg || L.neg[k] != 0;
     }
     if (keep) {
@@ -997,9 +991,11 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
       if (pos - 2 * FWD_WINDOW >= start) gnext = idx[pos - 2 * FWD_WINDOW];
     }
     __syncthreads();
-    // this wavefront's share: n (at most 64) entries of the window's K
+    // this wavefront's share: n (at most 64) of the K entries of its group's
+    // positions, from entry g0 on
     K = __builtin_amdgcn_readfirstlane(K);
-    const int ja = K * wv / FW, n = K * (wv + 1) / FW - ja;
+    g0 = __builtin_amdgcn_readfirstlane(g0);
+    const int in = wv & (group - 1), ja = g0 + K * in / group, n = g0 + K * (in + 1) / group - ja;
     const FwdRec* rec = L.rec + ja;
     const float4* col = L.col + ja;
     // entries whose curve differs from the entry before
@@ -1008,7 +1004,7 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
     // per run of entries of one curve as in fwd_serial.  STOP: pixels with
     // t >= eps stop where t falls below it, at position sp; lp is the last
     // position that they composited.
-    float t, ca[3];
+    float t, ca[3], con[3] = {0.0f, 0.0f, 0.0f};  // con: the share's colours at the pixels' own T
     int sp = -1, lp = start;
     auto composite = [&](auto stop_tag) {
       constexpr bool STOP = decltype(stop_tag)::value;
@@ -1091,14 +1087,12 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
           flag = goes;
         }
         T = goes ? -1.0f : (live ? Tn : T);
+        put_T(whi, k, T);
       }
       uint64_t left = __ballot(flag);
       if (Tw >= eps && !flag) {
-        acc[0] = __builtin_fmaf(Tw, ca[0], acc[0]);
-        if (C == 3) {
-          acc[1] = __builtin_fmaf(Tw, ca[1], acc[1]);
-          acc[2] = __builtin_fmaf(Tw, ca[2], acc[2]);
-        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) con[c] = Tw * ca[c];
       }
       // where the products say that a pixel stops in this share but its
       // factors one by one do not, it stops at its last entry of the share
@@ -1110,7 +1104,7 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
           L.stopT[lane] = fminf(t, under);
           L.stopP[lane] = sp >= 0 ? sp : lp;
 #pragma unroll
-          for (int c = 0; c < C; ++c) acc[c] += ca[c];
+          for (int c = 0; c < C; ++c) con[c] = ca[c];
         }
       } else if (left) {
         const FwdRec r = rec[lane < n ? lane : 0];
@@ -1153,7 +1147,7 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
 #pragma unroll
           for (int c = 0; c < C; ++c) {
             const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tot), c));
-            acc[c] += lane == l ? a : 0.0f;
+            con[c] = lane == l ? a : con[c];
           }
         }
       }
@@ -1164,7 +1158,7 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
           t = T;
           composite(std::true_type{});
 #pragma unroll
-          for (int c = 0; c < C; ++c) acc[c] += ca[c];
+          for (int c = 0; c < C; ++c) con[c] = ca[c];
           if (sp >= 0) {
             L.stopT[lane] = t;
             L.stopP[lane] = sp;
@@ -1173,31 +1167,41 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
         }
         __syncthreads();
         T = L.prod[0][lane];
+        put_T(whi, k, T);
         __syncthreads();
       }
     }
-    const int lo = whi - FWD_WINDOW;
-    if (lo > start && ((end - lo) & ((1 << ck_lg) - 1)) == 0) {
-      // at the front of chunk k = (end - lo) / CK: T, and the colour the chunk
-      // just finished contributed (the sum restarts for the next)
-      float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - lo) >> ck_lg) - 1) * (4 * TILE * TILE);
-      put_sums();
-      const int slot = quad * 64 + lane;
-      if (wv < C) ckp[(1 + wv) * TILE * TILE + slot] = get_sum(wv);
-      if (wv == FW - 1) ckp[slot] = T;
+    // the colours: wavefront c sums channel c over the shares, group by group,
+    // and stores what each chunk that ends here contributed
+    __syncthreads();  // every wavefront is done with the window's entries
+#pragma unroll
+    for (int c = 0; c < C; ++c) sums[(wv * C + c) * 64 + lane] = con[c];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < FW; k += group) {
+      if (wv < C) {
+        float a = 0.0f;
+#pragma unroll
+        for (int u = k; u < k + group; ++u) a += sums[(u * C + wv) * 64 + lane];
+        tail += a;
+        tot += a;
+      }
+      const int lo = whi - 64 * (k + group);
+      if (!boundary(lo)) continue;
+      if (wv < C) ck_at(lo)[(1 + wv) * TILE * TILE] = tail;
+      tail = 0.0f;
       ++n_ck;
     }
     if (__ballot(T >= eps) == 0ull) break;  // every pixel of the quadrant has stopped
   }
-  // The pixels' colours: the shares' sums, then suffix sums over the chunks,
-  // back to front, as in fwd_serial.  Wavefront c takes channel c and rereads
-  // only the slots that it wrote; the last one writes T and the positions.
-  put_sums();
+  // Suffix sums over the chunks, back to front, as in fwd_serial.  Wavefront c
+  // takes channel c and rereads only the slots that it wrote; the last one
+  // writes T and the positions.
+  __syncthreads();
   const int64_t plane = (int64_t)im.st.H * im.st.W;
   const int x = x0 + lx, y = y0 + ly;
   const bool inside = x < im.st.W && y < im.st.H;
   const int64_t at = (int64_t)y * im.st.W + x;
-  const int slot = quad * 64 + lane;
   float Tq = T;
   int stop = start;
   if (inside && !(Tq >= eps)) {
@@ -1205,14 +1209,14 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
     stop = L.stopP[lane];
   }
   if (wv < C) {
-    float a = get_sum(wv);
+    float a = tail;
     for (int k = n_ck; k >= 1; --k) {
       float* ckp = w.ckbuf + (int64_t)(ck0 + k - 1) * (4 * TILE * TILE) + (1 + wv) * TILE * TILE;
       const float ch = ckp[slot];
       ckp[slot] = a;
       a += ch;
     }
-    if (inside) image[(int64_t)im.st.pix_off * C + wv * plane + at] = __builtin_fmaf(Tq, bg[im.s * C + wv], a);
+    if (inside) image[(int64_t)im.st.pix_off * C + wv * plane + at] = __builtin_fmaf(Tq, bg[im.s * C + wv], tot);
   }
   if (wv == FW - 1 && inside) {
     Tfin[(int64_t)im.st.pix_off + at] = Tq;
@@ -2121,10 +2125,14 @@ template <int C, int TILE, int E, int KIND>
 hipError_t bwd_t(const Launch& L, const float* dL, const float* T_final, const int32_t* n_last, int persistent) {
   if (L.n_tiles <= 0) return hipSuccess;
   // the item count lives on the device; the grid covers its bound
-  // sum over tiles of QUADS * ceil(len / CK) <= QUADS * (pairs / CK + tiles)
-  const int64_t max_items =
-      (int64_t)adj_blocks(TILE, (KIND & KIND_FILL) != 0) * ((L.bf->caps.pairs >> (L.ck_lg >= 0 ? L.ck_lg : 9)) +
-                                                             L.n_tiles);
+  // sum over tiles of QUADS * ceil(len / CK) <= QUADS * (pairs / CK + tiles);
+  // where the binning chose a chunk below CK_MIN, QUADS * pairs / CK is at
+  // most twice its target (small_chunk_log2)
+  const int64_t blocks = adj_blocks(TILE, (KIND & KIND_FILL) != 0), pairs = L.bf->caps.pairs;
+  int64_t max_items = blocks * (pairs >> (L.ck_lg >= 0 ? L.ck_lg : 9));
+  if (L.ck_lg < 0 && TILE <= 16)
+    max_items = std::max(max_items, std::min(blocks * (pairs / CK_SMALL), (int64_t)2 * SMALL_ITEMS * L.n_cu));
+  max_items += blocks * L.n_tiles;
   const size_t lds = (size_t)WPB * bwd_wave_bytes(E) + BASIS_BYTES;
   int grid = (int)((max_items + WPB - 1) / WPB);
   if (persistent) {

@@ -80,8 +80,8 @@ struct Work {
 // the chunk boundaries it passes, and the adjoint runs one work item per
 // (tile, quadrant, chunk), so that a long list no longer sets the length of
 // the adjoint pass.  CK is params.chunk, or chosen per launch by the
-// binning (auto_chunk_log2); it is at least CK_MIN, for which the checkpoint
-// store is sized.
+// binning (auto_chunk_log2, small_chunk_log2); CK_MIN is what the checkpoint
+// store is sized for.
 constexpr int CK_MIN = 512, CK_MAX = 8192;
 __host__ __device__ inline int n_chunks(int len, int ck_lg) { return (len + (1 << ck_lg) - 1) >> ck_lg; }
 // About one adjoint item per two wavefront slots of the GPU: pairs x
@@ -94,6 +94,22 @@ __host__ __device__ inline int auto_chunk_log2(int64_t pairs, int quads, int n_c
   int lg = 9;
   while ((1 << lg) < CK_MAX && v >= 1.4142135623730951 * (double)(1 << lg)) ++lg;
   return lg;
+}
+// Launches without fills at 8 x 8 or 16 x 16 tiles: CK_MIN, or, where that
+// gives the adjoint fewer than SMALL_ITEMS items per compute unit, down to
+// CK_SMALL, for which the checkpoint store (sized for CK_MIN at 32 x 32 tiles)
+// suffices too.  An entry of a stroke costs an adjoint wavefront 140 ns, so
+// that 512 of them took as long as the rest of a small backward pass: the
+// adjoint of 32 strokes at 256^2 0.074 -> 0.041 ms, of 32 tangent-aligned ones
+// 0.067 -> 0.048, of 16 closed ones at 512^2 0.077 -> 0.057.  With enough items
+// at 512 shorter chunks only add stored states and item set-ups.
+constexpr int CK_SMALL = 128, SMALL_ITEMS = 16;
+static_assert(CK_SMALL * 4 >= CK_MIN, "16 x 16 tiles hold a quarter of the pixels");
+// Launch::ck_lg where the binning chooses: with fills, and without
+constexpr int CK_ARG_AUTO = -1, CK_ARG_SMALL = -2;
+__host__ __device__ inline int small_chunk_log2(int64_t pairs, int quads, int n_cu) {
+  const int64_t v = pairs * quads / (SMALL_ITEMS * (int64_t)(n_cu > 0 ? n_cu : 1));
+  return v >= 512 ? 9 : (v >= 256 ? 8 : 7);
 }
 // Adjoint work items per chunk of a tile list: the forward's quadrants (one
 // at 8 x 8 tiles, four above), except for the tiles of scenes with fills at
@@ -445,7 +461,7 @@ struct Launch {
   hipStream_t stream;
   int64_t n_tiles;
   int n_cu;
-  int ck_lg;  // log2 of params.chunk, or -1: chosen by the binning (Q_CKLG)
+  int ck_lg;  // log2 of params.chunk, or CK_ARG_*: chosen by the binning (Q_CKLG)
 };
 // the adjoint's pixel blocks per chunk for this launch's tile side and curves
 inline int adj_blocks_of(const Launch& L) { return adj_blocks(L.pr->tile, (L.cv->any_flags & NSPLAT_FILLED) != 0); }

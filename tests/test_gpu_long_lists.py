@@ -73,3 +73,23 @@ def test_against_one_wavefront(count, C, flags, persistent):
     assert other.sum() <= 2
     tol = 2 * n * EPS32 + np.where(np.tile(np.ravel(other), C), p.eps_T, 0.0)
     assert (np.abs(np.ravel(a["image"]) - np.ravel(c["image"])) <= tol).all()
+
+
+@pytest.mark.parametrize("delta_c", [4.0, 12.0, 44.0])
+@pytest.mark.parametrize("tile", [8, 16])
+def test_chosen_chunk_against_a_given_one(tile, delta_c):
+    """Left to choose, a launch of this size takes chunks of 128, 256 or 512
+    positions, and the same lists give the same gradients up to the order of
+    the sums (as batched against plain)."""
+    from helpers import PARAM_NAMES, grad_close
+    b = synth.config2(seed=31, n_curves=24, size=160)
+    p = Params(delta_c=delta_c, tile=tile)
+    up = np.random.default_rng(6).normal(size=3 * 160 * 160)
+    a = gpu_run(b, p, upstream=up)
+    c = gpu_run(b, p.replace(chunk=512), upstream=up)
+    print("pairs", len(a["idx"]), flush=True)
+    np.testing.assert_array_equal(a["idx"], c["idx"])
+    n = int((c["ranges"][:, 1] - c["ranges"][:, 0]).max())
+    assert (np.abs(np.ravel(a["image"]) - np.ravel(c["image"])) <= 2 * n * EPS32 + p.eps_T).all()
+    assert all(np.isfinite(a["grads"][n]).all() for n in PARAM_NAMES)
+    assert grad_close(a["grads"], c["grads"], rtol=1e-4, atol=1e-6) <= 1.0

@@ -198,9 +198,10 @@ typedef struct {
                        of two in
                        [512, 8192], or 0: chosen by nsplat_bin on the device
                        from the pair count (with fills about pairs x quadrants
-                       per tile / (8 x compute units), rounded to a power of
-                       two in [512, 8192]; without, 512, or down to 128 for
-                       small launches at 8 x 8 and 16 x 16 tiles).
+                       per tile / (8 x compute units), a quarter of it where
+                       strokes or fills at h != 1 are walked, rounded to a
+                       power of two in [512, 8192]; without, 512, or down to
+                       128 for small launches at 8 x 8 and 16 x 16 tiles).
                        At 0 the forward may also take a long list with
                        several wavefronts, depending on the pair count.
                        It only changes FP32 rounding.                        */

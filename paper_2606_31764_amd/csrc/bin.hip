@@ -581,15 +581,23 @@ __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict
 // Forward-state checkpoints of tile t: one per chunk boundary inside its list.
 // The launch's log2 chunk length: the caller's (ck_arg >= 0), or chosen from
 // the pair count.
-__device__ inline int launch_chunk_log2(int ck_arg, const int32_t* counters, int quads, int n_cu) {
-  if (ck_arg >= 0) return ck_arg;
+struct ChunkArg {
+  int ck_arg;
+  float h;
+  const float* h_dev;
+};
+__device__ inline int launch_chunk_log2(const ChunkArg& ca, const int32_t* queue, const int32_t* counters, int quads,
+                                        int n_cu) {
+  if (ca.ck_arg >= 0) return ca.ck_arg;
   const int64_t pairs = counters[NSPLAT_CNT_PAIRS];
-  return ck_arg == CK_ARG_SMALL ? small_chunk_log2(pairs, quads, n_cu) : auto_chunk_log2(pairs, quads, n_cu);
+  if (ca.ck_arg == CK_ARG_SMALL) return small_chunk_log2(pairs, quads, n_cu);
+  const bool runs = (ca.h_dev ? *ca.h_dev : ca.h) == 1.0f && (int64_t)queue[Q_NSTROKE] * 8 <= queue[Q_NFILL];
+  return auto_chunk_log2(pairs, quads, n_cu, runs);
 }
 
-__global__ void k_chunk_counts(const int32_t* __restrict__ ranges, int n_tiles, int ck_arg, const int32_t* counters,
+__global__ void k_chunk_counts(const int32_t* __restrict__ ranges, int n_tiles, ChunkArg ca, const int32_t* counters,
                                int quads, int n_cu, int32_t* __restrict__ queue, uint32_t* __restrict__ ck) {
-  const int ck_lg = launch_chunk_log2(ck_arg, counters, quads, n_cu);
+  const int ck_lg = launch_chunk_log2(ca, queue, counters, quads, n_cu);
   if (blockIdx.x == 0 && threadIdx.x == 0) queue[Q_CKLG] = ck_lg;
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n_tiles; t += gridDim.x * blockDim.x) {
     const int n = n_chunks(ranges[2 * t + 1] - ranges[2 * t], ck_lg);
@@ -616,12 +624,11 @@ __device__ inline int tile_blocks(int blocks, const SceneTab* st, int n_scenes, 
 }
 
 // Adjoint work items of the tile at blend-order position i: quadrants x chunks.
-// (quads, the forward's quadrants per tile, feeds the chunk rule; blocks is
-// the adjoint's pixel blocks per chunk, see tile_blocks)
+// (blocks is the adjoint's pixel blocks per chunk, see tile_blocks)
 __global__ void k_item_counts(const int32_t* __restrict__ ranges, const int32_t* __restrict__ order, int n_tiles,
-                              int quads, int blocks, const SceneTab* st, int n_scenes, int ck_arg,
-                              const int32_t* counters, int n_cu, uint32_t* __restrict__ items) {
-  const int ck_lg = launch_chunk_log2(ck_arg, counters, quads, n_cu);
+                              int blocks, const SceneTab* st, int n_scenes, const int32_t* __restrict__ queue,
+                              uint32_t* __restrict__ items) {
+  const int ck_lg = queue[Q_CKLG];
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_tiles; i += gridDim.x * blockDim.x) {
     const int t = order[i];
     const int nb = tile_blocks(blocks, st, n_scenes, t);
@@ -653,7 +660,7 @@ __device__ inline uint32_t plan_wave_scan(uint32_t v) {
 // starts (or at the pair count); empty tiles get [0, 0).
 __global__ __launch_bounds__(PLAN_THREADS) void k_tile_plan(int32_t* __restrict__ ranges, int n_tiles, int quads,
                                                             int blocks, const SceneTab* st, int n_scenes,
-                                                            int ck_arg, int split, int n_cu,
+                                                            ChunkArg ca, int split, int n_cu,
                                                             int32_t* __restrict__ queue,
                                                             int32_t* __restrict__ order, int32_t* __restrict__ ck_off,
                                                             int32_t* __restrict__ item_off,
@@ -662,7 +669,7 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_tile_plan(int32_t* __restrict_
   __shared__ int h[32], base[32];
   __shared__ uint32_t wsum[2][PLAN_THREADS / 64];
   const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
-  const int ck_lg = launch_chunk_log2(ck_arg, counters, quads, n_cu);
+  const int ck_lg = launch_chunk_log2(ca, queue, counters, quads, n_cu);
   if (tid == 0) queue[Q_CKLG] = ck_lg;
   if (hist) {
     const uint32_t total = (uint32_t)counters[NSPLAT_CNT_PAIRS];
@@ -761,6 +768,7 @@ hipError_t launch_bin(const Launch& L) {
   const Gauss* gs = (const Gauss*)L.bf->gauss;
   const int gg = grid_for(gcap, 256, 8192);
   const int split = split_long(*L.pr);
+  const ChunkArg ca = {L.ck_lg, L.pr->h, L.pr->h_dev};
   // number of key bits and radix passes (up to RADIX_BITS_MAX bits each)
   int key_bits = 0;
   while (key_bits < 31 && ((int64_t)1 << key_bits) < L.n_tiles) ++key_bits;
@@ -804,7 +812,7 @@ hipError_t launch_bin(const Launch& L) {
     if (one) {
       Phase ph(L, NSPLAT_T_RANGES);
       hipLaunchKernelGGL(k_tile_plan, dim3(1), dim3(PLAN_THREADS), 0, L.stream, L.bf->ranges, (int)L.n_tiles,
-                         L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, L.ck_lg,
+                         L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, ca,
                          split, L.n_cu, L.w.queue, L.w.order, L.w.ck_off, L.w.item_off,
                          (const uint32_t*)L.w.hist, nbk, nd, cnt, 1);
       return hipGetLastError();
@@ -854,7 +862,7 @@ hipError_t launch_bin(const Launch& L) {
                          L.bf->ranges);
     if (nt > 0 && nt <= SMALL_TILES) {
       hipLaunchKernelGGL(k_tile_plan, dim3(1), dim3(PLAN_THREADS), 0, L.stream, L.bf->ranges, nt,
-                         L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, L.ck_lg,
+                         L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, ca,
                          split, L.n_cu, L.w.queue, L.w.order, L.w.ck_off, L.w.item_off,
                          from_hist ? (const uint32_t*)L.w.hist : nullptr, sb, 1 << key_bits, cnt, 0);
     } else if (nt > 0) {
@@ -864,13 +872,12 @@ hipError_t launch_bin(const Launch& L) {
                          L.pr->tile == 8 ? 1 : 4, L.n_cu);
       hipLaunchKernelGGL(k_order_scatter, dim3(ob), dim3(256), 0, L.stream, L.bf->ranges, nt, L.w.obin, L.w.order);
       const int cb = grid_for(nt, 256, 4096);
-      hipLaunchKernelGGL(k_chunk_counts, dim3(cb), dim3(256), 0, L.stream, L.bf->ranges, nt, L.ck_lg, cnt,
+      hipLaunchKernelGGL(k_chunk_counts, dim3(cb), dim3(256), 0, L.stream, L.bf->ranges, nt, ca, cnt,
                          L.pr->tile == 8 ? 1 : 4, L.n_cu, L.w.queue, (uint32_t*)L.w.ck_off);
       e = launch_scan((uint32_t*)L.w.ck_off, nullptr, nt, (uint32_t*)L.w.ck_off + nt, L.w.scan_tmp, L.stream);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(k_item_counts, dim3(cb), dim3(256), 0, L.stream, L.bf->ranges, L.w.order, nt,
-                         L.pr->tile == 8 ? 1 : 4, adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, L.ck_lg,
-                         cnt, L.n_cu, (uint32_t*)L.w.item_off);
+                         adj_blocks_of(L), L.w.scenes, (int)L.sc->n_scenes, L.w.queue, (uint32_t*)L.w.item_off);
       e = launch_scan((uint32_t*)L.w.item_off, nullptr, nt, (uint32_t*)L.w.item_off + nt, L.w.scan_tmp, L.stream);
       if (e != hipSuccess) return e;
     } else {

@@ -84,13 +84,23 @@ struct Work {
 // store is sized for.
 constexpr int CK_MIN = 512, CK_MAX = 8192;
 __host__ __device__ inline int n_chunks(int len, int ck_lg) { return (len + (1 << ck_lg) - 1) >> ck_lg; }
-// About one adjoint item per two wavefront slots of the GPU: pairs x
-// quadrants / (8 x compute units) positions per chunk, rounded to a power of
-// two in [CK_MIN, CK_MAX].  Large launches keep whole lists together (fewer
-// stored states and item set-ups); small ones split long lists across
-// wavefronts.
-__host__ __device__ inline int auto_chunk_log2(int64_t pairs, int quads, int n_cu) {
-  const double v = (double)pairs * quads / (8.0 * (n_cu > 0 ? n_cu : 1));
+// With fills: pairs x quadrants / (8 x compute units) list positions, about one
+// adjoint item per two wavefront slots of the GPU.  Fill runs at h = 1 (runs)
+// are walked whole, and each chunk boundary in one costs a walk more, so that
+// longer chunks would be faster still (100 paths at 512^2 in 32 x 32 tiles,
+// forward and adjoint, at chunks of 512, 1024, 2048, 4096: 0.386, 0.342, 0.289,
+// 0.263 ms; the rule takes 1024), but the adjoint divides T back over a chunk
+// and loses precision with its length.  Entries taken one by one (strokes, more
+// than an eighth of the fill Gaussians, or fills at another h) take an adjoint
+// wavefront ten times as long per position, so that the longest chunk sets the
+// length of the pass: a quarter.  Adjoint at chunks of 512, 1024, 2048, 4096,
+// 8192: 16 mixed scenes at 768^2 in 32 x 32 tiles 1.66, 1.32, 1.26, 1.41, 1.46
+// ms (8192 without the quarter), 4 at 512^2 0.32, 0.44, 0.66, 0.96, 1.11 (1024),
+// 8 at 768^2 1.22, 0.92, 0.90, 1.07, 1.05 (4096).
+// Rounded to a power of two in [CK_MIN, CK_MAX].
+__host__ __device__ inline int auto_chunk_log2(int64_t pairs, int quads, int n_cu, bool runs) {
+  double v = (double)pairs * quads / (8.0 * (n_cu > 0 ? n_cu : 1));
+  if (!runs) v *= 0.25;
   int lg = 9;
   while ((1 << lg) < CK_MAX && v >= 1.4142135623730951 * (double)(1 << lg)) ++lg;
   return lg;

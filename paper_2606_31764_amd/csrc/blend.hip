@@ -20,8 +20,9 @@ namespace nsp {
 namespace {
 
 // Work decomposition: one wavefront per (tile, quadrant) item.  8x8 tiles are
-// one quadrant; 16x16 and 32x32 tiles have four (8x8 or 16x16 pixels), and
-// each lane owns a BLK x BLK block of its quadrant.  A wavefront walks the
+// one quadrant; 16x16 and 32x32 tiles have four (8x8 or, in the adjoint of
+// scenes without fills, 16x16 pixels; see FwdCfg and AdjCfg), and each lane
+// owns a BLK x BLK block of its quadrant.  A wavefront walks the
 // tile's list in steps of up to 64 entries (64 E in the adjoint): every lane
 // loads one (E; the next step's loads are issued before the current step is
 // processed), entries whose support disc misses the quadrant are dropped, the rest are
@@ -40,14 +41,24 @@ constexpr int WPB = 4;                  // wavefronts per block
 constexpr int KIND_ANI = 1, KIND_FILL = 2;
 constexpr int BLOCK = 64 * WPB;
 
+// The forward's pixel blocks (its quadrants): 8 x 8 pixels at every tile side,
+// one per lane.  At 32 x 32 tiles the sixteen of them drop four times the
+// entries that blocks of 16 x 16 with 2 x 2 pixels per lane did, and are four
+// times the wavefronts with a quarter of the work per entry: 16 mixed scenes at
+// 768^2 0.695 -> 0.571 ms, 4 at 512^2 0.498 -> 0.204, 100 fill paths at 512^2
+// 0.235 -> 0.069.
 template <int TILE>
-__device__ inline void pixel_of(int quad, int lane, int q, int* lx, int* ly) {
-  using Cfg = TileCfg<TILE>;
-  *lx = (quad & 1) * Cfg::SUB + (lane & 7) * Cfg::BLK + q % Cfg::BLK;
-  *ly = (quad >> 1) * Cfg::SUB + (lane >> 3) * Cfg::BLK + q / Cfg::BLK;
+struct FwdCfg {
+  static constexpr int SUB = 8, COLS = TILE / 8, QUADS = COLS * COLS;
+};
+
+template <int TILE>
+__device__ inline void pixel_of(int blk, int lane, int* lx, int* ly) {
+  *lx = (blk % FwdCfg<TILE>::COLS) * 8 + (lane & 7);
+  *ly = (blk / FwdCfg<TILE>::COLS) * 8 + (lane >> 3);
 }
 
-// The adjoint's pixel blocks (adj_blocks): the forward's quadrants, or, for
+// The adjoint's pixel blocks (adj_blocks): the quadrants, or, for
 // the tiles of scenes with fills at 32 x 32 tiles, sixteen 8 x 8 blocks with
 // one pixel per lane.  Block b sits at column b % COLS, row b / COLS of the
 // tile; lane l owns the BLK x BLK pixels at column l & 7, row l >> 3 of it.
@@ -69,15 +80,11 @@ __device__ inline void adj_pixel(int blk, int lane, int q, int* lx, int* ly) {
   *ly = (blk / A::COLS) * A::SUB + (lane >> 3) * A::BLK + q / A::BLK;
 }
 
-// Slot of tile pixel (lx, ly) in a stored forward state: the forward's
-// (quadrant x pixels per lane + pixel) x 64 + lane, as pixel_of lays it out.
+// Slot of tile pixel (lx, ly) in a stored forward state: the forward's block
+// x 64 + lane, as pixel_of lays it out.
 template <int TILE>
 __device__ inline int fwd_slot(int lx, int ly) {
-  using F = TileCfg<TILE>;
-  const int quad = lx / F::SUB + 2 * (ly / F::SUB);
-  const int lane = (lx % F::SUB) / F::BLK + 8 * ((ly % F::SUB) / F::BLK);
-  const int q = lx % F::BLK + F::BLK * (ly % F::BLK);
-  return (quad * F::PPT + q) * 64 + lane;
+  return (lx / 8 + FwdCfg<TILE>::COLS * (ly / 8)) * 64 + lx % 8 + 8 * (ly % 8);
 }
 
 // Next work item of this wavefront: the static assignment, or the next entry
@@ -144,19 +151,13 @@ __device__ inline Box live_box_of(int qx, int qy, uint64_t live) {
   return b;
 }
 
-template <int TILE>
-__device__ inline Box live_box(int quad, uint64_t live) {
-  using Cfg = TileCfg<TILE>;
-  return live_box_of<Cfg>((quad & 1) * Cfg::SUB, (quad >> 1) * Cfg::SUB, live);
-}
-
 // All pixel centres of the quadrant.
 template <int TILE>
 __device__ inline Box quad_box(int quad) {
-  using Cfg = TileCfg<TILE>;
+  using Cfg = FwdCfg<TILE>;
   Box b;
-  b.x0 = (float)((quad & 1) * Cfg::SUB);
-  b.y0 = (float)((quad >> 1) * Cfg::SUB);
+  b.x0 = (float)((quad % Cfg::COLS) * Cfg::SUB);
+  b.y0 = (float)((quad / Cfg::COLS) * Cfg::SUB);
   b.x1 = b.x0 + (float)(Cfg::SUB - 1);
   b.y1 = b.y0 + (float)(Cfg::SUB - 1);
   return b;
@@ -413,8 +414,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
                                            float* __restrict__ Tfin, int32_t* __restrict__ nlast,
                                            const int32_t* __restrict__ plan, int64_t gcap, int ck_lg,
                                            bool fill_lattice, char* mine_lds) {
-  using Cfg = TileCfg<TILE>;
-  constexpr int PPT = Cfg::PPT;
+  using Cfg = FwdCfg<TILE>;
   constexpr bool ANI = (KIND & KIND_ANI) != 0;
   const float amax = pr.alpha_max, eps = pr.eps_T, ks = pr.k_sigma;
   const float inv_tile = 1.0f / (float)TILE;
@@ -432,55 +432,41 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
   // run began, and adds col (Tst - T) where the run ends.  Runs end where
   // the curve changes between consecutive composited entries, at chunk
   // boundaries and at the end, all fixed by the list, so the result does not
-  // depend on the batch depth.  At one pixel per lane the image's sums (tot,
-  // runs from Trun) are kept apart from the chunks' and don't end at their
-  // boundaries, so that an image does not depend on the chunk length either,
-  // which a small launch takes shorter.
-  constexpr bool TOT = PPT == 1;
-  float px[PPT], py[PPT], T[PPT], Tst[PPT], acc[PPT][3];
-  float tot[3] = {0.0f, 0.0f, 0.0f}, Trun = 0.0f;
-  int stop[PPT];
+  // depend on the batch depth.  The image's sums (tot, runs from Trun) are kept
+  // apart from the chunks' and don't end at their boundaries, so that an image
+  // does not depend on the chunk length either, which a small launch takes
+  // shorter.
   int run_curve = -1, run_kind = 0;
   float rc0 = 0.0f, rc1 = 0.0f, rc2 = 0.0f;  // the run's colour
-#pragma unroll
-  for (int q = 0; q < PPT; ++q) {
-    int lx, ly;
-    pixel_of<TILE>(quad, lane, q, &lx, &ly);
-    px[q] = (float)lx;
-    py[q] = (float)ly;
-    // a pixel is live while T >= eps_T (0 <= eps_T <= 1): T only falls,
-    // and it falls below eps_T exactly at the entry where the pixel stops;
-    // pixels outside the image start at T = 0
-    T[q] = (x0 + lx < st.W && y0 + ly < st.H) ? 1.0f : 0.0f;
-    Tst[q] = T[q];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) acc[q][c] = 0.0f;
-    stop[q] = start;
-  }
-  Trun = T[0];
-  // pixel q's share of the chunk's colour from the current run so far
-  auto close_chunk = [&](int q) {
-    const float a = Tst[q] - T[q];
-    acc[q][0] = __builtin_fmaf(rc0, a, acc[q][0]);
+  int lx, ly;
+  pixel_of<TILE>(quad, lane, &lx, &ly);
+  const float px = (float)lx, py = (float)ly;
+  // a pixel is live while T >= eps_T (0 <= eps_T <= 1): T only falls,
+  // and it falls below eps_T exactly at the entry where the pixel stops;
+  // pixels outside the image start at T = 0
+  float T = (x0 + lx < st.W && y0 + ly < st.H) ? 1.0f : 0.0f;
+  float Tst = T, Trun = T, acc[3] = {0.0f, 0.0f, 0.0f}, tot[3] = {0.0f, 0.0f, 0.0f};
+  int stop = start;
+  // the pixel's share of the chunk's colour from the current run so far
+  auto close_chunk = [&]() {
+    const float a = Tst - T;
+    acc[0] = __builtin_fmaf(rc0, a, acc[0]);
     if (C == 3) {
-      acc[q][1] = __builtin_fmaf(rc1, a, acc[q][1]);
-      acc[q][2] = __builtin_fmaf(rc2, a, acc[q][2]);
+      acc[1] = __builtin_fmaf(rc1, a, acc[1]);
+      acc[2] = __builtin_fmaf(rc2, a, acc[2]);
     }
-    Tst[q] = T[q];
+    Tst = T;
   };
   // the end of a run
   auto close_run = [&]() {
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) close_chunk(q);
-    if (TOT) {
-      const float a = Trun - T[0];
-      tot[0] = __builtin_fmaf(rc0, a, tot[0]);
-      if (C == 3) {
-        tot[1] = __builtin_fmaf(rc1, a, tot[1]);
-        tot[2] = __builtin_fmaf(rc2, a, tot[2]);
-      }
-      Trun = T[0];
+    close_chunk();
+    const float a = Trun - T;
+    tot[0] = __builtin_fmaf(rc0, a, tot[0]);
+    if (C == 3) {
+      tot[1] = __builtin_fmaf(rc1, a, tot[1]);
+      tot[2] = __builtin_fmaf(rc2, a, tot[2]);
     }
+    Trun = T;
   };
   const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
   const Box qbox = quad_box<TILE>(quad);
@@ -517,7 +503,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
       rc2 = col2;
       run_curve = fr.c;
     }
-    const int qx = (quad & 1) * Cfg::SUB, qy = (quad >> 1) * Cfg::SUB;
+    const int qx = (quad % Cfg::COLS) * Cfg::SUB, qy = (quad / Cfg::COLS) * Cfg::SUB;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -535,28 +521,22 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
 #pragma unroll
     for (int it = 0; it < FNIT; ++it) neg = neg || !(og[it] >= 0.0f);
     const bool nonneg = __ballot(neg) == 0ull;  // no negative (or NaN) opacity in the run
-    int nb[PPT];
-    const int nb0 = end - ((n_ck + 1) << ck_lg);  // the next chunk boundary still to store
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) nb[q] = nb0;
-    // pixel q's LDS cell and the list position of its own lattice point:
-    // those of the lane's first pixel plus q's offset in the lane's block
-    int lx0, ly0;
-    pixel_of<TILE>(quad, lane, 0, &lx0, &ly0);
-    const int cell0 = (ly0 - qy + FR_R) * NB + (lx0 - qx + FR_R);
-    const int pb0 = fr.p_lo + (y0 + ly0 - fr.iy0 - fr.j0) * fr.w + (x0 + lx0 - fr.ix0 - fr.i0);
-    // the state of pixel q at chunk boundary nb[q] (all positions >= it done)
-    auto store_boundary = [&](int q) {
-      close_chunk(q);
-      float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - nb[q]) >> ck_lg) - 1) * (4 * TILE * TILE);
-      const int slot = (quad * PPT + q) * 64 + lane;
-      ckp[slot] = T[q];
+    int nb = end - ((n_ck + 1) << ck_lg);  // the next chunk boundary still to store
+    // the pixel's LDS cell and the list position of its own lattice point
+    const int cell0 = (ly - qy + FR_R) * NB + (lx - qx + FR_R);
+    const int pb0 = fr.p_lo + (y0 + ly - fr.iy0 - fr.j0) * fr.w + (x0 + lx - fr.ix0 - fr.i0);
+    // the state at chunk boundary nb (all positions >= it done)
+    auto store_boundary = [&]() {
+      close_chunk();
+      float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - nb) >> ck_lg) - 1) * (4 * TILE * TILE);
+      const int slot = quad * 64 + lane;
+      ckp[slot] = T;
 #pragma unroll
       for (int ch = 0; ch < C; ++ch) {
-        ckp[(1 + ch) * TILE * TILE + slot] = acc[q][ch];
-        acc[q][ch] = 0.0f;
+        ckp[(1 + ch) * TILE * TILE + slot] = acc[ch];
+        acc[ch] = 0.0f;
       }
-      nb[q] -= 1 << ck_lg;
+      nb -= 1 << ck_lg;
     };
     // A run that holds no chunk boundary, no negative opacity and none that
     // alpha_max could cut at a distance of 1 or more (all but the pixel's own
@@ -568,67 +548,61 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     bool cut = false;
 #pragma unroll
     for (int it = 0; it < FNIT; ++it) cut = cut || !(og[it] * G1 <= amax);
-    if (nonneg && fr.p_lo >= nb0 && __ballot(cut) == 0ull) {
+    if (nonneg && fr.p_lo >= nb && __ballot(cut) == 0ull) {
       const int Y = y0 + qy - fr.iy0;  // the quadrant's first window row
       const int d_lo = max(-FR_R, fr.j0 - (Y + Cfg::SUB - 1)), d_hi = min(FR_R, fr.j1 - Y);
+      auto row = [&](auto row_tag) {
+        constexpr int dy = decltype(row_tag)::value;
+        constexpr int dxm = dy * dy <= 4 ? 4 : (dy * dy == 9 ? 3 : 2);  // dx^2 + dy^2 <= FR_R2
+        if (dy < d_lo || dy > d_hi) return;
+        const int roff = cell0 + dy * NB;
+        float f[2 * FR_R + 1], Tr = T;
 #pragma unroll
-      for (int q = 0; q < PPT; ++q) {
-        auto row = [&](auto row_tag) {
-          constexpr int dy = decltype(row_tag)::value;
-          constexpr int dxm = dy * dy <= 4 ? 4 : (dy * dy == 9 ? 3 : 2);  // dx^2 + dy^2 <= FR_R2
-          if (dy < d_lo || dy > d_hi) return;
-          const int roff = cell0 + (q / Cfg::BLK + dy) * NB + q % Cfg::BLK;
-          float f[2 * FR_R + 1], Tr = T[q];
+        for (int dx = -dxm; dx <= dxm; ++dx) f[dx + FR_R] = ol[roff + dx];
 #pragma unroll
-          for (int dx = -dxm; dx <= dxm; ++dx) f[dx + FR_R] = ol[roff + dx];
+        for (int dx = dxm; dx >= -dxm; --dx) {
+          const float oG = f[dx + FR_R] * __int_as_float(__builtin_amdgcn_readlane(gtab, dx * dx + dy * dy));
+          f[dx + FR_R] = 1.0f - (dx == 0 && dy == 0 ? fminf(amax, oG) : oG);
+          Tr = Tr * f[dx + FR_R];
+        }
+        const bool live = T >= eps;
+        if (__ballot(live && !(Tr >= eps)) == 0ull) {
+          T = live ? Tr : T;
+          return;
+        }
+        // some pixel stops inside the row: cell by cell
+        const int rpos = pb0 + dy * fr.w;
 #pragma unroll
-          for (int dx = dxm; dx >= -dxm; --dx) {
-            const float oG = f[dx + FR_R] * __int_as_float(__builtin_amdgcn_readlane(gtab, dx * dx + dy * dy));
-            f[dx + FR_R] = 1.0f - (dx == 0 && dy == 0 ? fminf(amax, oG) : oG);
-            Tr = Tr * f[dx + FR_R];
-          }
-          const bool live = T[q] >= eps;
-          if (__ballot(live && !(Tr >= eps)) == 0ull) {
-            T[q] = live ? Tr : T[q];
-            return;
-          }
-          // some pixel stops inside the row: cell by cell
-          const int rpos = pb0 + (q / Cfg::BLK + dy) * fr.w + q % Cfg::BLK;
-#pragma unroll
-          for (int dx = dxm; dx >= -dxm; --dx) {
-            const float Tn = T[q] * f[dx + FR_R];
-            const bool lv = T[q] >= eps;
-            stop[q] = (lv && Tn < eps) ? rpos + dx : stop[q];
-            T[q] = lv ? Tn : T[q];
-          }
-        };
-        row(std::integral_constant<int, 4>{});
-        row(std::integral_constant<int, 3>{});
-        row(std::integral_constant<int, 2>{});
-        row(std::integral_constant<int, 1>{});
-        row(std::integral_constant<int, 0>{});
-        if (q == 0) next_row();
-        row(std::integral_constant<int, -1>{});
-        row(std::integral_constant<int, -2>{});
-        row(std::integral_constant<int, -3>{});
-        row(std::integral_constant<int, -4>{});
-        static_assert(FR_R == 4, "nine rows");
-      }
-    } else
-    // pixels are independent here: one pixel's whole walk at a time
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
+        for (int dx = dxm; dx >= -dxm; --dx) {
+          const float Tn = T * f[dx + FR_R];
+          const bool lv = T >= eps;
+          stop = (lv && Tn < eps) ? rpos + dx : stop;
+          T = lv ? Tn : T;
+        }
+      };
+      row(std::integral_constant<int, 4>{});
+      row(std::integral_constant<int, 3>{});
+      row(std::integral_constant<int, 2>{});
+      row(std::integral_constant<int, 1>{});
+      row(std::integral_constant<int, 0>{});
+      next_row();
+      row(std::integral_constant<int, -1>{});
+      row(std::integral_constant<int, -2>{});
+      row(std::integral_constant<int, -3>{});
+      row(std::integral_constant<int, -4>{});
+      static_assert(FR_R == 4, "nine rows");
+    } else {
 #pragma unroll 1
       for (int dy = FR_R; dy >= -FR_R; --dy) {
         const int dxm = dy * dy <= 4 ? 4 : (dy * dy == 9 ? 3 : 2);  // dx^2 + dy^2 <= FR_R2
-        const int roff = cell0 + (q / Cfg::BLK + dy) * NB + q % Cfg::BLK;
-        const int rpos = pb0 + (q / Cfg::BLK + dy) * fr.w + q % Cfg::BLK;
+        const int roff = cell0 + dy * NB;
+        const int rpos = pb0 + dy * fr.w;
         {
           // a row with no Gaussian still to composite for any live pixel
           // changes nothing (chunk boundaries it crosses are stored with
           // the unchanged state at the end)
-          const int jr = y0 + ly0 + q / Cfg::BLK + dy - fr.iy0, ir = x0 + lx0 + q % Cfg::BLK - fr.ix0;
-          const bool any = T[q] >= eps && jr >= fr.j0 && jr <= fr.j1 && ir + dxm >= fr.i0 && ir - dxm <= fr.i1 &&
+          const int jr = y0 + ly + dy - fr.iy0, ir = x0 + lx - fr.ix0;
+          const bool any = T >= eps && jr >= fr.j0 && jr <= fr.j1 && ir + dxm >= fr.i0 && ir - dxm <= fr.i1 &&
                            rpos - dxm <= top;
           if (__ballot(any) == 0ull) continue;
         }
@@ -644,26 +618,26 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
           const float o = orow[dx + FR_R];
           const int pos = rpos + dx;
           if (check && o != 0.0f)
-            while (pos < nb[q]) store_boundary(q);
-          const float Tn = T[q] * (1.0f - fminf(amax, o * G));
-          const bool live = T[q] >= eps;
-          stop[q] = (live && Tn < eps) ? pos : stop[q];
-          T[q] = live ? Tn : T[q];
+            while (pos < nb) store_boundary();
+          const float Tn = T * (1.0f - fminf(amax, o * G));
+          const bool live = T >= eps;
+          stop = (live && Tn < eps) ? pos : stop;
+          T = live ? Tn : T;
         };
         // a chunk boundary falls in the row of some lane only now and then
-        if (__ballot(rpos - dxm < nb[q]) == 0ull) {
+        if (__ballot(rpos - dxm < nb) == 0ull) {
           // With no negative opacity in the run T does not grow along the
           // row, so a pixel live at its start whose T ends it at or above
           // eps_T was live at every cell: the row's product, with no stop
           // test, is then the cell-by-cell result.  Only where some pixel
           // stops inside the row is the row taken cell by cell.
-          float Tr = T[q];
+          float Tr = T;
 #pragma unroll
           for (int dx = FR_R; dx >= -FR_R; --dx)
             if (dx <= dxm && dx >= -dxm) Tr = Tr * (1.0f - fminf(amax, orow[dx + FR_R] * Gr[dx < 0 ? -dx : dx]));
-          const bool live = T[q] >= eps;
+          const bool live = T >= eps;
           if (nonneg && __ballot(live && !(Tr >= eps)) == 0ull) {
-            T[q] = live ? Tr : T[q];
+            T = live ? Tr : T;
           } else {
 #pragma unroll
             for (int dx = FR_R; dx >= -FR_R; --dx)
@@ -678,9 +652,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     }
     // boundaries at or above the run's bottom (none at or below start)
     const int bl = max(fr.p_lo, start + 1);
-#pragma unroll
-    for (int q = 0; q < PPT; ++q)
-      while (nb[q] >= bl) store_boundary(q);
+    while (nb >= bl) store_boundary();
     n_ck = (end - bl) >> ck_lg;
   };
   while (hi > start) {
@@ -697,7 +669,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
           fill_run_at(plan, prow, c, __builtin_amdgcn_readfirstlane(e.g), __builtin_amdgcn_readfirstlane(e.r.local),
                       sg, hi - 1, start, end, 1.0, ks, inv_tile, st, lt, TILE, &fr)) {
         // the opacities and the corner check in flight together
-        const int ib = x0 + (quad & 1) * Cfg::SUB - fr.ix0 - FR_R, jb = y0 + (quad >> 1) * Cfg::SUB - fr.iy0 - FR_R;
+        const int ib = x0 + (quad % Cfg::COLS) * Cfg::SUB - fr.ix0 - FR_R, jb = y0 + (quad / Cfg::COLS) * Cfg::SUB - fr.iy0 - FR_R;
         fill_gather<FNB, FNIT>(w.gop, gcap, fr, ib, jb, fr.p_lo, hi - 1, 0.0f, og);
         take = fill_corners_ok(idx, fr);
       }
@@ -713,10 +685,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
         load_entry(idx, gs, w.gcol, hi - 1 - lane, lane < hi - lo_s, &e);
         gnext = lane < nhi - nlo ? idx[nhi - 1 - lane] : 0;
         fill_run_fwd(fr, col0, col1, col2, top, og);
-        bool done = true;
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) done = done && !(T[q] >= eps);
-        if (__ballot(!done) == 0ull) break;  // every pixel of the quadrant has stopped
+        if (__ballot(T >= eps) == 0ull) break;  // every pixel of the quadrant has stopped
         continue;
       }
     }
@@ -756,13 +725,8 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     // entry before, the first one compared with the previous step's run)
     const int prev = lane == 0 ? run_curve : wrec[lane > 0 ? lane - 1 : 0].curve;
     const uint64_t rs = __ballot(lane < cnt && wrec[lane].curve != prev);
-    int last[PPT];   // the pixel's last composited entry of the step
-    bool was[PPT];  // live in front of it
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      last[q] = 0;
-      was[q] = T[q] >= eps;
-    }
+    int last = 0;                // the pixel's last composited entry of the step
+    const bool was = T >= eps;  // live in front of the step
     for (int j = 0; j < cnt;) {
       // this segment: j up to the next run start (or the step's end)
       const uint64_t after = j < 63 ? rs & (~0ull << (j + 1)) : 0ull;
@@ -782,43 +746,32 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
         for (; j < jend; ++j) {
           const float4 gm = wrec[j].geo;
           const float op = wrec[j].op, rq = __int_as_float(wrec[j].g);
-#pragma unroll
-          for (int q = 0; q < PPT; ++q) {
-            const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-            const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
-            const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
-            const float m = __builtin_fmaf(a, a, b * b);
-            const float G = __builtin_amdgcn_exp2f(-m);
-            const bool in = (m <= lim) && (T[q] >= eps);
-            const float Tn = T[q] * (1.0f - fminf(amax, op * G));
-            last[q] = in ? j : last[q];
-            T[q] = in ? Tn : T[q];
-          }
+          const float dx = px - gm.x, dy = py - gm.y;
+          const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
+          const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
+          const float m = __builtin_fmaf(a, a, b * b);
+          const float G = __builtin_amdgcn_exp2f(-m);
+          const bool in = (m <= lim) && (T >= eps);
+          const float Tn = T * (1.0f - fminf(amax, op * G));
+          last = in ? j : last;
+          T = in ? Tn : T;
         }
       }
 #pragma unroll 8
       for (; j < jend; ++j) {
         const float4 gm = wrec[j].geo;
         const float op = wrec[j].op;
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-          const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-          const float d2 = __builtin_fmaf(dx, dx, dy * dy);
-          const float G = __builtin_amdgcn_exp2f(gm.w * d2);
-          const bool in = (d2 <= gm.z) && (T[q] >= eps);
-          const float Tn = T[q] * (1.0f - fminf(amax, op * G));
-          last[q] = in ? j : last[q];
-          T[q] = in ? Tn : T[q];
-        }
+        const float dx = px - gm.x, dy = py - gm.y;
+        const float d2 = __builtin_fmaf(dx, dx, dy * dy);
+        const float G = __builtin_amdgcn_exp2f(gm.w * d2);
+        const bool in = (d2 <= gm.z) && (T >= eps);
+        const float Tn = T * (1.0f - fminf(amax, op * G));
+        last = in ? j : last;
+        T = in ? Tn : T;
       }
     }
-    bool mine = true;
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      mine = mine && !(T[q] >= eps);
-      // a pixel that stopped in this step did so at the last entry it took
-      if (was[q] && T[q] < eps) stop[q] = wrec[last[q]].pos;
-    }
+    // a pixel that stopped in this step did so at the last entry it took
+    if (was && T < eps) stop = wrec[last].pos;
     hi = nhi;
     lo_s = nlo;
     nhi = n2hi;
@@ -828,22 +781,18 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
       // chunk just finished contributed (the current run closed at the
       // boundary; the sum restarts for the next chunk)
       float* ckp = w.ckbuf + (int64_t)(ck0 + ((end - hi) >> ck_lg) - 1) * (4 * TILE * TILE);
+      close_chunk();
+      const int slot = quad * 64 + lane;
+      ckp[slot] = T;
 #pragma unroll
-      for (int q = 0; q < PPT; ++q) close_chunk(q);
-#pragma unroll
-      for (int q = 0; q < PPT; ++q) {
-        const int slot = (quad * PPT + q) * 64 + lane;
-        ckp[slot] = T[q];
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          ckp[(1 + c) * TILE * TILE + slot] = acc[q][c];
-          acc[q][c] = 0.0f;
-        }
+      for (int c = 0; c < C; ++c) {
+        ckp[(1 + c) * TILE * TILE + slot] = acc[c];
+        acc[c] = 0.0f;
       }
       ++n_ck;
     }
     __builtin_amdgcn_wave_barrier();
-    if (__ballot(!mine) == 0ull) break;  // every pixel of the quadrant has stopped
+    if (__ballot(T >= eps) == 0ull) break;  // every pixel of the quadrant has stopped
   }
   close_run();
   // Suffix sums over the chunks, back to front: each boundary's slot
@@ -854,33 +803,25 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
   const int64_t ck_first = (int64_t)ck0 * (4 * TILE * TILE);
   for (int k = n_ck; k >= 1; --k) {
     float* ckp = w.ckbuf + ck_first + (int64_t)(k - 1) * (4 * TILE * TILE);
+    const int slot = quad * 64 + lane;
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      const int slot = (quad * PPT + q) * 64 + lane;
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const float ch = ckp[(1 + c) * TILE * TILE + slot];
-        ckp[(1 + c) * TILE * TILE + slot] = acc[q][c];
-        acc[q][c] += ch;
-      }
+    for (int c = 0; c < C; ++c) {
+      const float ch = ckp[(1 + c) * TILE * TILE + slot];
+      ckp[(1 + c) * TILE * TILE + slot] = acc[c];
+      acc[c] += ch;
     }
   }
+  const int x = x0 + lx, y = y0 + ly;
+  if (x < st.W && y < st.H) {
+    const int64_t pix = (int64_t)st.pix_off + (int64_t)y * st.W + x;
+    const int64_t plane = (int64_t)st.H * st.W;
 #pragma unroll
-  for (int q = 0; q < PPT; ++q) {
-    int lx, ly;
-    pixel_of<TILE>(quad, lane, q, &lx, &ly);
-    const int x = x0 + lx, y = y0 + ly;
-    if (x < st.W && y < st.H) {
-      const int64_t pix = (int64_t)st.pix_off + (int64_t)y * st.W + x;
-      const int64_t plane = (int64_t)st.H * st.W;
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)y * st.W + x;
-        image[o] = __builtin_fmaf(T[q], bg[s * C + c], TOT ? tot[c] : acc[q][c]);
-      }
-      Tfin[pix] = T[q];
-      nlast[pix] = stop[q];
+    for (int c = 0; c < C; ++c) {
+      const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)y * st.W + x;
+      image[o] = __builtin_fmaf(T, bg[s * C + c], tot[c]);
     }
+    Tfin[pix] = T;
+    nlast[pix] = stop;
   }
 }
 
@@ -980,7 +921,6 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
                                           const float* __restrict__ bg, float* __restrict__ image,
                                           float* __restrict__ Tfin, int32_t* __restrict__ nlast, int ck_lg,
                                           FwdLds& L) {
-  static_assert(TileCfg<TILE>::PPT == 1, "one pixel per lane");
   constexpr bool ANI = (KIND & KIND_ANI) != 0;
   static_assert(sizeof(L.rec) + sizeof(L.col) >= sizeof(float) * FW * 64 * C, "colour sums fit");
   const float amax = pr.alpha_max, eps = pr.eps_T, ks = pr.k_sigma;
@@ -992,7 +932,7 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
   // A pixel is live while T >= eps_T (0 <= eps_T <= 1); -1 stands for a
   // stopped one (stopT, stopP) and for pixels outside the image.
   int lx, ly;
-  pixel_of<TILE>(quad, lane, 0, &lx, &ly);
+  pixel_of<TILE>(quad, lane, &lx, &ly);
   const float px = (float)lx, py = (float)ly;
   float T = (x0 + lx < im.st.W && y0 + ly < im.st.H) ? 1.0f : -1.0f;
   const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
@@ -1301,12 +1241,12 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
 // The first n_long tiles of the blend order (the binning's choice) take a
 // block per quadrant, the others a wavefront per quadrant, eight to a block.
 template <int C, int TILE, int KIND>
-__global__ __launch_bounds__(FWD_BLOCK, TileCfg<TILE>::PPT == 1 && !(KIND & KIND_FILL) ? 6 : 4) void k_blend_fwd(
+__global__ __launch_bounds__(FWD_BLOCK, KIND & KIND_FILL ? 4 : 6) void k_blend_fwd(
     nsplat_params pr, Work w, int n_scenes, int n_tiles, const Gauss* __restrict__ gs,
     const int32_t* __restrict__ ranges, const int32_t* __restrict__ idx, const float* __restrict__ bg,
     float* __restrict__ image, float* __restrict__ Tfin, int32_t* __restrict__ nlast, const int32_t* __restrict__ plan,
     int64_t gcap, int persistent, int ck_arg) {
-  using Cfg = TileCfg<TILE>;
+  using Cfg = FwdCfg<TILE>;
   __shared__ __align__(16) FwdLds L;
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
   // the chunk length: the caller's, or the one the binning chose
@@ -1345,11 +1285,10 @@ __global__ __launch_bounds__(FWD_BLOCK, TileCfg<TILE>::PPT == 1 && !(KIND & KIND
     im.y0 = (im.lt / im.st.tiles_x) * TILE;
     im.start = ranges[2 * im.tile];
     im.end = ranges[2 * im.tile + 1];
-    if constexpr (Cfg::PPT == 1)
-      if (whole) {
-        fwd_block<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, ck_lg, L);
-        continue;
-      }
+    if (whole) {
+      fwd_block<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, ck_lg, L);
+      continue;
+    }
     fwd_serial<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, plan, gcap, ck_lg, fill_lattice,
                               (char*)L.rec + wv * (64 * FWD_ENTRY_BYTES));
   }
@@ -1651,7 +1590,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
         // a pixel still live behind this chunk starts from the stored state,
         // one that stopped inside it from T_final with only the background
         // behind it (no chunk is stored after a pixel's stop is passed)
-        const int slot = Cfg::SPLIT ? fwd_slot<TILE>(lx, ly) : (quad * PPT + q) * 64 + lane;
+        const int slot = TILE == 32 ? fwd_slot<TILE>(lx, ly) : quad * 64 + lane;
         float behind[3] = {0.0f, 0.0f, 0.0f};
         T[q] = tf;
         if (stop[q] < c_lo) {  // then c_lo > start, so a chunk follows and ckn is set
@@ -2177,7 +2116,7 @@ inline int depth_factor(int batch) { return batch <= 64 ? 1 : (batch <= 128 ? 2 
 
 template <int C, int TILE, int KIND>
 hipError_t fwd_t(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
-  constexpr int QUADS = TileCfg<TILE>::QUADS;
+  constexpr int QUADS = FwdCfg<TILE>::QUADS;
   const int64_t n_items = L.n_tiles * QUADS;
   if (n_items <= 0) return hipSuccess;
   // blocks: one per item of a long list (at least LONG_LEAST positions each;

@@ -177,10 +177,9 @@ constexpr int Q_NLONG = 12;
 // LONG_LEAST 512, 256, 128: 32 strokes at 256^2 0.038, 0.028, 0.028 ms, 32
 // tangent-aligned ones (longest list 265) 0.029, 0.028, 0.022.
 constexpr int LONG_SHARE = 9, LONG_LEAST = 128;
-// Whether a launch may take long lists so: at one pixel per lane, and where
-// the chunk length is left to choose as well (both move the rounding with the
-// size of the launch).
-inline bool split_long(const nsplat_params& pr) { return pr.chunk == 0 && pr.tile <= 16; }
+// Whether a launch may take long lists so: where the chunk length is left to
+// choose as well (both move the rounding with the size of the launch).
+inline bool split_long(const nsplat_params& pr) { return pr.chunk == 0; }
 __device__ inline int long_class(int64_t pairs, int quads, int n_cu) {
   const int64_t len = pairs * quads / ((int64_t)LONG_SHARE * (n_cu > 0 ? n_cu : 1));
   return __builtin_clz((unsigned)(len < LONG_LEAST ? LONG_LEAST : len));

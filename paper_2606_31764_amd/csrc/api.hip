@@ -291,6 +291,12 @@ bool scene_table_current(nsplat_ctx* ctx, const void* ws, const nsplat_scenes* s
   return false;
 }
 
+// Whether a launch at 32 x 32 tiles declares fills (the binning and the adjoint
+// of a step must agree).
+int blocks_of(const Launch& L) {
+  return L.pr->tile == 32 ? ((L.cv->any_flags & NSPLAT_FILLED) ? 2 : 1) : 0;
+}
+
 void record_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int blocks) {
   for (auto& e : ctx->bin_tile)
     if (e.ws == ws) {
@@ -304,8 +310,8 @@ void record_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int b
 
 // NSPLAT_EINVAL when the workspace's tile lists were built (by this context)
 // for another tile side or params.chunk than this launch's, or (blocks > 0,
-// the adjoint) with adjoint items for another pixel-block split: at 32 x 32
-// tiles the split follows whether the curves declare fills.
+// the adjoint) for curves that declared fills where these do not, or the other
+// way round, at 32 x 32 tiles (blocks_of).
 int check_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int blocks = 0) {
   for (const auto& e : ctx->bin_tile) {
     if (e.ws != ws) continue;
@@ -316,9 +322,8 @@ int check_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int blo
       return fail(ctx, NSPLAT_EINVAL, "the tile lists of this workspace were built by nsplat_bin with chunk %d, "
                   "but params.chunk is %d", e.chunk, chunk);
     if (blocks > 0 && e.blocks != blocks)
-      return fail(ctx, NSPLAT_EINVAL, "the adjoint items of this workspace were built by nsplat_bin for %d pixel "
-                  "blocks per chunk, but these curves need %d (any_flags differs in NSPLAT_FILLED)", e.blocks,
-                  blocks);
+      return fail(ctx, NSPLAT_EINVAL, "the adjoint items (pixel blocks per chunk) of this workspace were built by "
+                  "nsplat_bin for other curves: any_flags differs in NSPLAT_FILLED");
   }
   return NSPLAT_OK;
 }
@@ -429,7 +434,7 @@ int nsplat_bin(nsplat_ctx* ctx, const nsplat_curves* cv, const nsplat_scenes* sc
   }
   if (h == hipSuccess) h = launch_bin(L);
   if (h != hipSuccess) return hip_fail(ctx, h, "nsplat_bin");
-  record_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, nsp::adj_blocks_of(L));
+  record_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, blocks_of(L));
   return NSPLAT_OK;
 }
 
@@ -453,7 +458,7 @@ int nsplat_backward_reg(nsplat_ctx* ctx, const nsplat_curves* cv, const nsplat_s
   int e = prepare(ctx, cv, sc, pr, bf, stream, &L);
   if (e) return e;
   if (!dL || !T_final || !n_last || !gr) return fail(ctx, NSPLAT_EINVAL, "dL_dimage / T_final / n_last / grads is NULL");
-  if ((e = check_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, nsp::adj_blocks_of(L)))) return e;
+  if ((e = check_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, blocks_of(L)))) return e;
   const bool use_reg = reg && (reg->bbox_weight != 0.0f || reg->deriv_weight != 0.0f);
   if (use_reg) {
     if (reg->deriv_weight != 0.0f && (reg->deriv_order < 1 || reg->deriv_order > 3))

@@ -8,21 +8,24 @@
 // forward stops a pixel once T < eps_T and a wavefront once all its pixels
 // have stopped, and stores each pixel's state at every chunk boundary (a
 // chunk is 2^ck_lg list positions, chosen per launch) it passes.  The
-// adjoint runs one wavefront per (tile, quadrant or 8x8 pixel block, chunk)
-// (AdjCfg), back to front from the state stored at the chunk's back
-// boundary, parks each Gaussian's per-lane gradient values in LDS and sums
-// a dozen or more such rows at a time, with one atomic per value and
-// wavefront.
+// adjoint runs one wavefront per (tile, quadrant, chunk), back to front from
+// the state stored at the chunk's back boundary, parks each Gaussian's
+// per-lane gradient values in LDS and sums a dozen or more such rows at a time,
+// with one atomic per value and wavefront.
 #include "nsplat_internal.h"
 
 namespace nsp {
 
 namespace {
 
-// Work decomposition: one wavefront per (tile, quadrant) item.  8x8 tiles are
-// one quadrant; 16x16 and 32x32 tiles have four (8x8 or, in the adjoint of
-// scenes without fills, 16x16 pixels; see FwdCfg and AdjCfg), and each lane
-// owns a BLK x BLK block of its quadrant.  A wavefront walks the
+// Work decomposition: one wavefront per (tile, quadrant) item.  A quadrant is
+// 8x8 pixels, one per lane, whatever the tile side: 8x8 tiles are one, 16x16
+// tiles have four and 32x32 tiles sixteen.  (Four quadrants of 16x16 with 2x2
+// pixels per lane at 32x32 tiles kept four times the entries and put four times
+// the work of each on one wavefront: forward and adjoint of 16 mixed scenes at
+// 768^2 0.695 and 1.246 -> 0.565 and 1.185 ms, of 8 at 768^2 0.463 and 0.907 ->
+// 0.267 and 0.636, of 4 at 512^2 0.498 and 0.324 -> 0.203 and 0.312, of 100 fill
+// paths at 512^2 0.235 and 0.105 -> 0.070 and 0.082.)  A wavefront walks the
 // tile's list in steps of up to 64 entries (64 E in the adjoint): every lane
 // loads one (E; the next step's loads are issued before the current step is
 // processed), entries whose support disc misses the quadrant are dropped, the rest are
@@ -30,10 +33,8 @@ namespace {
 // one after another.  Wavefronts never wait for each other.
 template <int TILE>
 struct TileCfg {
-  static constexpr int QUADS = TILE == 8 ? 1 : 4;
-  static constexpr int SUB = TILE == 8 ? 8 : TILE / 2;
-  static constexpr int BLK = SUB / 8;
-  static constexpr int PPT = BLK * BLK;
+  static constexpr int SUB = 8, COLS = TILE / 8, QUADS = COLS * COLS;
+  static_assert(QUADS == adj_blocks(TILE), "the binning's items");
 };
 constexpr int WPB = 4;                  // wavefronts per block
 // Kernel forms (template KIND): with the tangent-aligned kind, with the
@@ -41,50 +42,10 @@ constexpr int WPB = 4;                  // wavefronts per block
 constexpr int KIND_ANI = 1, KIND_FILL = 2;
 constexpr int BLOCK = 64 * WPB;
 
-// The forward's pixel blocks (its quadrants): 8 x 8 pixels at every tile side,
-// one per lane.  At 32 x 32 tiles the sixteen of them drop four times the
-// entries that blocks of 16 x 16 with 2 x 2 pixels per lane did, and are four
-// times the wavefronts with a quarter of the work per entry: 16 mixed scenes at
-// 768^2 0.695 -> 0.571 ms, 4 at 512^2 0.498 -> 0.204, 100 fill paths at 512^2
-// 0.235 -> 0.069.
-template <int TILE>
-struct FwdCfg {
-  static constexpr int SUB = 8, COLS = TILE / 8, QUADS = COLS * COLS;
-};
-
 template <int TILE>
 __device__ inline void pixel_of(int blk, int lane, int* lx, int* ly) {
-  *lx = (blk % FwdCfg<TILE>::COLS) * 8 + (lane & 7);
-  *ly = (blk / FwdCfg<TILE>::COLS) * 8 + (lane >> 3);
-}
-
-// The adjoint's pixel blocks (adj_blocks): the quadrants, or, for
-// the tiles of scenes with fills at 32 x 32 tiles, sixteen 8 x 8 blocks with
-// one pixel per lane.  Block b sits at column b % COLS, row b / COLS of the
-// tile; lane l owns the BLK x BLK pixels at column l & 7, row l >> 3 of it.
-template <int TILE, bool SPLIT_>
-struct AdjCfg {
-  static constexpr bool SPLIT = SPLIT_;
-  static constexpr int QUADS = SPLIT ? 16 : TileCfg<TILE>::QUADS;
-  static constexpr int SUB = SPLIT ? 8 : TileCfg<TILE>::SUB;
-  static constexpr int BLK = SUB / 8;
-  static constexpr int PPT = BLK * BLK;
-  static constexpr int COLS = TILE / SUB;
-  static_assert(!SPLIT || TILE == 32, "8 x 8 blocks split 32 x 32 tiles only");
-  static_assert(QUADS == adj_blocks(TILE, SPLIT), "adjoint blocks follow the binning's items");
-};
-
-template <class A>
-__device__ inline void adj_pixel(int blk, int lane, int q, int* lx, int* ly) {
-  *lx = (blk % A::COLS) * A::SUB + (lane & 7) * A::BLK + q % A::BLK;
-  *ly = (blk / A::COLS) * A::SUB + (lane >> 3) * A::BLK + q / A::BLK;
-}
-
-// Slot of tile pixel (lx, ly) in a stored forward state: the forward's block
-// x 64 + lane, as pixel_of lays it out.
-template <int TILE>
-__device__ inline int fwd_slot(int lx, int ly) {
-  return (lx / 8 + FwdCfg<TILE>::COLS * (ly / 8)) * 64 + lx % 8 + 8 * (ly % 8);
+  *lx = (blk % TileCfg<TILE>::COLS) * 8 + (lane & 7);
+  *ly = (blk / TileCfg<TILE>::COLS) * 8 + (lane >> 3);
 }
 
 // Next work item of this wavefront: the static assignment, or the next entry
@@ -135,7 +96,6 @@ struct Box {
 // the BLK x BLK block at column l & 7, row l >> 3 of the quadrant): rows from
 // the lowest and highest set bits, columns from the eight row bytes folded
 // together.  Scalar work on a wavefront-uniform mask; `live` != 0.
-template <class Cfg>
 __device__ inline Box live_box_of(int qx, int qy, uint64_t live) {
   const int r0 = __builtin_ctzll(live) >> 3, r1 = (63 - __builtin_clzll(live)) >> 3;
   uint64_t f = live | (live >> 32);
@@ -144,17 +104,17 @@ __device__ inline Box live_box_of(int qx, int qy, uint64_t live) {
   const uint32_t cols = (uint32_t)f & 0xffu;
   const int c0 = __builtin_ctz(cols), c1 = 31 - __builtin_clz(cols);
   Box b;
-  b.x0 = (float)(qx + c0 * Cfg::BLK);
-  b.x1 = (float)(qx + c1 * Cfg::BLK + Cfg::BLK - 1);
-  b.y0 = (float)(qy + r0 * Cfg::BLK);
-  b.y1 = (float)(qy + r1 * Cfg::BLK + Cfg::BLK - 1);
+  b.x0 = (float)(qx + c0);
+  b.x1 = (float)(qx + c1);
+  b.y0 = (float)(qy + r0);
+  b.y1 = (float)(qy + r1);
   return b;
 }
 
 // All pixel centres of the quadrant.
 template <int TILE>
 __device__ inline Box quad_box(int quad) {
-  using Cfg = FwdCfg<TILE>;
+  using Cfg = TileCfg<TILE>;
   Box b;
   b.x0 = (float)((quad % Cfg::COLS) * Cfg::SUB);
   b.y0 = (float)((quad / Cfg::COLS) * Cfg::SUB);
@@ -346,18 +306,17 @@ constexpr int FWD_ENTRY_BYTES = sizeof(FwdRec) + 16;
 constexpr int BWD_ENTRY_BYTES = 48;
 // The adjoint parks the per-lane gradient values it still has to sum over
 // the wavefront in LDS rows of 64 floats and sums 16 rows at a time
-// (flush_moments, flush_triples, flush_rows): one row for a stroke or fill entry at
-// one pixel per lane, three at 2 x 2 or of a very long curve (LONG_TAUS), five
+// (flush_moments, flush_rows): one row for a stroke or fill entry, three for one
+// of a very long curve (LONG_TAUS), five
 // for a tangent-aligned one.  Rows are padded
 // to 68 floats so that the 16-byte reads of 8 rows fall into different banks.
 constexpr int RB = 16;      // parked rows
 constexpr int RB_ROW = 68;  // floats per parked row
 // wavefronts per SIMD the adjoint is built for: five without the fill-run
-// walk at one pixel per lane and one entry per lane (their LDS slices, 7.6 KB
-// each, fill the CU), four with it (or at several pixels per lane), one at
-// several entries per lane
-__host__ __device__ constexpr int bwd_waves(int tile, int E, int kind) {
-  return tile <= 16 && E == 1 && !(kind & KIND_FILL) ? 5 : (E == 1 ? 4 : 1);
+// walk at one entry per lane (their LDS slices, 7.6 KB each, fill the CU), four
+// with it, one at several entries per lane
+__host__ __device__ constexpr int bwd_waves(int E, int kind) {
+  return E == 1 ? (kind & KIND_FILL ? 4 : 5) : 1;
 }
 __host__ __device__ constexpr size_t bwd_wave_bytes(int E) {
   return (size_t)64 * E * BWD_ENTRY_BYTES + (size_t)RB * (RB_ROW * 4 + 8);
@@ -414,7 +373,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
                                            float* __restrict__ Tfin, int32_t* __restrict__ nlast,
                                            const int32_t* __restrict__ plan, int64_t gcap, int ck_lg,
                                            bool fill_lattice, char* mine_lds) {
-  using Cfg = FwdCfg<TILE>;
+  using Cfg = TileCfg<TILE>;
   constexpr bool ANI = (KIND & KIND_ANI) != 0;
   const float amax = pr.alpha_max, eps = pr.eps_T, ks = pr.k_sigma;
   const float inv_tile = 1.0f / (float)TILE;
@@ -1246,7 +1205,7 @@ __global__ __launch_bounds__(FWD_BLOCK, KIND & KIND_FILL ? 4 : 6) void k_blend_f
     const int32_t* __restrict__ ranges, const int32_t* __restrict__ idx, const float* __restrict__ bg,
     float* __restrict__ image, float* __restrict__ Tfin, int32_t* __restrict__ nlast, const int32_t* __restrict__ plan,
     int64_t gcap, int persistent, int ck_arg) {
-  using Cfg = FwdCfg<TILE>;
+  using Cfg = TileCfg<TILE>;
   __shared__ __align__(16) FwdLds L;
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
   // the chunk length: the caller's, or the one the binning chose
@@ -1308,25 +1267,19 @@ __device__ inline int wave_min(int v) {
 
 // Folds one wavefront's running FP32 per-curve sums into `tot`, whose lane 0
 // keeps the FP64 opacity gradient of a stroke curve and lane 1 + ch the colour
-// gradient of channel ch, sum_q dL/dI_c(q) sum(alpha T) (aT: each pixel's sum
+// gradient of channel ch, dL/dI_c sum(alpha T) (aT: the pixel's sum
 // of alpha T over the run, reset here).  `tot` goes to the curve's
 // accumulators once, where the wavefront's run of the curve ends
 // (flush_curve): with an atomic every FLUSH stroke entries a launch of few
 // curves queued up on their few addresses (one curve of 10,240 key points at
 // 1024^2, 2.0M pairs: adjoint 1.30 ms, now 0.39 ms).
-template <int C, int PPT>
-__device__ inline void fold_curve(bool fill, const float (&gI)[PPT][3], float (&aT)[PPT], float& accO, double& tot) {
+template <int C>
+__device__ inline void fold_curve(bool fill, const float (&gI)[3], float& aT, float& accO, double& tot) {
   float v[C + 1];
   v[0] = fill ? 0.0f : accO;
 #pragma unroll
-  for (int ch = 0; ch < C; ++ch) {
-    float a = 0.0f;
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) a = __builtin_fmaf(gI[q][ch], aT[q], a);
-    v[1 + ch] = a;
-  }
-#pragma unroll
-  for (int q = 0; q < PPT; ++q) aT[q] = 0.0f;
+  for (int ch = 0; ch < C; ++ch) v[1 + ch] = gI[ch] * aT;
+  aT = 0.0f;
   accO = 0.0f;
   tot += (double)wave_totals_to_lanes<C + 1>(v);
 }
@@ -1442,40 +1395,6 @@ __device__ inline void flush_moments(const float* park, const float* basis, cons
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The same for up to RB / 3 entries of a block with 2 x 2 pixels per lane,
-// whose lanes park three rows per entry: sum v dx, sum v dy and sum v |d|^2
-// over their pixels (a fill entry: sum v first), formed from the in-lane sums
-// of v, which is cheaper there than four rows of v (batches of 16 scenes:
-// adjoint 1.746 ms with four rows, 1.381 ms with three).  Summed as in
-// flush_rows.  Every lane of the wavefront must call it.
-__device__ inline void flush_triples(const float* park, const float4* geo, const int4* meta, int e0, int n,
-                                     float* __restrict__ ggrad) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int lane = __lane_id(), r = lane >> 2, part = lane & 3;
-  const float* row = park + r * RB_ROW + part;
-  float t = 0.0f;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) t += row[4 * j];
-  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x111, 0xf, 0xf, true));  // row_shr:1
-  t += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x112, 0xf, 0xf, true));  // row_shr:2
-  if (part == 3 && r < 3 * n) {
-    const int e = (r * 11) >> 5, val = r - 3 * e;  // r / 3, r % 3 below 16
-    const int4 mt = meta[e0 + e];
-    if (mt.x < 0) {
-      if (val == 0 && t != 0.0f) unsafeAtomicAdd(ggrad + (int64_t)~mt.x * GG + 3, t);
-    } else {
-      const float op = __int_as_float(mt.z);
-      const float v = t * (val == 2 ? op * __int_as_float(mt.w) : -2.0f * (float)LN2 * geo[e0 + e].w * op);
-      if (v != 0.0f) unsafeAtomicAdd(ggrad + (int64_t)mt.x * GG + val, v);
-    }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Adjoint of the forward blend, one work item per (tile, quadrant, chunk).
 // Inside its chunk an item walks back to front, starting from the state the
 // forward stored at the chunk's back end (T there, and the colour of
@@ -1497,19 +1416,13 @@ __device__ inline void flush_triples(const float* park, const float4* geo, const
 // flushed when the curve changes along the list (and for strokes folded into
 // FP64 every FLUSH entries).  The entries of a step are cut into runs of one curve with one
 // ballot, and each run is composited by a loop for its kind, with no
-// per-entry curve test.  Occupancy: six wavefronts per SIMD for one pixel per
-// lane at depth 64, four for 32 x 32 tiles at depth 64 (128 VGPRs, unspilled);
-// elsewhere the registers decide.
+// per-entry curve test.  Occupancy: bwd_waves.
 template <int C, int TILE, int E, int KIND>
-__global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
+__global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
     nsplat_curves cv, nsplat_params pr, Work w, int n_scenes, int n_tiles, const Gauss* __restrict__ gs,
     const int32_t* __restrict__ ranges, const int32_t* __restrict__ idx, const float* __restrict__ bg,
     const float* __restrict__ dL, const float* __restrict__ Tfin, const int32_t* __restrict__ nlast,
     const int32_t* __restrict__ plan, int64_t gcap, int persistent, int ck_arg) {
-  // both block forms in one kernel where a launch can hold both (32 x 32
-  // tiles with fills): scenes with fills in 8 x 8 blocks, the others in
-  // quadrants
-  constexpr bool DUAL = TILE == 32 && (KIND & KIND_FILL) != 0;
   constexpr int FLUSH = 32;
   extern __shared__ __align__(16) char smem[];
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
@@ -1518,8 +1431,8 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
   const float amax = pr.alpha_max, ks = pr.k_sigma;
   const float ln2 = (float)LN2;
   constexpr bool ANI = (KIND & KIND_ANI) != 0;
-  // fill runs pixel by pixel (see FillRun), in blocks of one pixel per lane
-  const bool fill_h1 = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
+  // fill runs pixel by pixel (see FillRun)
+  const bool fill_lattice = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
   const float inv_tile = 1.0f / (float)TILE;
   const int lane = __lane_id(), wv = threadIdx.x >> 6;
   float* basis = (float*)smem;  // (shared by the block's wavefronts)
@@ -1555,10 +1468,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
     const int tile = w.order[tq];
     const int s = scene_of_tile(w.scenes, n_scenes, tile);
     const SceneTab st = w.scenes[s];
-    auto item_body = [&](auto cfg) {
-    using Cfg = decltype(cfg);
-    constexpr int PPT = Cfg::PPT;
-    const bool fill_lattice = fill_h1 && PPT == 1;
+    using Cfg = TileCfg<TILE>;
     const int quad = r_it % Cfg::QUADS, kc = r_it / Cfg::QUADS;
     const int qx = (quad % Cfg::COLS) * Cfg::SUB, qy = (quad / Cfg::COLS) * Cfg::SUB;  // the block's first pixel
     const int lt = tile - st.tile_off;
@@ -1569,74 +1479,55 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
     // the forward's state at the chunk's back end (the front of chunk kc + 1),
     // stored when a chunk follows
     const float* ckn = c_lo > start ? w.ckbuf + (int64_t)(w.ck_off[tile] + kc) * (4 * TILE * TILE) : nullptr;
-    float px[PPT], py[PPT], T[PPT], Wc[PPT], gI[PPT][3];
-    int stop[PPT];
-    int my_lo = end;
+    int lx, ly;
+    pixel_of<TILE>(quad, lane, &lx, &ly);
+    const float px = (float)lx, py = (float)ly;
+    float T = 1.0f, Wc = 0.0f, gI[3] = {0.0f, 0.0f, 0.0f};
+    int stop = end;  // invalid pixels never take part
+    if (x0 + lx < st.W && y0 + ly < st.H) {
+      const int64_t pix = (int64_t)st.pix_off + (int64_t)(y0 + ly) * st.W + (x0 + lx);
+      const float tf = Tfin[pix];
+      stop = nlast[pix];
+      // a pixel still live behind this chunk starts from the stored state,
+      // one that stopped inside it from T_final with only the background
+      // behind it (no chunk is stored after a pixel's stop is passed)
+      const int slot = quad * 64 + lane;
+      float behind[3] = {0.0f, 0.0f, 0.0f};
+      T = tf;
+      if (stop < c_lo) {  // then c_lo > start, so a chunk follows and ckn is set
+        T = ckn[slot];
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      int lx, ly;
-      adj_pixel<Cfg>(quad, lane, q, &lx, &ly);
-      px[q] = (float)lx;
-      py[q] = (float)ly;
-      T[q] = 1.0f;
-      Wc[q] = 0.0f;
-      stop[q] = end;  // invalid pixels never take part
-#pragma unroll
-      for (int c = 0; c < 3; ++c) gI[q][c] = 0.0f;
-      if (x0 + lx < st.W && y0 + ly < st.H) {
-        const int64_t pix = (int64_t)st.pix_off + (int64_t)(y0 + ly) * st.W + (x0 + lx);
-        const float tf = Tfin[pix];
-        stop[q] = nlast[pix];
-        // a pixel still live behind this chunk starts from the stored state,
-        // one that stopped inside it from T_final with only the background
-        // behind it (no chunk is stored after a pixel's stop is passed)
-        const int slot = TILE == 32 ? fwd_slot<TILE>(lx, ly) : quad * 64 + lane;
-        float behind[3] = {0.0f, 0.0f, 0.0f};
-        T[q] = tf;
-        if (stop[q] < c_lo) {  // then c_lo > start, so a chunk follows and ckn is set
-          T[q] = ckn[slot];
-#pragma unroll
-          for (int c = 0; c < C; ++c) behind[c] = ckn[(1 + c) * TILE * TILE + slot];
-        }
-        float B = 0.0f;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)(y0 + ly) * st.W + (x0 + lx);
-          gI[q][c] = dL[o];
-          B = __builtin_fmaf(gI[q][c], __builtin_fmaf(tf, bg[s * C + c], behind[c]), B);
-        }
-        Wc[q] = B;  // W = B - K T' with no curve yet (K = 0)
-        my_lo = min(my_lo, stop[q]);
+        for (int c = 0; c < C; ++c) behind[c] = ckn[(1 + c) * TILE * TILE + slot];
       }
+      float B = 0.0f;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int64_t o = (int64_t)st.pix_off * C + c * plane + (int64_t)(y0 + ly) * st.W + (x0 + lx);
+        gI[c] = dL[o];
+        B = __builtin_fmaf(gI[c], __builtin_fmaf(tf, bg[s * C + c], behind[c]), B);
+      }
+      Wc = B;  // W = B - K T' with no curve yet (K = 0)
     }
     // positions below every pixel's stopping position take no part
-    const int lo = max(wave_min(my_lo), c_lo);
-    if (c_hi <= lo) return;
+    const int lo = max(wave_min(stop), c_lo);
+    if (c_hi <= lo) continue;
     int cur = -1, since = 0;
     bool cur_fill = false, cur_aniso = false, cur_long = false;
     // per pixel: K of the current curve, W (fixed over a run of one curve),
     // and the run's sum of alpha T (the curve's colour gradient is dL/dI_c
     // times it)
-    float Kc[PPT], aT[PPT], accO = 0.0f;
+    float Kc = 0.0f, aT = 0.0f, accO = 0.0f;
     double ctot = 0.0;  // the open run's curve sums (fold_curve)
     // the end of the run of curve `cur`
     auto close_curve = [&]() {
       if (cur < 0) return;
-      fold_curve<C, PPT>(cur_fill, gI, aT, accO, ctot);
+      fold_curve<C>(cur_fill, gI, aT, accO, ctot);
       flush_curve<C>(w.gcurve, cur, ctot);
     };
     // the parked rows of the n entries before entry j
     auto flush_pending = [&](int j, int n) {
-      if constexpr (PPT == 1)
-        flush_moments(park, basis, wgeo, wmeta, j - n, n, (float)qx + 3.5f, (float)qy + 3.5f, ggrad);
-      else
-        flush_triples(park, wgeo, wmeta, j - n, n, ggrad);
+      flush_moments(park, basis, wgeo, wmeta, j - n, n, (float)qx + 3.5f, (float)qy + 3.5f, ggrad);
     };
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      Kc[q] = 0.0f;
-      aT[q] = 0.0f;
-    }
     const double ox = (double)x0 + 0.5, oy = (double)y0 + 0.5;
     // back to front over the chunk's positions lo up to c_hi - 1, in steps
     // of `depth` (each lane loads one entry per 64 of a step)
@@ -1656,8 +1547,6 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
     constexpr int BNIT = (BNB * BNB + 63) / 64;
     PlanRow prow;
     auto fill_run_bwd = [&](const FillRun& fr, const float (&col)[3], int p0, int p1, const float (&og)[BNIT]) {
-      // (one pixel per lane: lane (l & 7, l >> 3) of the 8 x 8 pixel
-      // block; fill_lattice is false otherwise)
       constexpr int NB = BNB;                  // 16 cells per axis
       constexpr int NS = FR_NS;                // LDS row stride (conflict-free rows)
       float* ol = (float*)mine_lds;  // [NB][NS] opacities (0: no Gaussian at p0 .. p1 there)
@@ -1666,9 +1555,9 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
         close_curve();
         float K = 0.0f;
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch) K = __builtin_fmaf(gI[0][ch], col[ch], K);
-        Wc[0] = __builtin_fmaf(-K, T[0], __builtin_fmaf(Kc[0], T[0], Wc[0]));
-        Kc[0] = K;
+        for (int ch = 0; ch < C; ++ch) K = __builtin_fmaf(gI[ch], col[ch], K);
+        Wc = __builtin_fmaf(-K, T, __builtin_fmaf(Kc, T, Wc));
+        Kc = K;
         cur = fr.c;
         cur_fill = true;
         cur_aniso = false;
@@ -1698,7 +1587,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
       const float coef = (float)(-0.5 * LOG2E / (sgd * sgd));  // as entry_geometry
       // lane k holds G at squared lattice distance k, as the entry path forms it
       const int gtab = __float_as_int(__builtin_amdgcn_exp2f(coef * (float)lane));
-      const float nW = -Wc[0];  // dL/dalpha (1 - alpha) over the run
+      const float nW = -Wc;  // dL/dalpha (1 - alpha) over the run
       const int lx = lane & 7, ly = lane >> 3;
       const bool col0 = lx == 0, col7 = lx == 7;
       const int pb0 = fr.p_lo + (y0 + qy + ly - fr.iy0 - fr.j0) * fr.w + (x0 + qx + lx - fr.ix0 - fr.i0);
@@ -1715,7 +1604,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           // stop adds nothing
           const int jr = y0 + qy + ly + dy - fr.iy0, ir = x0 + qx + lx - fr.ix0;
           const bool any = jr >= fr.j0 && jr <= fr.j1 && ir + dxm >= fr.i0 && ir - dxm <= fr.i1 &&
-                           rpos + dxm >= max(p0, stop[0]) && rpos - dxm <= p1;
+                           rpos + dxm >= max(p0, stop) && rpos - dxm <= p1;
           if (__ballot(any) == 0ull) continue;
         }
         // the row's opacities first, one LDS wait per row (each becomes the
@@ -1725,7 +1614,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
         for (int dx = -FR_R; dx <= FR_R; ++dx) v[dx + FR_R] = ol[roff + dx];
 #pragma unroll
         for (int a = 0; a <= FR_R; ++a) Gr[a] = __int_as_float(__builtin_amdgcn_readlane(gtab, a * a + dy * dy));
-        const int sd = stop[0] - rpos;  // cells at dx >= sd lie at or behind the pixel's stop
+        const int sd = stop - rpos;  // cells at dx >= sd lie at or behind the pixel's stop
 #pragma unroll
         for (int dx = -FR_R; dx <= FR_R; ++dx) {
           const float o = v[dx + FR_R];
@@ -1738,8 +1627,8 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           const bool lt = oG < amax;
           const float alpha = fminf(oG, amax);  // lt ? oG : amax, also for a NaN oG
           const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
-          T[0] *= r;
-          aT[0] = __builtin_fmaf(alpha, T[0], aT[0]);
+          T *= r;
+          aT = __builtin_fmaf(alpha, T, aT);
           v[dx + FR_R] = lt ? nW * r * G : 0.0f;  // dL/do_j of the cell at dx
         }
         // the row's cells get their sums over the pixels of each lane row
@@ -1816,9 +1705,8 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
       // its top); walking back to front the set only grows.  Entries that
       // reach none of them are dropped.
       bool lv = false, step_aniso = false;
-#pragma unroll
-      for (int q = 0; q < PPT; ++q) lv = lv || (stop[q] < s_hi);
-      const Box box = live_box_of<Cfg>(qx, qy, __ballot(lv));
+      lv = lv || (stop < s_hi);
+      const Box box = live_box_of(qx, qy, __ballot(lv));
 #pragma unroll
       for (int u = 0; u < E; ++u) {
         const int k = u * 64 + lane;
@@ -1890,15 +1778,12 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           const int4 mt = wmeta[j];
           const float4 pc = wpc[j];
           const float col[3] = {pc.x, pc.y, pc.z};
+          float K = 0.0f;
 #pragma unroll
-          for (int q = 0; q < PPT; ++q) {
-            float K = 0.0f;
-#pragma unroll
-            for (int c = 0; c < C; ++c) K = __builtin_fmaf(gI[q][c], col[c], K);
-            // B = W + K_old T' is unchanged; W re-expressed with the new K
-            Wc[q] = __builtin_fmaf(-K, T[q], __builtin_fmaf(Kc[q], T[q], Wc[q]));
-            Kc[q] = K;
-          }
+          for (int c = 0; c < C; ++c) K = __builtin_fmaf(gI[c], col[c], K);
+          // B = W + K_old T' is unchanged; W re-expressed with the new K
+          Wc = __builtin_fmaf(-K, T, __builtin_fmaf(Kc, T, Wc));
+          Kc = K;
           cur = __builtin_amdgcn_readfirstlane(__float_as_int(pc.w));
           cur_fill = __builtin_amdgcn_readfirstlane(mt.x) < 0;
           cur_aniso = ANI && !cur_fill && __builtin_amdgcn_readfirstlane(mt.w) < 0;
@@ -1918,7 +1803,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           int n_rows = 0;
           for (; j < jend; ++j) {
             if (since >= FLUSH) {
-              fold_curve<C, PPT>(false, gI, aT, accO, ctot);
+              fold_curve<C>(false, gI, aT, accO, ctot);
               since = 0;
             }
             ++since;
@@ -1932,30 +1817,27 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             const float rux = rq * gm.z, ruy = rq * gm.w;
             float v[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
             bool act = false;
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-              const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-              const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
-              const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
-              const float m = __builtin_fmaf(a, a, b * b);
-              const bool in = (mt.y >= stop[q]) && (m <= lim);
-              act = act || in;
-              const float G = __builtin_amdgcn_exp2f(-m);
-              const float oG = op * G;
-              const bool lt = oG < amax;
-              const float alpha = in ? fminf(oG, amax) : 0.0f;  // = lt ? oG : amax
-              const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
-              const float dLda = (in && lt) ? -Wc[q] * r : 0.0f;
-              T[q] = in ? T[q] * r : T[q];
-              aT[q] = __builtin_fmaf(alpha, T[q], aT[q]);
-              v[5] = __builtin_fmaf(dLda, G, v[5]);  // dL/do_j
-              const float h = dLda * op * G * two_ln2;
-              v[0] = __builtin_fmaf(h, __builtin_fmaf(a, gm.z, -(b * ruy)), v[0]);
-              v[1] = __builtin_fmaf(h, __builtin_fmaf(a, gm.w, b * rux), v[1]);
-              v[2] = __builtin_fmaf(h * a, a * isg, v[2]);
-              v[3] = __builtin_fmaf(h * b, b * isp, v[3]);
-              v[4] = __builtin_fmaf(h * a, b * rr, v[4]);
-            }
+            const float dx = px - gm.x, dy = py - gm.y;
+            const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
+            const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
+            const float m = __builtin_fmaf(a, a, b * b);
+            const bool in = (mt.y >= stop) && (m <= lim);
+            act = act || in;
+            const float G = __builtin_amdgcn_exp2f(-m);
+            const float oG = op * G;
+            const bool lt = oG < amax;
+            const float alpha = in ? fminf(oG, amax) : 0.0f;  // = lt ? oG : amax
+            const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
+            const float dLda = (in && lt) ? -Wc * r : 0.0f;
+            T = in ? T * r : T;
+            aT = __builtin_fmaf(alpha, T, aT);
+            v[5] = __builtin_fmaf(dLda, G, v[5]);  // dL/do_j
+            const float h = dLda * op * G * two_ln2;
+            v[0] = __builtin_fmaf(h, __builtin_fmaf(a, gm.z, -(b * ruy)), v[0]);
+            v[1] = __builtin_fmaf(h, __builtin_fmaf(a, gm.w, b * rux), v[1]);
+            v[2] = __builtin_fmaf(h * a, a * isg, v[2]);
+            v[3] = __builtin_fmaf(h * b, b * isp, v[3]);
+            v[4] = __builtin_fmaf(h * a, b * rr, v[4]);
             if (__ballot(act) == 0ull) continue;
             if (n_rows + 5 > RB) {
               flush_rows(park, ptgt, n_rows, ggrad);
@@ -1976,7 +1858,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
           int n_rows = 0;
           for (; j < jend; ++j) {
             if (since >= FLUSH) {
-              fold_curve<C, PPT>(false, gI, aT, accO, ctot);
+              fold_curve<C>(false, gI, aT, accO, ctot);
               since = 0;
             }
             ++since;
@@ -1986,27 +1868,24 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             const float is3 = __int_as_float(mt.w);
             float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             bool act = false;
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-              const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-              const float d2 = __builtin_fmaf(dx, dx, dy * dy);
-              const bool in = (mt.y >= stop[q]) && (d2 <= gm.z);
-              act = act || in;
-              const float G = __builtin_amdgcn_exp2f(gm.w * d2);
-              const float oG = op * G;
-              const bool lt = oG < amax;
-              const float alpha = in ? fminf(oG, amax) : 0.0f;  // = lt ? oG : amax
-              const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
-              const float dLda = (in && lt) ? -Wc[q] * r : 0.0f;
-              T[q] *= r;
-              aT[q] = __builtin_fmaf(alpha, T[q], aT[q]);
-              v[3] = __builtin_fmaf(dLda, G, v[3]);  // dL/do_j
-              const float dG = dLda * op;
-              const float dd2 = dG * G * gm.w * ln2;  // d exp2(a d2) / d d2 = G a ln 2
-              v[0] = __builtin_fmaf(-2.0f * dx, dd2, v[0]);
-              v[1] = __builtin_fmaf(-2.0f * dy, dd2, v[1]);
-              v[2] = __builtin_fmaf(dG * G, d2 * is3, v[2]);
-            }
+            const float dx = px - gm.x, dy = py - gm.y;
+            const float d2 = __builtin_fmaf(dx, dx, dy * dy);
+            const bool in = (mt.y >= stop) && (d2 <= gm.z);
+            act = act || in;
+            const float G = __builtin_amdgcn_exp2f(gm.w * d2);
+            const float oG = op * G;
+            const bool lt = oG < amax;
+            const float alpha = in ? fminf(oG, amax) : 0.0f;  // = lt ? oG : amax
+            const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
+            const float dLda = (in && lt) ? -Wc * r : 0.0f;
+            T *= r;
+            aT = __builtin_fmaf(alpha, T, aT);
+            v[3] = __builtin_fmaf(dLda, G, v[3]);  // dL/do_j
+            const float dG = dLda * op;
+            const float dd2 = dG * G * gm.w * ln2;  // d exp2(a d2) / d d2 = G a ln 2
+            v[0] = __builtin_fmaf(-2.0f * dx, dd2, v[0]);
+            v[1] = __builtin_fmaf(-2.0f * dy, dd2, v[1]);
+            v[2] = __builtin_fmaf(dG * G, d2 * is3, v[2]);
             if (__ballot(act) == 0ull) continue;
             if (n_rows + 3 > RB) {
               flush_rows(park, ptgt, n_rows, ggrad);
@@ -2030,45 +1909,25 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             const float4 gm = wgeo[jj];
             const int4 mt = wmeta[jj];
             const float op = __int_as_float(mt.z);
-            float v[PPT];
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-              const float dx = px[q] - gm.x, dy = py[q] - gm.y;
-              const float d2 = __builtin_fmaf(dx, dx, dy * dy);
-              const bool in = (mt.y >= stop[q]) && (d2 <= gm.z);
-              const float G = in ? __builtin_amdgcn_exp2f(gm.w * d2) : 0.0f;
-              const float oG = op * G;
-              const bool lt = oG < amax;
-              const float alpha = fminf(oG, amax);  // lt ? oG : amax, also for a NaN oG
-              const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
-              T[q] *= r;  // the transmittance in front of the entry
-              aT[q] = __builtin_fmaf(alpha, T[q], aT[q]);
-              // dL/dalpha = (T' K - B) / (1 - alpha) = -W / (1 - alpha)
-              v[q] = (in && lt) ? -Wc[q] * r * G : 0.0f;
-            }
-            if constexpr (PPT == 1) {
-              accO += v[0];
-              park[ent * RB_ROW + lane] = v[0];
-            } else {
-              // sums over the lane's 2 x 2 pixels of v {1, ox, oy}, ox and oy
-              // the pixel's offset (0 or 1) from the first
-              const float m1 = v[1] + v[3], m2 = v[2] + v[3], m0 = (v[0] + v[1]) + (v[2] + v[3]);
-              const float dx = px[0] - gm.x, dy = py[0] - gm.y;
-              const float sx = __builtin_fmaf(dx, m0, m1), sy = __builtin_fmaf(dy, m0, m2);
-              // sum v |d + offset|^2 (ox^2 = ox, oy^2 = oy)
-              const float sr = __builtin_fmaf(dx, sx + m1, __builtin_fmaf(dy, sy + m2, m1 + m2));
-              accO += m0;
-              float* row = park + 3 * ent * RB_ROW + lane;
-              row[0] = cur_fill ? m0 : sx;
-              row[RB_ROW] = sy;
-              row[2 * RB_ROW] = sr;
-            }
+            const float dx = px - gm.x, dy = py - gm.y;
+            const float d2 = __builtin_fmaf(dx, dx, dy * dy);
+            const bool in = (mt.y >= stop) && (d2 <= gm.z);
+            const float G = in ? __builtin_amdgcn_exp2f(gm.w * d2) : 0.0f;
+            const float oG = op * G;
+            const bool lt = oG < amax;
+            const float alpha = fminf(oG, amax);  // lt ? oG : amax, also for a NaN oG
+            const float r = __builtin_amdgcn_rcpf(1.0f - alpha);
+            T *= r;  // the transmittance in front of the entry
+            aT = __builtin_fmaf(alpha, T, aT);
+            // dL/dalpha = (T' K - B) / (1 - alpha) = -W / (1 - alpha)
+            const float v = (in && lt) ? -Wc * r * G : 0.0f;
+            accO += v;
+            park[ent * RB_ROW + lane] = v;
           };
-          constexpr int EPF = PPT == 1 ? RB : RB / 3;  // entries per flush
           while (j < jend) {
-            const int m = min(jend - j, EPF - n_ent);
+            const int m = min(jend - j, RB - n_ent);
             if (!cur_fill && since + m > FLUSH) {
-              fold_curve<C, PPT>(false, gI, aT, accO, ctot);
+              fold_curve<C>(false, gI, aT, accO, ctot);
               since = 0;
             }
             since += m;
@@ -2076,7 +1935,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
             for (int i = 0; i < m; ++i) eval(j + i, n_ent + i);
             j += m;
             n_ent += m;
-            if (n_ent == EPF) {
+            if (n_ent == RB) {
               flush_pending(j, n_ent);
               n_ent = 0;
             }
@@ -2089,13 +1948,6 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(TILE, E, KIND)) void k_blend_bwd(
       s_hi = n_hi;
     }
     close_curve();
-    };
-    if constexpr (DUAL) {
-      if (st.fills) item_body(AdjCfg<TILE, true>{});
-      else item_body(AdjCfg<TILE, false>{});
-    } else {
-      item_body(AdjCfg<TILE, false>{});
-    }
   }
 }
 
@@ -2116,7 +1968,7 @@ inline int depth_factor(int batch) { return batch <= 64 ? 1 : (batch <= 128 ? 2 
 
 template <int C, int TILE, int KIND>
 hipError_t fwd_t(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
-  constexpr int QUADS = FwdCfg<TILE>::QUADS;
+  constexpr int QUADS = TileCfg<TILE>::QUADS;
   const int64_t n_items = L.n_tiles * QUADS;
   if (n_items <= 0) return hipSuccess;
   // blocks: one per item of a long list (at least LONG_LEAST positions each;
@@ -2145,7 +1997,7 @@ hipError_t bwd_t(const Launch& L, const float* dL, const float* T_final, const i
   // sum over tiles of QUADS * ceil(len / CK) <= QUADS * (pairs / CK + tiles);
   // where the binning chose a chunk below CK_MIN, QUADS * pairs / CK is at
   // most twice its target (small_chunk_log2)
-  const int64_t blocks = adj_blocks(TILE, (KIND & KIND_FILL) != 0), pairs = L.bf->caps.pairs;
+  const int64_t blocks = adj_blocks(TILE), pairs = L.bf->caps.pairs;
   int64_t max_items = blocks * (pairs >> (L.ck_lg >= 0 ? L.ck_lg : 9));
   if (L.ck_lg < 0 && TILE <= 16)
     max_items = std::max(max_items, std::min(blocks * (pairs / CK_SMALL), (int64_t)2 * SMALL_ITEMS * L.n_cu));

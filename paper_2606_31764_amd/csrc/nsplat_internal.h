@@ -35,7 +35,7 @@ static_assert(sizeof(Gauss) == 32, "Gaussian record must be 32 bytes");
 
 struct SceneTab {
   int32_t H, W, tiles_x, tiles_y, tile_off, pix_off, n_L;
-  int32_t fills;  // 1: a curve of the scene is filled (set by nsplat_bin at 32 x 32 tiles, see adj_blocks)
+  int32_t pad;
 };
 
 enum { P_COUNT = 0, P_NSAMP, P_IX0, P_IY0, P_NX, P_NY, P_GOFF, P_BOFF, P_FLAGS, P_STRIDE };
@@ -121,13 +121,12 @@ __host__ __device__ inline int small_chunk_log2(int64_t pairs, int quads, int n_
   const int64_t v = pairs * quads / (SMALL_ITEMS * (int64_t)(n_cu > 0 ? n_cu : 1));
   return v >= 512 ? 9 : (v >= 256 ? 8 : 7);
 }
-// Adjoint work items per chunk of a tile list: the forward's quadrants (one
-// at 8 x 8 tiles, four above), except for the tiles of scenes with fills at
-// 32 x 32 tiles, which the adjoint takes as sixteen 8 x 8 pixel blocks with
-// one pixel per lane (its fill-run walk is written for one pixel per lane).
-__host__ __device__ constexpr int adj_blocks(int tile, bool fills) {
-  return tile == 8 ? 1 : (tile == 32 && fills ? 16 : 4);
-}
+// Forward work items per tile and adjoint work items per chunk of its list: its
+// 8 x 8 pixel blocks (the quadrants).
+__host__ __device__ constexpr int adj_blocks(int tile) { return (tile / 8) * (tile / 8); }
+// The chunk and long-list rules count a tile's positions once per 16 x 16
+// pixels at 32 x 32 tiles, whose 8 x 8 blocks drop most of them.
+__host__ __device__ constexpr int rule_quads(int tile) { return tile == 8 ? 1 : 4; }
 
 // Boundary segments per bounding box in the fill SDF.  Curve c (first
 // boundary point boff) has a header at cbox_base(boff, c) holding the box
@@ -473,7 +472,6 @@ struct Launch {
   int ck_lg;  // log2 of params.chunk, or CK_ARG_*: chosen by the binning (Q_CKLG)
 };
 // the adjoint's pixel blocks per chunk for this launch's tile side and curves
-inline int adj_blocks_of(const Launch& L) { return adj_blocks(L.pr->tile, (L.cv->any_flags & NSPLAT_FILLED) != 0); }
 
 // Scene table; also clears the NSPLAT_NUM_COUNTERS counters when given.
 hipError_t launch_scene_setup(const Launch& L, int32_t* clear_counters);

@@ -123,20 +123,27 @@ __device__ inline Box quad_box(int quad) {
   return b;
 }
 
-// Tile-local centre (relative to the tile's first pixel centre), squared
-// support radius, exp2 coefficient -log2(e) / (2 sigma^2), and whether the
-// support disc reaches the rectangle `bx` of pixel centres (the quadrant's
+// Tile-local centre (relative to the tile's first pixel centre), and whether
+// the support disc reaches the rectangle `bx` of pixel centres (the quadrant's
 // pixels that can still take part), with the radius enlarged by a relative
 // 1e-4 so that the test is conservative under FP32 rounding.
 __device__ inline bool entry_geometry(const Gauss& r, double ox, double oy, float ks, const Box& bx, float4* geo) {
+  geo->x = (float)(r.mx - ox);
+  geo->y = (float)(r.my - oy);
+  const float rc = ks * r.sigma * 1.0001f + 1e-4f;
+  const float dx = fmaxf(fmaxf(bx.x0 - geo->x, geo->x - bx.x1), 0.0f);
+  const float dy = fmaxf(fmaxf(bx.y0 - geo->y, geo->y - bx.y1), 0.0f);
+  return dx * dx + dy * dy <= rc * rc;
+}
+
+// The rest of a kept entry's geometry: squared support radius and exp2
+// coefficient -log2(e) / (2 sigma^2), whose division in FP64 is most of an
+// entry's staging and is left out in the steps that keep none.
+__device__ inline void entry_support(const Gauss& r, float ks, float4* geo) {
   const double sg = (double)r.sigma;
   const float rr = ks * r.sigma;
-  const float cx = (float)(r.mx - ox), cy = (float)(r.my - oy);
-  *geo = make_float4(cx, cy, rr * rr, (float)(-0.5 * LOG2E / (sg * sg)));
-  const float rc = rr * 1.0001f + 1e-4f;
-  const float dx = fmaxf(fmaxf(bx.x0 - cx, cx - bx.x1), 0.0f);
-  const float dy = fmaxf(fmaxf(bx.y0 - cy, cy - bx.y1), 0.0f);
-  return dx * dx + dy * dy <= rc * rc;
+  geo->z = rr * rr;
+  geo->w = (float)(-0.5 * LOG2E / (sg * sg));
 }
 
 // A tangent-aligned Gaussian (axis sigma along t, sp across it, sigma >= sp)
@@ -654,6 +661,7 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
     const int cnt = __popcll(m);
     const bool step_aniso = ANI && __ballot(keep && e.kind == 2) != 0ull;
     if (keep) {
+      entry_support(e.r, ks, &geo);
       const int dst = __popcll(m & below);
       FwdRec rec;
       rec.geo = geo;
@@ -946,6 +954,7 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
       any_neg = any_neg || L.neg[k] != 0;
     }
     if (keep) {
+      entry_support(e.r, ks, &geo);
       const int dst = base + __popcll(m & below);
       FwdRec rec;
       rec.geo = geo;
@@ -1717,6 +1726,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
         const uint64_t m = __ballot(keep);
         if (ANI) step_aniso = step_aniso || __ballot(keep && e[u].kind == 2) != 0ull;
         if (keep) {
+          entry_support(e[u].r, ks, &geo);
           const int dst = cnt + __popcll(m & below);
           const double sg = (double)e[u].r.sigma;
           // tangent-aligned entries: -1 (negative: the kind) in place of 1 / sigma^3

@@ -1365,8 +1365,13 @@ __device__ inline double quad_bcast(double v) {
 // 512^2 0.132 -> 0.076 ms, of 16 x 2000 key points at 1024^2 0.940 -> 0.705 ms).
 // In FP64, because moving the sums to the Gaussian's centre cancels: in FP32
 // (0.076, 0.726 ms, v_mfma_f32_16x16x4) the knot-interval gradients of long splines, themselves
-// sums that cancel, were ten times further from the exact ones.  Every lane of
-// the wavefront must call it.
+// sums that cancel, were ten times further from the exact ones.
+// A disc of a radius below a half (gm.z < 0.2, with a margin for the rounding of
+// the pixels' own tests) reaches one pixel at most: there sum v |x - mu|^2 is
+// |sum v (x - mu)|^2 / sum v, while the moved sum keeps 1e-15 px^2, which may be
+// more than sigma^2; and with no pixel nothing is added, also where the factors
+// (1 / sigma^3 from sigma = 1.4e-13 down) are infinite.  Every lane of the
+// wavefront must call it.
 __device__ inline void flush_moments(const float* park, const float* basis, const float4* geo, const int4* meta,
                                      int e0, int n, float mx, float my, float* __restrict__ ggrad) {
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -1391,13 +1396,15 @@ __device__ inline void flush_moments(const float* park, const float* basis, cons
   const double M0 = quad_bcast<0>(m), Mx = quad_bcast<1>(m), My = quad_bcast<2>(m), Mr = quad_bcast<3>(m);
   const double cx = (double)gm.x - (double)mx, cy = (double)gm.y - (double)my;
   const double Ax = __builtin_fma(-cx, M0, Mx), Ay = __builtin_fma(-cy, M0, My);
-  const double Ar = __builtin_fma(-cy, My + Ay, __builtin_fma(-cx, Mx + Ax, Mr));
+  const bool thin = gm.z < 0.2f;
+  const double Ar = thin ? __builtin_fma(Ax, Ax, Ay * Ay) * __builtin_amdgcn_rcp(M0)
+                         : __builtin_fma(-cy, My + Ay, __builtin_fma(-cx, Mx + Ax, Mr));
   const float op = __int_as_float(mt.z);
   const float k1 = -2.0f * (float)LN2 * gm.w * op, k2 = op * __int_as_float(mt.w);
   const double A = val == 0 ? Ax : (val == 1 ? Ay : Ar);
   const float v = mt.x < 0 ? (float)M0 : (val == 2 ? k2 : k1) * (float)A;
   // strokes take values 0..2, fills value 3
-  if (ok && ((val == 3) == (mt.x < 0)) && v != 0.0f)
+  if (ok && ((val == 3) == (mt.x < 0)) && v != 0.0f && !(thin && M0 == 0.0))
     unsafeAtomicAdd(ggrad + (int64_t)(mt.x < 0 ? ~mt.x : mt.x) * GG + val, v);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

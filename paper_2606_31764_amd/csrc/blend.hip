@@ -1396,15 +1396,18 @@ __device__ inline void flush_moments(const float* park, const float* basis, cons
   const double M0 = quad_bcast<0>(m), Mx = quad_bcast<1>(m), My = quad_bcast<2>(m), Mr = quad_bcast<3>(m);
   const double cx = (double)gm.x - (double)mx, cy = (double)gm.y - (double)my;
   const double Ax = __builtin_fma(-cx, M0, Mx), Ay = __builtin_fma(-cy, M0, My);
-  const bool thin = gm.z < 0.2f;
-  const double Ar = thin ? __builtin_fma(Ax, Ax, Ay * Ay) * __builtin_amdgcn_rcp(M0)
-                         : __builtin_fma(-cy, My + Ay, __builtin_fma(-cx, Mx + Ax, Mr));
+  const double Ar = __builtin_fma(-cy, My + Ay, __builtin_fma(-cx, Mx + Ax, Mr));
   const float op = __int_as_float(mt.z);
   const float k1 = -2.0f * (float)LN2 * gm.w * op, k2 = op * __int_as_float(mt.w);
   const double A = val == 0 ? Ax : (val == 1 ? Ay : Ar);
-  const float v = mt.x < 0 ? (float)M0 : (val == 2 ? k2 : k1) * (float)A;
+  float v = mt.x < 0 ? (float)M0 : (val == 2 ? k2 : k1) * (float)A;
+  const bool thin = gm.z < 0.2f && mt.x >= 0;
+  if (__ballot(thin) != 0ull) {
+    if (thin && val == 2) v = k2 * (float)(__builtin_fma(Ax, Ax, Ay * Ay) * __builtin_amdgcn_rcp(M0));
+    if (thin && M0 == 0.0) v = 0.0f;
+  }
   // strokes take values 0..2, fills value 3
-  if (ok && ((val == 3) == (mt.x < 0)) && v != 0.0f && !(thin && M0 == 0.0))
+  if (ok && ((val == 3) == (mt.x < 0)) && v != 0.0f)
     unsafeAtomicAdd(ggrad + (int64_t)(mt.x < 0 ? ~mt.x : mt.x) * GG + val, v);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

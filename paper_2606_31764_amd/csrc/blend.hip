@@ -215,29 +215,39 @@ __device__ inline bool fill_axis(int org, int n, double h, float r, float inv, i
 }
 
 // A fill curve's plan row, one word per lane, so that the next run's can be
-// loaded while a run is walked.
+// loaded while a run is walked (the forward).
 struct PlanRow {
-  int c = -1, word = 0;
+  int c = -1, held = 0;
   __device__ void load(const int32_t* __restrict__ plan, int curve) {
     c = curve;
-    word = plan[(int64_t)P_STRIDE * curve + min((int)__lane_id(), P_STRIDE - 1)];
+    held = plan[(int64_t)P_STRIDE * curve + min((int)__lane_id(), P_STRIDE - 1)];
   }
+  __device__ int word(int k) const { return __builtin_amdgcn_readlane(held, k); }
 };
 
-// The run of fill curve c that holds list position `at` (whose Gaussian has
-// window index `local`): its rectangle and list positions, if they fit the
-// list.  `row` is loaded unless it is c's.  Wavefront-uniform.  Whether the list holds the whole rectangle there
-// is for fill_corners_ok to say.
-__device__ inline bool fill_run_at(const int32_t* __restrict__ plan, PlanRow& row, int c, int g, int local, float sigma, int at,
-                                   int start, int end, double h, float ks, float inv, const SceneTab& st, int lt,
-                                   int tile, FillRun* fr) {
-  if (row.c != c) row.load(plan, c);
+// The same by scalar loads where the run begins: the adjoint, which the row's
+// registers cost more than its loads (256 fill paths at 512^2, held by the lanes
+// and so: 0.136 and 0.132 ms in 8 x 8 tiles, 0.1345 and 0.1335 in 16 x 16).
+struct PlanRowScalar {
+  const __attribute__((address_space(4))) int32_t* row;
+  __device__ PlanRowScalar(const int32_t* plan, int curve)
+      : row((const __attribute__((address_space(4))) int32_t*)(plan + (int64_t)P_STRIDE * curve)) {}
+  __device__ int word(int k) const { return row[k]; }
+};
+
+// The run of fill curve c (its plan row: `row`) that holds list position `at`
+// (whose Gaussian has window index `local`): its rectangle and list positions,
+// if they fit the list.  Wavefront-uniform.  Whether the list holds the whole
+// rectangle there is for fill_corners_ok to say.
+template <class Row>
+__device__ inline bool fill_run_at(const Row& row, int c, int g, int local, float sigma, int at, int start, int end,
+                                   double h, float ks, float inv, const SceneTab& st, int lt, int tile, FillRun* fr) {
   fr->c = c;
-  fr->ix0 = __builtin_amdgcn_readlane(row.word, P_IX0);
-  fr->iy0 = __builtin_amdgcn_readlane(row.word, P_IY0);
-  fr->nx = __builtin_amdgcn_readlane(row.word, P_NX);
-  fr->goff = __builtin_amdgcn_readlane(row.word, P_GOFF);
-  const int ny = __builtin_amdgcn_readlane(row.word, P_NY);
+  fr->ix0 = row.word(P_IX0);
+  fr->iy0 = row.word(P_IY0);
+  fr->nx = row.word(P_NX);
+  fr->goff = row.word(P_GOFF);
+  const int ny = row.word(P_NY);
   fr->g_top = g;
   fr->sigma = sigma;
   if (fr->nx <= 0 || ny <= 0) return false;
@@ -631,13 +641,16 @@ __device__ __forceinline__ void fwd_serial(const nsplat_params& pr, const Work& 
       const float rr = ks * sg;
       float og[FNIT];
       bool take = false;
-      if (rr * rr >= (float)FR_R2 && rr * rr < (float)(FR_R2 + 5) &&
-          fill_run_at(plan, prow, c, __builtin_amdgcn_readfirstlane(e.g), __builtin_amdgcn_readfirstlane(e.r.local),
-                      sg, hi - 1, start, end, 1.0, ks, inv_tile, st, lt, TILE, &fr)) {
-        // the opacities and the corner check in flight together
-        const int ib = x0 + (quad % Cfg::COLS) * Cfg::SUB - fr.ix0 - FR_R, jb = y0 + (quad / Cfg::COLS) * Cfg::SUB - fr.iy0 - FR_R;
-        fill_gather<FNB, FNIT>(w.gop, gcap, fr, ib, jb, fr.p_lo, hi - 1, 0.0f, og);
-        take = fill_corners_ok(idx, fr);
+      if (rr * rr >= (float)FR_R2 && rr * rr < (float)(FR_R2 + 5)) {
+        if (prow.c != c) prow.load(plan, c);
+        if (fill_run_at(prow, c, __builtin_amdgcn_readfirstlane(e.g), __builtin_amdgcn_readfirstlane(e.r.local), sg,
+                        hi - 1, start, end, 1.0, ks, inv_tile, st, lt, TILE, &fr)) {
+          // the opacities and the corner check in flight together
+          const int ib = x0 + (quad % Cfg::COLS) * Cfg::SUB - fr.ix0 - FR_R,
+                    jb = y0 + (quad / Cfg::COLS) * Cfg::SUB - fr.iy0 - FR_R;
+          fill_gather<FNB, FNIT>(w.gop, gcap, fr, ib, jb, fr.p_lo, hi - 1, 0.0f, og);
+          take = fill_corners_ok(idx, fr);
+        }
       }
       if (take) {
         const int top = hi - 1;
@@ -1564,7 +1577,6 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
     // atomic.
     constexpr int BNB = Cfg::SUB + 2 * FR_R;  // lattice neighbourhood of the pixel block, per axis
     constexpr int BNIT = (BNB * BNB + 63) / 64;
-    PlanRow prow;
     auto fill_run_bwd = [&](const FillRun& fr, const float (&col)[3], int p0, int p1, const float (&og)[BNIT]) {
       constexpr int NB = BNB;                  // 16 cells per axis
       constexpr int NS = FR_NS;                // LDS row stride (conflict-free rows)
@@ -1612,9 +1624,6 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
       const int pb0 = fr.p_lo + (y0 + qy + ly - fr.iy0 - fr.j0) * fr.w + (x0 + qx + lx - fr.ix0 - fr.i0);
 #pragma unroll 1
       for (int dy = -FR_R; dy <= FR_R; ++dy) {
-        // by the middle of the walk the next step's first entry is there
-        if (dy == 0 && s_lo < c_hi && __builtin_amdgcn_readfirstlane(e[0].kind) == 1)
-          prow.load(plan, __builtin_amdgcn_readfirstlane(e[0].r.curve));
         const int dxm = dy * dy <= 4 ? 4 : (dy * dy == 9 ? 3 : 2);  // dx^2 + dy^2 <= FR_R2
         const int roff = (ly + dy + FR_R) * NS + lx + FR_R;         // this pixel's cell in row dy
         const int rpos = pb0 + dy * fr.w;
@@ -1696,9 +1705,9 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
         const int p0 = s_lo;
         int p1 = 0;
         if (rr * rr >= (float)FR_R2 && rr * rr < (float)(FR_R2 + 5) &&
-            fill_run_at(plan, prow, c, __builtin_amdgcn_readfirstlane(e[0].g),
-                        __builtin_amdgcn_readfirstlane(e[0].r.local),
-                        sg, s_lo, start, end, 1.0, ks, inv_tile, st, lt, TILE, &fr)) {
+            fill_run_at(PlanRowScalar(plan, c), c, __builtin_amdgcn_readfirstlane(e[0].g),
+                        __builtin_amdgcn_readfirstlane(e[0].r.local), sg, s_lo, start, end, 1.0, ks, inv_tile, st, lt,
+                        TILE, &fr)) {
           // the opacities and the corner check in flight together
           p1 = min(fr.p_hi, c_hi - 1);
           const int ib = x0 + qx - fr.ix0 - FR_R, jb = y0 + qy - fr.iy0 - FR_R;

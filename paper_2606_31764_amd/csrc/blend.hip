@@ -38,8 +38,9 @@ struct TileCfg {
 };
 constexpr int WPB = 4;                  // wavefronts per block
 // Kernel forms (template KIND): with the tangent-aligned kind, with the
-// fill-run walk (see FillRun).
-constexpr int KIND_ANI = 1, KIND_FILL = 2;
+// fill-run walk (see FillRun), and (the adjoint) with the sums of very long
+// curves (LONG_TAUS).
+constexpr int KIND_ANI = 1, KIND_FILL = 2, KIND_LONG = 4;
 constexpr int BLOCK = 64 * WPB;
 
 template <int TILE>
@@ -338,13 +339,19 @@ __host__ __device__ constexpr int bwd_waves(int E, int kind) {
 __host__ __device__ constexpr size_t bwd_wave_bytes(int E) {
   return (size_t)64 * E * BWD_ENTRY_BYTES + (size_t)RB * (RB_ROW * 4 + 8);
 }
-// Stroke curves of more knot intervals than this keep their per-pixel FP32
-// terms and the order of their sums (three parked rows per entry, flush_rows)
-// instead of the moments of flush_moments: their knot-interval gradients are
-// suffix sums over thousands of samples that nearly cancel, so any other order
-// moves them by that many roundings.  The moments (FP64 sums) agree with them
-// within 3e-6 at 2,000 intervals and are nearer to the exact values, but at
-// 10,240 they differ by 1.2e-5 to 2.0e-5, where a change of version should not.
+// Stroke curves of more knot intervals than this keep the per-pixel FP32 terms
+// and the order of their sums (three parked rows per entry, flush_rows) that all
+// strokes had before the moments of flush_moments.  Not for their precision: the
+// moments are the nearer form.  A knot interval's gradient is a suffix sum over
+// all samples behind it that nearly cancels, and against 64-bit values the
+// intervals' gradients of one curve at 1024^2 are off by (relative, 2-norm; the
+// mean of three curves, three rows and moments, in 1e-6) 8.3 and 4.7 at 2,000
+// intervals, 13.5 and 6.8 at 4,000, 14.9 and 7.7 at 10,240, 21.4 and 6.1 at
+// 16,000.  But the two forms also differ from each other by that much, growing
+// with the count (the largest of 24 curves: 0.7e-5 at 2,000, 1.4e-5 at 4,000,
+// 1.6e-5 at 6,000, 1.9e-5 at 8,000, 2.5e-5 at 10,240), and a curve's results are
+// held to 2e-5 of what they were.  The switch stands where that is met with a
+// margin; the price is an adjoint of 0.354 ms instead of 0.263 at 10,240.
 constexpr int LONG_TAUS = 6000;
 // the flush's basis table (one per block): four functions of the 64 lanes
 constexpr int BASIS_BYTES = 4 * RB_ROW * 4;
@@ -1462,7 +1469,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
   const int depth = min(pr.batch, 64 * E);
   const float amax = pr.alpha_max, ks = pr.k_sigma;
   const float ln2 = (float)LN2;
-  constexpr bool ANI = (KIND & KIND_ANI) != 0;
+  constexpr bool ANI = (KIND & KIND_ANI) != 0, LONG = (KIND & KIND_LONG) != 0;
   // fill runs pixel by pixel (see FillRun)
   const bool fill_lattice = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
   const float inv_tile = 1.0f / (float)TILE;
@@ -1479,7 +1486,6 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
   const uint64_t below = lanes_below();
   float* __restrict__ ggrad = w.ggrad;
   const const_i32 taus = (const_i32)cv.tau_off;
-  const bool any_long = cv.n_taus > LONG_TAUS;
   const const_i32 item_off = (const_i32)w.item_off;  // not written during the kernel: scalar loads
   const int n_items = item_off[n_tiles];
   for (int it = 0;; ++it) {
@@ -1816,7 +1822,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
           cur = __builtin_amdgcn_readfirstlane(__float_as_int(pc.w));
           cur_fill = __builtin_amdgcn_readfirstlane(mt.x) < 0;
           cur_aniso = ANI && !cur_fill && __builtin_amdgcn_readfirstlane(mt.w) < 0;
-          cur_long = any_long && !cur_fill && taus[cur + 1] - taus[cur] > LONG_TAUS;
+          cur_long = LONG && !cur_fill && taus[cur + 1] - taus[cur] > LONG_TAUS;
           since = 0;
         }
         if (ANI && cur_aniso) {
@@ -1879,7 +1885,7 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
             n_rows = __builtin_amdgcn_readfirstlane(n_rows + 5);
           }
           if (n_rows > 0) flush_rows(park, ptgt, n_rows, ggrad);
-        } else if (cur_long) {
+        } else if (LONG && cur_long) {
           // stroke Gaussians of very long curves (LONG_TAUS): dL/dmu (2) and
           // dL/dsigma formed per pixel and parked in three rows
           if (n_ent > 0) flush_pending(j, n_ent);  // the rows are shared
@@ -2061,13 +2067,19 @@ hipError_t fwd_d(const Launch& L, float* image, float* T_final, int32_t* n_last,
   }
 }
 
+// (KIND_LONG only where the batch has intervals enough for a curve of more than
+// LONG_TAUS: its registers cost the other launches 1 to 2 %, 256 fill paths at
+// 512^2 0.1335 -> 0.1325 ms without, 12 quintic strokes 0.293 -> 0.289)
 template <int C, int TILE, int E>
 hipError_t bwd_k(const Launch& L, const float* dL, const float* T_final, const int32_t* n_last, int persistent) {
-  switch (kinds_of(L)) {
+  switch (kinds_of(L) | (L.cv->n_taus > LONG_TAUS ? KIND_LONG : 0)) {
     case 0: return bwd_t<C, TILE, E, 0>(L, dL, T_final, n_last, persistent);
     case KIND_ANI: return bwd_t<C, TILE, E, KIND_ANI>(L, dL, T_final, n_last, persistent);
     case KIND_FILL: return bwd_t<C, TILE, E, KIND_FILL>(L, dL, T_final, n_last, persistent);
-    default: return bwd_t<C, TILE, E, KIND_ANI | KIND_FILL>(L, dL, T_final, n_last, persistent);
+    case KIND_ANI | KIND_FILL: return bwd_t<C, TILE, E, KIND_ANI | KIND_FILL>(L, dL, T_final, n_last, persistent);
+    case KIND_LONG: return bwd_t<C, TILE, E, KIND_LONG>(L, dL, T_final, n_last, persistent);
+    case KIND_FILL | KIND_LONG: return bwd_t<C, TILE, E, KIND_FILL | KIND_LONG>(L, dL, T_final, n_last, persistent);
+    default: return bwd_t<C, TILE, E, KIND_ANI | KIND_FILL | KIND_LONG>(L, dL, T_final, n_last, persistent);
   }
 }
 

@@ -1226,16 +1226,28 @@ __device__ __forceinline__ void fwd_block(const nsplat_params& pr, const Work& w
   }
 }
 
-// The first n_long tiles of the blend order (the binning's choice) take a
+struct FwdSerialLds {
+  FwdRec rec[WPB * 64 * FWD_ENTRY_BYTES / sizeof(FwdRec)];
+  int next;
+};
+
+// SPLIT: the first n_long tiles of the blend order (the binning's choice) take a
 // block per quadrant, the others a wavefront per quadrant, eight to a block.
-template <int C, int TILE, int KIND>
-__global__ __launch_bounds__(FWD_BLOCK, KIND & KIND_FILL ? 4 : 6) void k_blend_fwd(
+// Otherwise every quadrant takes a wavefront, four to a block, in a form of its
+// own: fwd_serial alone waits for the longest list, where registers for eight
+// entries in flight count and a fifth wavefront per SIMD does not.  With a given
+// chunk, in the split form's registers (79), held to five wavefronts (72) and to
+// four (107): 12 quintic strokes at 512^2 0.470, 0.428, 0.378 ms, 16 closed ones
+// 0.077, 0.072, 0.065; 16 x 2000 key points at 1024^2, which fill the GPU, 0.298,
+// 0.274, 0.295.
+template <int C, int TILE, int KIND, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? FWD_BLOCK : BLOCK, SPLIT && !(KIND & KIND_FILL) ? 6 : 4) void k_blend_fwd(
     nsplat_params pr, Work w, int n_scenes, int n_tiles, const Gauss* __restrict__ gs,
     const int32_t* __restrict__ ranges, const int32_t* __restrict__ idx, const float* __restrict__ bg,
     float* __restrict__ image, float* __restrict__ Tfin, int32_t* __restrict__ nlast, const int32_t* __restrict__ plan,
     int64_t gcap, int persistent, int ck_arg) {
   using Cfg = TileCfg<TILE>;
-  __shared__ __align__(16) FwdLds L;
+  __shared__ __align__(16) std::conditional_t<SPLIT, FwdLds, FwdSerialLds> L;
   typedef const __attribute__((address_space(4))) int32_t* const_i32;
   // the chunk length: the caller's, or the one the binning chose
   const int ck_lg = ck_arg >= 0 ? ck_arg : ((const_i32)w.queue)[Q_CKLG];
@@ -1244,10 +1256,8 @@ __global__ __launch_bounds__(FWD_BLOCK, KIND & KIND_FILL ? 4 : 6) void k_blend_f
   const bool fill_lattice = (KIND & KIND_FILL) != 0 && read_h(pr) == 1.0f;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_items = n_tiles * Cfg::QUADS;
-  // (launches that cannot hold a long list come in blocks of WPB wavefronts)
-  const int wpb = blockDim.x >> 6;
-  const int n_long =
-      wpb < FW || fill_lattice ? 0 : min(max(((const_i32)w.queue)[Q_NLONG], 0), n_tiles) * Cfg::QUADS;
+  constexpr int wpb = SPLIT ? FW : WPB;
+  const int n_long = !SPLIT || fill_lattice ? 0 : min(max(((const_i32)w.queue)[Q_NLONG], 0), n_tiles) * Cfg::QUADS;
   for (int it = 0;; ++it) {
     int b = blockIdx.x;
     if (persistent) {
@@ -1273,9 +1283,11 @@ __global__ __launch_bounds__(FWD_BLOCK, KIND & KIND_FILL ? 4 : 6) void k_blend_f
     im.y0 = (im.lt / im.st.tiles_x) * TILE;
     im.start = ranges[2 * im.tile];
     im.end = ranges[2 * im.tile + 1];
-    if (whole) {
-      fwd_block<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, ck_lg, L);
-      continue;
+    if constexpr (SPLIT) {
+      if (whole) {
+        fwd_block<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, ck_lg, L);
+        continue;
+      }
     }
     fwd_serial<C, TILE, KIND>(pr, w, im, gs, idx, bg, image, Tfin, nlast, plan, gcap, ck_lg, fill_lattice,
                               (char*)L.rec + wv * (64 * FWD_ENTRY_BYTES));
@@ -2001,28 +2013,36 @@ int resident_grid(K kernel, int n_blocks, int n_cu, size_t lds, int block = BLOC
 
 inline int depth_factor(int batch) { return batch <= 64 ? 1 : (batch <= 128 ? 2 : 4); }
 
-template <int C, int TILE, int KIND>
-hipError_t fwd_t(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
+template <int C, int TILE, int KIND, bool SPLIT>
+hipError_t fwd_s(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
   constexpr int QUADS = TileCfg<TILE>::QUADS;
   const int64_t n_items = L.n_tiles * QUADS;
   if (n_items <= 0) return hipSuccess;
   // blocks: one per item of a long list (at least LONG_LEAST positions each;
   // their number is on the device), one per wpb others
-  const bool split = split_long(*L.pr) && !((KIND & KIND_FILL) && !L.pr->h_dev && L.pr->h == 1.0f);
-  const int wpb = split ? FW : WPB;
-  const int64_t n_long = split ? std::min(L.n_tiles, (int64_t)L.bf->caps.pairs / LONG_LEAST) * QUADS : 0;
+  constexpr int wpb = SPLIT ? FW : WPB;
+  const int64_t n_long = SPLIT ? std::min(L.n_tiles, (int64_t)L.bf->caps.pairs / LONG_LEAST) * QUADS : 0;
   int64_t blocks = std::min(n_items, n_long + (n_items + wpb - 1) / wpb);
   // (a launch counts its threads in 32 bits)
   if (persistent || blocks * 64 * wpb > 0x7fffffffLL) {
     persistent = 1;
-    blocks = resident_grid(k_blend_fwd<C, TILE, KIND>, (int)std::min<int64_t>(blocks, 0x7fffffff), L.n_cu, 0, 64 * wpb);
+    blocks = resident_grid(k_blend_fwd<C, TILE, KIND, SPLIT>, (int)std::min<int64_t>(blocks, 0x7fffffff), L.n_cu, 0, 64 * wpb);
     hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, L.stream, L.w.queue);
   }
   Phase ph(L, NSPLAT_T_BLEND_FWD);
-  hipLaunchKernelGGL((k_blend_fwd<C, TILE, KIND>), dim3((int)blocks), dim3(64 * wpb), 0, L.stream, *L.pr, L.w,
+  hipLaunchKernelGGL((k_blend_fwd<C, TILE, KIND, SPLIT>), dim3((int)blocks), dim3(64 * wpb), 0, L.stream, *L.pr, L.w,
                      L.sc->n_scenes, (int)L.n_tiles, (const Gauss*)L.bf->gauss, L.bf->ranges, L.bf->idx, L.sc->bg,
                      image, T_final, n_last, L.bf->plan, (int64_t)L.bf->caps.gauss, persistent, L.ck_lg);
   return hipGetLastError();
+}
+
+// Long lists on blocks (SPLIT) where the chunk length is left to choose, and not
+// at a grid step of 1 known here, where fill runs are walked whole.
+template <int C, int TILE, int KIND>
+hipError_t fwd_t(const Launch& L, float* image, float* T_final, int32_t* n_last, int persistent) {
+  if (split_long(*L.pr) && !((KIND & KIND_FILL) && !L.pr->h_dev && L.pr->h == 1.0f))
+    return fwd_s<C, TILE, KIND, true>(L, image, T_final, n_last, persistent);
+  return fwd_s<C, TILE, KIND, false>(L, image, T_final, n_last, persistent);
 }
 
 template <int C, int TILE, int E, int KIND>

@@ -548,7 +548,29 @@ __global__ __launch_bounds__(256) void k_order_count(const int32_t* __restrict__
   if (threadIdx.x < 32 && h[threadIdx.x] > 0) atomicAdd(&obin[threadIdx.x], h[threadIdx.x]);
 }
 
-__global__ void k_order_scan(int32_t* obin, int32_t* queue, const int32_t* counters, int split, int quads, int n_cu) {
+// The number of long lists (Q_NLONG): those of the classes up to long_class's,
+// or, where that makes a launch of many lists about as long as each other, up to
+// the next class above.  A long list's block saves time while the launch waits for
+// it.  Where the blocks don't all start at once (a compute unit holds two or three)
+// and the longest list is below four times the bound, the launch waits for the sum
+// of its work instead, to which the blocks add.  Forward with and without this:
+// 256 fill paths at 512^2 and h = 4 0.085 and 0.097 ms (0.083 on wavefronts alone),
+// in 8 x 8 tiles 0.077 and 0.111, 100 paths at h = 2 0.054 and 0.074, at h = 5
+// 0.037 and 0.049, 160 mixed curves at 512^2 and h = 2 0.139 and 0.166; one class
+// up for every launch costs 12 quintic strokes at 512^2 (longest list six times the
+// bound) 0.231 -> 0.311, one curve of 10,240 key points (35 long lists) 0.116 ->
+// 0.163.  Called by a wavefront; lane l < 32 holds the number n of lists of class l
+// and their running sum; blocks: per list.
+__device__ inline int n_long_lists(int n, int incl, int64_t pairs, int quads, int blocks, int n_cu) {
+  const int lane = __lane_id(), c = long_class(pairs, quads, n_cu);
+  const uint64_t some = __ballot(lane < 32 && n > 0);
+  const int longest = some ? __builtin_ctzll(some) : 31;
+  const int at = __shfl(incl, c), above = __shfl(incl, c > 0 ? c - 1 : 0);
+  return 2 * (int64_t)at * blocks > 5 * (int64_t)n_cu && c - longest <= 1 ? above : at;
+}
+
+__global__ void k_order_scan(int32_t* obin, int32_t* queue, const int32_t* counters, int split, int quads, int blocks,
+                             int n_cu) {
   const int l = threadIdx.x;
   const int v = l < 32 ? obin[l] : 0;
   int incl = v;
@@ -558,7 +580,8 @@ __global__ void k_order_scan(int32_t* obin, int32_t* queue, const int32_t* count
     if (l >= off) incl += o;
   }
   if (l < 32) obin[32 + l] = incl - v;
-  if (l == long_class(counters[NSPLAT_CNT_PAIRS], quads, n_cu)) queue[Q_NLONG] = split ? incl : 0;
+  const int n_long = n_long_lists(v, incl, counters[NSPLAT_CNT_PAIRS], quads, blocks, n_cu);
+  if (l == 0) queue[Q_NLONG] = split ? n_long : 0;
 }
 
 __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict__ ranges, int n_tiles,
@@ -679,8 +702,9 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_tile_plan(int32_t* __restrict_
     if (tid < 32) {
       base[tid] = incl - v;
       h[tid] = 0;
-      if (tid == long_class(counters[NSPLAT_CNT_PAIRS], quads, n_cu)) queue[Q_NLONG] = split ? incl : 0;
     }
+    const int n_long = n_long_lists(v, incl, counters[NSPLAT_CNT_PAIRS], quads, blocks, n_cu);
+    if (tid == 0) queue[Q_NLONG] = split ? n_long : 0;
   }
   __syncthreads();
   for (int t = tid; t < n_tiles; t += PLAN_THREADS) {
@@ -846,7 +870,7 @@ hipError_t launch_bin(const Launch& L) {
       hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, L.stream, L.w.obin, 0, (int64_t)64);
       hipLaunchKernelGGL(k_order_count, dim3(ob), dim3(256), 0, L.stream, L.bf->ranges, nt, L.w.obin);
       hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(64), 0, L.stream, L.w.obin, L.w.queue, cnt, split,
-                         rule_quads(L.pr->tile), L.n_cu);
+                         rule_quads(L.pr->tile), adj_blocks(L.pr->tile), L.n_cu);
       hipLaunchKernelGGL(k_order_scatter, dim3(ob), dim3(256), 0, L.stream, L.bf->ranges, nt, L.w.obin, L.w.order);
       const int cb = grid_for(nt, 256, 4096);
       hipLaunchKernelGGL(k_chunk_counts, dim3(cb), dim3(256), 0, L.stream, L.bf->ranges, nt, ca, cnt,

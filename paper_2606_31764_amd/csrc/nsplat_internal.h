@@ -166,13 +166,16 @@ constexpr int Q_CKLG = 11;
 constexpr int Q_NLONG = 12;
 // Lists are long from this length class (__clz of the length) on: those whose
 // length is at least the positions of all quadrants / (LONG_SHARE x compute
-// units), rounded down to a power of two, and at least LONG_LEAST.  A list
-// below the first bound ends, on one wavefront, before the rest of the launch
-// does, and a block composites it with about half more instructions; one above
-// it would be waited for.  Measured at 1/3, 1, 2 and 16 times the share: 12
-// quintic strokes at 512^2 0.410, 0.228, 0.179, 0.175 ms; one curve of 10,240
-// key points at 1024^2 0.162, 0.140, 0.157, 0.250; 16 x 2000 key points at
-// 1024^2 0.307, 0.307, 0.313, 0.48 (0.139 and 0.322 on one wavefront each).
+// units), rounded down to a power of two, and at least LONG_LEAST (n_long_lists
+// may go one class up).  A list below the first bound ends, on one wavefront,
+// before the rest of the launch does, and a block composites it with about half
+// more instructions; one above it would be waited for.  Forward with the bound at
+// 1/4, 1/2, 1, 2 and 4 times this: 12 quintic strokes at 512^2 0.172, 0.195, 0.231,
+// 0.311, 0.444 ms; one curve of 10,240 key points at 1024^2 0.216, 0.158, 0.116,
+// 0.163, 0.166; 16 x 2000 key points at 1024^2 0.430, 0.295, 0.294, 0.293, 0.293; 16
+// closed strokes at 512^2 0.051, 0.051, 0.052, 0.053, 0.055; 200 mixed curves at
+// 777 x 1003 and h = 2 0.363, 0.229, 0.208, 0.208, 0.208.  A lower bound would serve
+// the first at the cost of the others, where most of the lists are near it.
 // LONG_LEAST 512, 256, 128: 32 strokes at 256^2 0.038, 0.028, 0.028 ms, 32
 // tangent-aligned ones (longest list 265) 0.029, 0.028, 0.022.
 constexpr int LONG_SHARE = 9, LONG_LEAST = 128;

@@ -553,7 +553,8 @@ __global__ __launch_bounds__(256) void k_order_count(const int32_t* __restrict__
 // the next class above.  A long list's block saves time while the launch waits for
 // it.  Where the blocks don't all start at once (a compute unit holds two or three)
 // and the longest list is below four times the bound, the launch waits for the sum
-// of its work instead, to which the blocks add.  Forward with and without this:
+// of its work instead, to which the blocks add (not where LONG_LEAST is the bound:
+// there the sum is small).  Forward with and without this:
 // 256 fill paths at 512^2 and h = 4 0.085 and 0.097 ms (0.083 on wavefronts alone),
 // in 8 x 8 tiles 0.077 and 0.111, 100 paths at h = 2 0.054 and 0.074, at h = 5
 // 0.037 and 0.049, 160 mixed curves at 512^2 and h = 2 0.139 and 0.166; one class
@@ -566,7 +567,8 @@ __device__ inline int n_long_lists(int n, int incl, int64_t pairs, int quads, in
   const uint64_t some = __ballot(lane < 32 && n > 0);
   const int longest = some ? __builtin_ctzll(some) : 31;
   const int at = __shfl(incl, c), above = __shfl(incl, c > 0 ? c - 1 : 0);
-  return 2 * (int64_t)at * blocks > 5 * (int64_t)n_cu && c - longest <= 1 ? above : at;
+  const bool full = c < __builtin_clz(LONG_LEAST) && 2 * (int64_t)at * blocks > 5 * (int64_t)n_cu;
+  return full && c - longest <= 1 ? above : at;
 }
 
 __global__ void k_order_scan(int32_t* obin, int32_t* queue, const int32_t* counters, int split, int quads, int blocks,

@@ -474,7 +474,6 @@ struct Launch {
   int n_cu;
   int ck_lg;  // log2 of params.chunk, or CK_ARG_*: chosen by the binning (Q_CKLG)
 };
-// the adjoint's pixel blocks per chunk for this launch's tile side and curves
 
 // Scene table; also clears the NSPLAT_NUM_COUNTERS counters when given.
 hipError_t launch_scene_setup(const Launch& L, int32_t* clear_counters);

@@ -194,8 +194,7 @@ typedef struct {
   int32_t chunk;    /* list positions per chunk of the adjoint's split of each
                        tile list (the forward stores every pixel's state at
                        chunk boundaries; the adjoint runs one work item per
-                       tile quadrant, or 8 x 8 block, and chunk): a power
-                       of two in
+                       8 x 8 pixels of the tile and chunk): a power of two in
                        [512, 8192], or 0: chosen by nsplat_bin on the device
                        from the pair count (with fills about pairs x quadrants
                        per tile / (8 x compute units), a quarter of it where
@@ -312,9 +311,8 @@ int nsplat_forward(nsplat_ctx* ctx, const nsplat_curves* curves, const nsplat_sc
  * key-point / interval parametrisation.  Counts, windows and span choices are
  * held fixed (piecewise constant).  All gradients are overwritten.
  * NSPLAT_EINVAL also when, at 32 x 32 tiles, the last nsplat_bin on these
- * buffers saw curves that differ from these in whether any is NSPLAT_FILLED:
- * it laid out the adjoint's work items per 8 x 8 pixel block for the tiles
- * of scenes with fills and per quadrant for the others. */
+ * buffers saw curves that differ from these in whether any is NSPLAT_FILLED
+ * (its lists belong to another step). */
 int nsplat_backward(nsplat_ctx* ctx, const nsplat_curves* curves, const nsplat_scenes* scenes,
                     const nsplat_params* params, const nsplat_buffers* bufs, const float* dL_dimage,
                     const float* T_final, const int32_t* n_last, const nsplat_grads* grads,

@@ -18,12 +18,12 @@ struct nsplat_ctx {
   int n_cu = 256;
   std::string err;
   nsp::Timer timer;
-  // tile side, chunk length and adjoint pixel blocks per chunk of the last
-  // nsplat_bin on each workspace (the tile lists, checkpoint offsets and
-  // adjoint items in it are laid out for them)
+  // tile side and chunk length of the last nsplat_bin on each workspace (the
+  // tile lists, checkpoint offsets and adjoint items in it are laid out for
+  // them), and whether its curves declared fills (fills_of)
   struct BinState {
     const void* ws;
-    int tile, chunk, blocks;
+    int tile, chunk, fills;
   };
   std::vector<BinState> bin_tile;
   // what the scene table of each workspace was last built for (tile side,
@@ -293,26 +293,26 @@ bool scene_table_current(nsplat_ctx* ctx, const void* ws, const nsplat_scenes* s
 
 // Whether a launch at 32 x 32 tiles declares fills (the binning and the adjoint
 // of a step must agree).
-int blocks_of(const Launch& L) {
+int fills_of(const Launch& L) {
   return L.pr->tile == 32 ? ((L.cv->any_flags & NSPLAT_FILLED) ? 2 : 1) : 0;
 }
 
-void record_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int blocks) {
+void record_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int fills) {
   for (auto& e : ctx->bin_tile)
     if (e.ws == ws) {
       e.tile = tile;
       e.chunk = chunk;
-      e.blocks = blocks;
+      e.fills = fills;
       return;
     }
-  ctx->bin_tile.push_back({ws, tile, chunk, blocks});
+  ctx->bin_tile.push_back({ws, tile, chunk, fills});
 }
 
 // NSPLAT_EINVAL when the workspace's tile lists were built (by this context)
-// for another tile side or params.chunk than this launch's, or (blocks > 0,
+// for another tile side or params.chunk than this launch's, or (fills > 0,
 // the adjoint) for curves that declared fills where these do not, or the other
-// way round, at 32 x 32 tiles (blocks_of).
-int check_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int blocks = 0) {
+// way round, at 32 x 32 tiles (fills_of).
+int check_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int fills = 0) {
   for (const auto& e : ctx->bin_tile) {
     if (e.ws != ws) continue;
     if (e.tile != tile)
@@ -321,7 +321,7 @@ int check_bin_tile(nsplat_ctx* ctx, const void* ws, int tile, int chunk, int blo
     if (e.chunk != chunk)
       return fail(ctx, NSPLAT_EINVAL, "the tile lists of this workspace were built by nsplat_bin with chunk %d, "
                   "but params.chunk is %d", e.chunk, chunk);
-    if (blocks > 0 && e.blocks != blocks)
+    if (fills > 0 && e.fills != fills)
       return fail(ctx, NSPLAT_EINVAL, "the adjoint items (pixel blocks per chunk) of this workspace were built by "
                   "nsplat_bin for other curves: any_flags differs in NSPLAT_FILLED");
   }
@@ -434,7 +434,7 @@ int nsplat_bin(nsplat_ctx* ctx, const nsplat_curves* cv, const nsplat_scenes* sc
   }
   if (h == hipSuccess) h = launch_bin(L);
   if (h != hipSuccess) return hip_fail(ctx, h, "nsplat_bin");
-  record_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, blocks_of(L));
+  record_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, fills_of(L));
   return NSPLAT_OK;
 }
 
@@ -458,7 +458,7 @@ int nsplat_backward_reg(nsplat_ctx* ctx, const nsplat_curves* cv, const nsplat_s
   int e = prepare(ctx, cv, sc, pr, bf, stream, &L);
   if (e) return e;
   if (!dL || !T_final || !n_last || !gr) return fail(ctx, NSPLAT_EINVAL, "dL_dimage / T_final / n_last / grads is NULL");
-  if ((e = check_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, blocks_of(L)))) return e;
+  if ((e = check_bin_tile(ctx, bf->ws, pr->tile, pr->chunk, fills_of(L)))) return e;
   const bool use_reg = reg && (reg->bbox_weight != 0.0f || reg->deriv_weight != 0.0f);
   if (use_reg) {
     if (reg->deriv_weight != 0.0f && (reg->deriv_order < 1 || reg->deriv_order > 3))

@@ -603,7 +603,6 @@ __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict
   if (t < n_tiles) order[base[k] + r] = t;
 }
 
-// Forward-state checkpoints of tile t: one per chunk boundary inside its list.
 // The launch's log2 chunk length: the caller's (ck_arg >= 0), or chosen from
 // the pair count.
 struct ChunkArg {
@@ -620,6 +619,7 @@ __device__ inline int launch_chunk_log2(const ChunkArg& ca, const int32_t* queue
   return auto_chunk_log2(pairs, quads, n_cu, runs);
 }
 
+// Forward-state checkpoints of each tile: one per chunk boundary inside its list.
 __global__ void k_chunk_counts(const int32_t* __restrict__ ranges, int n_tiles, ChunkArg ca, const int32_t* counters,
                                int quads, int n_cu, int32_t* __restrict__ queue, uint32_t* __restrict__ ck) {
   const int ck_lg = launch_chunk_log2(ca, queue, counters, quads, n_cu);

@@ -30,7 +30,9 @@ namespace {
 // loads one (E; the next step's loads are issued before the current step is
 // processed), entries whose support disc misses the quadrant are dropped, the rest are
 // compacted in order into the wavefront's own LDS arrays and then composited
-// one after another.  Wavefronts never wait for each other.
+// one after another.  Wavefronts work on their own, except for a block's on a long
+// list (fwd_block), and where a forward with a work queue takes its next items,
+// one per wavefront of the block, when all of the last are done.
 template <int TILE>
 struct TileCfg {
   static constexpr int SUB = 8, COLS = TILE / 8, QUADS = COLS * COLS;
@@ -95,7 +97,7 @@ struct Box {
 };
 
 // The pixel centres held by the lanes with a set bit in `live` (lane l owns
-// the BLK x BLK block at column l & 7, row l >> 3 of the quadrant): rows from
+// the pixel at column l & 7, row l >> 3 of the quadrant): rows from
 // the lowest and highest set bits, columns from the eight row bytes folded
 // together.  Scalar work on a wavefront-uniform mask; `live` != 0.
 __device__ inline Box live_box_of(int qx, int qy, uint64_t live) {
@@ -308,7 +310,6 @@ constexpr int FR_R2 = 20;  // dx^2 + dy^2 bound for k_sigma sigma = 4.5
 // lane rows of a half-wavefront in four different bank octets
 constexpr int FR_NS = 24;
 
-// LDS bytes per wavefront for a step of `depth` entries.
 // A forward entry: what every composited pixel reads, in one 32-byte record
 // (one LDS address per entry), and the colour, read where a run begins.
 struct FwdRec {
@@ -1766,9 +1767,8 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
       // pixels that take part somewhere in this step (their stop lies below
       // its top); walking back to front the set only grows.  Entries that
       // reach none of them are dropped.
-      bool lv = false, step_aniso = false;
-      lv = lv || (stop < s_hi);
-      const Box box = live_box_of(qx, qy, __ballot(lv));
+      bool step_aniso = false;
+      const Box box = live_box_of(qx, qy, __ballot(stop < s_hi));
 #pragma unroll
       for (int u = 0; u < E; ++u) {
         const int k = u * 64 + lane;
@@ -1878,14 +1878,11 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
             const float isp = isg * rq;           // 1 / sp
             const float rr = rq - 1.0f / rq;      // sigma / sp - sp / sigma
             const float rux = rq * gm.z, ruy = rq * gm.w;
-            float v[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            bool act = false;
             const float dx = px - gm.x, dy = py - gm.y;
             const float a = __builtin_fmaf(dx, gm.z, dy * gm.w);
             const float b = rq * __builtin_fmaf(dy, gm.z, -(dx * gm.w));
             const float m = __builtin_fmaf(a, a, b * b);
             const bool in = (mt.y >= stop) && (m <= lim);
-            act = act || in;
             const float G = __builtin_amdgcn_exp2f(-m);
             const float oG = op * G;
             const bool lt = oG < amax;
@@ -1894,19 +1891,15 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
             const float dLda = (in && lt) ? -Wc * r : 0.0f;
             T = in ? T * r : T;
             aT = __builtin_fmaf(alpha, T, aT);
-            v[5] = __builtin_fmaf(dLda, G, v[5]);  // dL/do_j
             const float h = dLda * op * G * two_ln2;
-            v[0] = __builtin_fmaf(h, __builtin_fmaf(a, gm.z, -(b * ruy)), v[0]);
-            v[1] = __builtin_fmaf(h, __builtin_fmaf(a, gm.w, b * rux), v[1]);
-            v[2] = __builtin_fmaf(h * a, a * isg, v[2]);
-            v[3] = __builtin_fmaf(h * b, b * isp, v[3]);
-            v[4] = __builtin_fmaf(h * a, b * rr, v[4]);
-            if (__ballot(act) == 0ull) continue;
+            const float v[5] = {h * __builtin_fmaf(a, gm.z, -(b * ruy)), h * __builtin_fmaf(a, gm.w, b * rux),
+                                (h * a) * (a * isg), (h * b) * (b * isp), (h * a) * (b * rr)};
+            if (__ballot(in) == 0ull) continue;
             if (n_rows + 5 > RB) {
               flush_rows(park, ptgt, n_rows, ggrad);
               n_rows = 0;
             }
-            accO += v[5];
+            accO += dLda * G;  // dL/do_j
 #pragma unroll
             for (int i = 0; i < 5; ++i) park[(n_rows + i) * RB_ROW + lane] = v[i];
             if (lane < 5) ptgt[n_rows + lane] = make_int2(mt.x, lane);
@@ -1929,12 +1922,9 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
             const int4 mt = wmeta[j];
             const float op = __int_as_float(mt.z);
             const float is3 = __int_as_float(mt.w);
-            float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            bool act = false;
             const float dx = px - gm.x, dy = py - gm.y;
             const float d2 = __builtin_fmaf(dx, dx, dy * dy);
             const bool in = (mt.y >= stop) && (d2 <= gm.z);
-            act = act || in;
             const float G = __builtin_amdgcn_exp2f(gm.w * d2);
             const float oG = op * G;
             const bool lt = oG < amax;
@@ -1943,18 +1933,15 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
             const float dLda = (in && lt) ? -Wc * r : 0.0f;
             T *= r;
             aT = __builtin_fmaf(alpha, T, aT);
-            v[3] = __builtin_fmaf(dLda, G, v[3]);  // dL/do_j
             const float dG = dLda * op;
             const float dd2 = dG * G * gm.w * ln2;  // d exp2(a d2) / d d2 = G a ln 2
-            v[0] = __builtin_fmaf(-2.0f * dx, dd2, v[0]);
-            v[1] = __builtin_fmaf(-2.0f * dy, dd2, v[1]);
-            v[2] = __builtin_fmaf(dG * G, d2 * is3, v[2]);
-            if (__ballot(act) == 0ull) continue;
-            if (n_rows + 3 > RB) {
+            const float v[3] = {-2.0f * dx * dd2, -2.0f * dy * dd2, dG * G * (d2 * is3)};
+            if (__ballot(in) == 0ull) continue;
+            if (__builtin_expect(n_rows + 3 > RB, 0)) {
               flush_rows(park, ptgt, n_rows, ggrad);
               n_rows = 0;
             }
-            accO += v[3];
+            accO += dLda * G;  // dL/do_j
 #pragma unroll
             for (int i = 0; i < 3; ++i) park[(n_rows + i) * RB_ROW + lane] = v[i];
             if (lane < 3) ptgt[n_rows + lane] = make_int2(mt.x, lane);

@@ -2061,13 +2061,16 @@ hipError_t bwd_t(const Launch& L, const float* dL, const float* T_final, const i
     max_items = std::max(max_items, std::min(blocks * (pairs / CK_SMALL), (int64_t)2 * SMALL_ITEMS * L.n_cu));
   max_items += blocks * L.n_tiles;
   const size_t lds = (size_t)WPB * bwd_wave_bytes(E) + BASIS_BYTES;
-  int grid = (int)((max_items + WPB - 1) / WPB);
-  if (persistent) {
-    grid = resident_grid(k_blend_bwd<C, TILE, E, KIND>, grid, L.n_cu, lds);
+  int64_t grid = (max_items + WPB - 1) / WPB;
+  // (a launch counts its threads in 32 bits and drops what is above: a grid for
+  // 2^31 pairs in 32 x 32 tiles left out most of the items, with no error)
+  if (persistent || grid * BLOCK > 0x7fffffffLL) {
+    persistent = 1;
+    grid = resident_grid(k_blend_bwd<C, TILE, E, KIND>, (int)std::min<int64_t>(grid, 0x7fffffff), L.n_cu, lds);
     hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(64), 0, L.stream, L.w.queue);
   }
   Phase ph(L, NSPLAT_T_BLEND_BWD);
-  hipLaunchKernelGGL((k_blend_bwd<C, TILE, E, KIND>), dim3(grid), dim3(BLOCK), lds, L.stream, *L.cv, *L.pr, L.w,
+  hipLaunchKernelGGL((k_blend_bwd<C, TILE, E, KIND>), dim3((int)grid), dim3(BLOCK), lds, L.stream, *L.cv, *L.pr, L.w,
                      L.sc->n_scenes, (int)L.n_tiles, (const Gauss*)L.bf->gauss, L.bf->ranges, L.bf->idx, L.sc->bg,
                      dL, T_final, n_last, L.bf->plan, (int64_t)L.bf->caps.gauss, persistent, 32 * 16 * L.n_cu, L.ck_lg);
   return hipGetLastError();

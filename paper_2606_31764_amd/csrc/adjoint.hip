@@ -1250,7 +1250,8 @@ hipError_t launch_adjoint(const Launch& L, const nsplat_grads* g) {
   }
   Phase ph(L, NSPLAT_T_FOLD);
   if (L.cv->n_curves > 0) {
-    if ((int64_t)L.cv->n_taus > 128 * (int64_t)L.cv->n_curves)  // long curves on average
+    // long curves on average (a launch counts its threads in 32 bits)
+    if ((int64_t)L.cv->n_taus > 128 * (int64_t)L.cv->n_curves && L.cv->n_curves < (1 << 21))
       hipLaunchKernelGGL(k_fold<1024>, dim3(L.cv->n_curves), dim3(1024), 0, L.stream, *L.cv, L.w, *g);
     else
       hipLaunchKernelGGL(k_fold<64>, dim3(L.cv->n_curves), dim3(64), 0, L.stream, *L.cv, L.w, *g);

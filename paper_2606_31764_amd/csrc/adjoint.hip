@@ -273,11 +273,10 @@ __device__ inline void accumulate_points(const Work& w, PointSums<PD>* st, bool 
       first = sum;
       sum = 0.0;
     }
-    // the lower half's last run goes on with the upper half's first samples
+    // the lower half's last run goes on with the upper half's first samples (with
+    // no run in the lower half, the upper half's first active sample begins one)
     const double up = __shfl(first, i + 32);
-    const bool lower = part == 0;
-    if (at >= 0) emit(at, lower ? sum + up : sum);
-    else if (lower && up != 0.0) emit(0, up);  // (no run in the lower half: up is 0)
+    if (at >= 0) emit(at, part == 0 ? sum + up : sum);
   }
 }
 

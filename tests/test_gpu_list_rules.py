@@ -1,0 +1,118 @@
+"""What nsplat_bin chooses from the lists' lengths (the adjoint's chunk length and
+the number of long lists) against the rules written out here, at sizes on both
+sides of each bound; and the block form of long lists in 32 x 32 tiles and in
+batches with fills off the pixel lattice, against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from helpers import IMG_TOL, PARAM_NAMES, gpu_run, gpu_vs_oracle, grad_close
+from paper_2606_31764_amd import synth
+from paper_2606_31764_amd.render import Params
+from test_gpu_long_lists import _params, _scene
+
+pytestmark = pytest.mark.gpu
+KNOT_PAD = 11
+
+
+def _choices(r):
+    """(log2 chunk length, long lists) of the last nsplat_bin, from the workspace."""
+    m, g, p, b = r.meta, r.caps["gauss"], r.caps["pairs"], max(r.caps["boundary"], 1)
+    N, tiles8 = m.n_curves, r.n_tiles_alloc
+    hist = max(1024 * max(-(-p // 4096), 1), 1025 * max(-(-g // 4096), 1))
+    scan = -(-max(g, hist, tiles8 + 1, 1) // 4096)
+    sizes = [8 * (m.n_taus + KNOT_PAD * N), 8 * N, 4 * (N + 1), 16 * b, 32 * (m.n_scenes + 1), 4 * (g + 1),
+             4 * p, 4 * p, 4 * p, 4 * hist, 4 * (scan + 1), 20 * g, 32 * (m.n_keys + 5 * N),
+             8 * (m.n_taus + KNOT_PAD * N), 32 * N, 16 * b]
+    off = r.ws_ptr - r.ws.data_ptr() + sum(-(-s // 256) * 256 for s in sizes)
+    q = r.ws[off:off + 256].cpu().numpy().view(np.int32)
+    G = r.read_counters()[0]
+    assert q[8] + q[9] == G, "the slots read are the binning's"
+    return int(q[11]), int(q[12])
+
+
+def _cu():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def _long(ranges, tile):
+    """The number of long lists by the rule: a power-of-two bound of the share of a
+    compute unit's ninth, at least 128, one up where the blocks are many and the
+    lists alike."""
+    n = ranges[:, 1] - ranges[:, 0]
+    quads, blocks = (1 if tile == 8 else 4), (tile // 8) ** 2
+    share = int(n.sum()) * quads // (9 * _cu())
+    bound = 1 << (max(share, 128).bit_length() - 1)
+    count = int((n >= bound).sum())
+    if bound > 128 and 2 * count * blocks > 5 * _cu() and n.max() < 4 * bound:
+        return int((n >= 2 * bound).sum())
+    return count
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+@pytest.mark.parametrize("lg", [7, 8, 9])
+def test_chosen_chunk(lg, tile):
+    """Sampled for a pair count in the middle of each length's range."""
+    b = synth.config2(seed=31, n_curves=24, size=160)
+    quads = 1 if tile == 8 else 4
+    per = 256 * 16 * _cu() / quads                      # pairs from which on 256 are taken
+    at = dict(zip((7, 8, 9), (0.6 * per, 1.4 * per, 2.5 * per)))[lg]
+    p = Params(delta_c=4.0, tile=tile)
+    p = p.replace(delta_c=4.0 * at / len(gpu_run(b, p, backward=False)["idx"]))
+    up = np.random.default_rng(6).normal(size=3 * 160 * 160)
+    a = gpu_run(b, p, upstream=up)
+    assert _choices(a["renderer"])[0] == lg, len(a["idx"])
+    c = gpu_run(b, p.replace(chunk=512), upstream=up)
+    assert _choices(c["renderer"]) == (9, 0)
+    np.testing.assert_array_equal(a["idx"], c["idx"])
+    assert np.abs(a["image"] - c["image"]).max() <= 2 * IMG_TOL      # each within IMG_TOL of the oracle's
+    assert all(np.isfinite(a["grads"][n]).all() for n in PARAM_NAMES)
+    assert grad_close(a["grads"], c["grads"], rtol=1e-4, atol=1e-6) <= 1.0
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("kind,n,size,h", [("stroke", 3, 64, 1.0), ("stroke", 32, 256, 1.0), ("fill", 60, 200, 4.0),
+                                           ("fill", 100, 512, 2.0), ("fill", 100, 512, 5.0), ("fill", 20, 512, 2.0)])
+def test_long_lists(kind, n, size, h, tile):
+    if kind == "stroke":
+        b = synth.config2(seed=7, n_curves=n, size=size)
+    else:
+        parts = synth.fills(8, n_paths=n, size=size, radius=(5.0 * size / 512, 80.0 * size / 512))
+        b = synth._assemble(parts, [[size, size]], [[1.0, 1.0, 1.0]], 3)
+    p = Params(tile=tile, h=h)
+    a = gpu_run(b, p, backward=False)
+    assert _choices(a["renderer"])[1] == _long(a["ranges"], tile)
+    c = gpu_run(b, p.replace(chunk=512), backward=False)
+    assert np.abs(a["image"] - c["image"]).max() <= 2 * IMG_TOL
+
+
+@pytest.mark.parametrize("count", [150, 560, 1700])
+@pytest.mark.parametrize("opacity", [(0.002, 0.004, 0.003), (0.02, 0.5, 0.1), (0.9, 0.9, 0.9)])
+def test_blocks_in_32x32_tiles(opacity, count):
+    b = _scene(count, opacity, seed=count + 32)
+    out = gpu_vs_oracle(b, _params(b, count, 32), np.random.default_rng(count).uniform(0.0, 1.0, 3 * 15 * 13))[0]
+    assert _choices(out["renderer"])[1] > 0
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("h", [0.4, 0.9, 2.0])
+@pytest.mark.parametrize("opacity", [0.02, 0.6])
+def test_blocks_with_fills_off_the_lattice(opacity, h, tile):
+    """Two filled paths, strokes between and over them."""
+    rng = np.random.default_rng(int(10 * h) + tile)
+    strokes = _scene(300, (0.5 * opacity, opacity), seed=int(100 * h))
+    parts = []
+    for k in range(2):
+        a = 2 * np.pi * np.arange(6) / 6
+        xy = np.stack([7.0 + k + 6.0 * np.cos(a), 7.0 - k + 6.0 * np.sin(a)], 1)
+        parts.append(dict(scene=0, degree=3, flags=3, key_xy=xy, key_w=np.ones(6), key_s=np.ones(6), tau=np.ones(6),
+                          color=rng.uniform(0, 1, 3), opacity=opacity))
+        parts.append(dict(scene=0, degree=3, flags=0, key_xy=strokes.key_xy[4 * k:4 * k + 4], key_w=np.ones(4),
+                          key_s=strokes.key_s[4 * k:4 * k + 4], tau=[1.0], color=rng.uniform(0, 1, 3),
+                          opacity=0.5 * opacity))
+    b = synth._assemble(parts, [[15, 13]], [[1.0, 1.0, 1.0]], 3)
+    p = Params(h=h, tile=tile, delta_c=9.0)
+    out = gpu_vs_oracle(b, p, rng.uniform(0.0, 1.0, 3 * 15 * 13))[0]
+    assert _choices(out["renderer"])[1] > 0

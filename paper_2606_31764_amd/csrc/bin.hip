@@ -548,26 +548,30 @@ __global__ __launch_bounds__(256) void k_order_count(const int32_t* __restrict__
   if (threadIdx.x < 32 && h[threadIdx.x] > 0) atomicAdd(&obin[threadIdx.x], h[threadIdx.x]);
 }
 
+// Whether lists are split: not at all, in a batch with fills, in another.
+constexpr int SPLIT_FILLS = 1, SPLIT_ANY = 2;
+
 // The number of long lists (Q_NLONG): those of the classes up to long_class's,
-// or, where that makes a launch of many lists about as long as each other, up to
-// the next class above.  A long list's block saves time while the launch waits for
-// it.  Where the blocks don't all start at once (a compute unit holds two or three)
-// and the longest list is below four times the bound, the launch waits for the sum
-// of its work instead, to which the blocks add (not where LONG_LEAST is the bound:
-// there the sum is small).  Forward with and without this:
-// 256 fill paths at 512^2 and h = 4 0.085 and 0.097 ms (0.083 on wavefronts alone),
-// in 8 x 8 tiles 0.077 and 0.111, 100 paths at h = 2 0.054 and 0.074, at h = 5
-// 0.037 and 0.049, 160 mixed curves at 512^2 and h = 2 0.139 and 0.166; one class
-// up for every launch costs 12 quintic strokes at 512^2 (longest list six times the
-// bound) 0.231 -> 0.311, one curve of 10,240 key points (35 long lists) 0.116 ->
-// 0.163.  Called by a wavefront; lane l < 32 holds the number n of lists of class l
-// and their running sum; blocks: per list.
-__device__ inline int n_long_lists(int n, int incl, int64_t pairs, int quads, int blocks, int n_cu) {
+// or, in a batch with fills whose lists are many and about as long as each other,
+// up to the next class above.  A list's block saves time while the launch waits for
+// it.  The forward with fills keeps four wavefronts per SIMD and two blocks per
+// compute unit: where the blocks don't all start at once and the longest list is
+// below four times the bound, the launch waits for the sum of its work instead, to
+// which the blocks add (not where LONG_LEAST is the bound: there the sum is small).
+// Forward with and without this: 256 fill paths at 512^2 and h = 4 0.085 and 0.097
+// ms (0.083 on wavefronts alone), in 8 x 8 tiles 0.077 and 0.111, 100 paths at
+// h = 2 0.054 and 0.074, at h = 5 0.037 and 0.049, 160 mixed curves at 512^2 and
+// h = 2 0.139 and 0.166.  Strokes alone leave wavefront slots empty, and lose by it
+// (12 quintic ones at 512^2 0.231 and 0.311, where the longest list happens to be
+// below the limit).  Called by a wavefront; lane l < 32 holds the number n of lists
+// of class l and their running sum; blocks: per list.
+__device__ inline int n_long_lists(int n, int incl, int64_t pairs, int quads, int blocks, int n_cu, int split) {
+  if (split == 0) return 0;
   const int lane = __lane_id(), c = long_class(pairs, quads, n_cu);
   const uint64_t some = __ballot(lane < 32 && n > 0);
   const int longest = some ? __builtin_ctzll(some) : 31;
   const int at = __shfl(incl, c), above = __shfl(incl, c > 0 ? c - 1 : 0);
-  const bool full = c < __builtin_clz(LONG_LEAST) && 2 * (int64_t)at * blocks > 5 * (int64_t)n_cu;
+  const bool full = split == SPLIT_FILLS && c < __builtin_clz(LONG_LEAST) && 2 * (int64_t)at * blocks > 5 * (int64_t)n_cu;
   return full && c - longest <= 1 ? above : at;
 }
 
@@ -582,8 +586,8 @@ __global__ void k_order_scan(int32_t* obin, int32_t* queue, const int32_t* count
     if (l >= off) incl += o;
   }
   if (l < 32) obin[32 + l] = incl - v;
-  const int n_long = n_long_lists(v, incl, counters[NSPLAT_CNT_PAIRS], quads, blocks, n_cu);
-  if (l == 0) queue[Q_NLONG] = split ? n_long : 0;
+  const int n_long = n_long_lists(v, incl, counters[NSPLAT_CNT_PAIRS], quads, blocks, n_cu, split);
+  if (l == 0) queue[Q_NLONG] = n_long;
 }
 
 __global__ __launch_bounds__(256) void k_order_scatter(const int32_t* __restrict__ ranges, int n_tiles,
@@ -705,8 +709,8 @@ __global__ __launch_bounds__(PLAN_THREADS) void k_tile_plan(int32_t* __restrict_
       base[tid] = incl - v;
       h[tid] = 0;
     }
-    const int n_long = n_long_lists(v, incl, counters[NSPLAT_CNT_PAIRS], quads, blocks, n_cu);
-    if (tid == 0) queue[Q_NLONG] = split ? n_long : 0;
+    const int n_long = n_long_lists(v, incl, counters[NSPLAT_CNT_PAIRS], quads, blocks, n_cu, split);
+    if (tid == 0) queue[Q_NLONG] = n_long;
   }
   __syncthreads();
   for (int t = tid; t < n_tiles; t += PLAN_THREADS) {
@@ -772,7 +776,7 @@ hipError_t launch_bin(const Launch& L) {
   int32_t* cnt = L.bf->counters;
   const Gauss* gs = (const Gauss*)L.bf->gauss;
   const int gg = grid_for(gcap, 256, 8192);
-  const int split = split_long(*L.pr);
+  const int split = !split_long(*L.pr) ? 0 : ((L.cv->any_flags & NSPLAT_FILLED) ? SPLIT_FILLS : SPLIT_ANY);
   const ChunkArg ca = {L.ck_lg, L.pr->h, L.pr->h_dev};
   // number of key bits and radix passes (up to RADIX_BITS_MAX bits each)
   int key_bits = 0;

@@ -37,16 +37,16 @@ def _cu():
     return torch.cuda.get_device_properties(0).multi_processor_count
 
 
-def _long(ranges, tile):
+def _long(ranges, tile, fills):
     """The number of long lists by the rule: a power-of-two bound of the share of a
-    compute unit's ninth, at least 128, one up where the blocks are many and the
-    lists alike."""
+    compute unit's ninth, at least 128, with fills one up where the blocks are many
+    and the lists alike."""
     n = ranges[:, 1] - ranges[:, 0]
     quads, blocks = (1 if tile == 8 else 4), (tile // 8) ** 2
     share = int(n.sum()) * quads // (9 * _cu())
     bound = 1 << (max(share, 128).bit_length() - 1)
     count = int((n >= bound).sum())
-    if bound > 128 and 2 * count * blocks > 5 * _cu() and n.max() < 4 * bound:
+    if fills and bound > 128 and 2 * count * blocks > 5 * _cu() and n.max() < 4 * bound:
         return int((n >= 2 * bound).sum())
     return count
 
@@ -73,17 +73,21 @@ def test_chosen_chunk(lg, tile):
 
 
 @pytest.mark.parametrize("tile", [8, 16, 32])
-@pytest.mark.parametrize("kind,n,size,h", [("stroke", 3, 64, 1.0), ("stroke", 32, 256, 1.0), ("fill", 60, 200, 4.0),
+@pytest.mark.parametrize("kind,n,size,h", [("stroke", 3, 64, 1.0), ("stroke", 32, 256, 1.0), ("wide", 8, 512, 1.0),
+                                           ("fill", 60, 200, 4.0),
                                            ("fill", 100, 512, 2.0), ("fill", 100, 512, 5.0), ("fill", 20, 512, 2.0)])
 def test_long_lists(kind, n, size, h, tile):
-    if kind == "stroke":
+    if kind == "wide":
+        b = synth._assemble(synth.strokes(3, n_curves=n, size=size, nk_range=(26, 26), step=16.0, width=(4.0, 16.0),
+                                          degree=5), [[size, size]], [[1.0, 1.0, 1.0]], 3)
+    elif kind == "stroke":
         b = synth.config2(seed=7, n_curves=n, size=size)
     else:
         parts = synth.fills(8, n_paths=n, size=size, radius=(5.0 * size / 512, 80.0 * size / 512))
         b = synth._assemble(parts, [[size, size]], [[1.0, 1.0, 1.0]], 3)
     p = Params(tile=tile, h=h)
     a = gpu_run(b, p, backward=False)
-    assert _choices(a["renderer"])[1] == _long(a["ranges"], tile)
+    assert _choices(a["renderer"])[1] == _long(a["ranges"], tile, kind == "fill")
     c = gpu_run(b, p.replace(chunk=512), backward=False)
     assert np.abs(a["image"] - c["image"]).max() <= 2 * IMG_TOL
 

@@ -1503,12 +1503,13 @@ __global__ __launch_bounds__(BLOCK, bwd_waves(E, KIND)) void k_blend_bwd(
   const const_i32 item_off = (const_i32)w.item_off;  // not written during the kernel: scalar loads
   const int n_items = item_off[n_tiles];
   // All wavefronts take their items from one address, which gives one every 12 ns:
-  // with 32 items or more per wavefront slot (16 slots per compute unit: pop_from)
+  // with 24 items or more per wavefront slot (16 slots per compute unit: pop_from)
   // that is what the launch waits for, and they take four at a time (with fewer,
   // four long ones in one wavefront would be waited for).  16 mixed scenes at 768^2
-  // in 32 x 32 tiles, chunks of 512: 2.40 ms one by one, 1.26 by fours (1.76 in the
-  // quadrants of 16 x 16 pixels, a quarter of the items); chunks of 4096: 1.09, 1.30;
-  // 64 scenes, the whole step: 11.45, 10.0, in 16 x 16 tiles 11.05, 9.9.
+  // in 32 x 32 tiles, one by one and by fours: chunks of 512 (196,000 items) 2.40 and
+  // 1.22 ms (1.76 in the quadrants of 16 x 16 pixels, a quarter of the items), of
+  // 1024 (113,000) 1.49 and 1.20, of 2048 (75,000) 1.17 and 1.18, of 4096 (58,000)
+  // 1.09 and 1.30; 16 x 2000 key points at 1024^2 (120,000) 1.54 and 0.79.
   const int pop = persistent && n_items >= pop_from ? 4 : 1;
   int item = 0, left = 0;  // items of the last pop still to take
   for (int it = 0;; ++it) {
@@ -2072,7 +2073,7 @@ hipError_t bwd_t(const Launch& L, const float* dL, const float* T_final, const i
   Phase ph(L, NSPLAT_T_BLEND_BWD);
   hipLaunchKernelGGL((k_blend_bwd<C, TILE, E, KIND>), dim3((int)grid), dim3(BLOCK), lds, L.stream, *L.cv, *L.pr, L.w,
                      L.sc->n_scenes, (int)L.n_tiles, (const Gauss*)L.bf->gauss, L.bf->ranges, L.bf->idx, L.sc->bg,
-                     dL, T_final, n_last, L.bf->plan, (int64_t)L.bf->caps.gauss, persistent, 32 * 16 * L.n_cu, L.ck_lg);
+                     dL, T_final, n_last, L.bf->plan, (int64_t)L.bf->caps.gauss, persistent, 24 * 16 * L.n_cu, L.ck_lg);
   return hipGetLastError();
 }
 

@@ -87,16 +87,19 @@ __host__ __device__ inline int n_chunks(int len, int ck_lg) { return (len + (1 <
 // With fills: pairs x quadrants / (8 x compute units) list positions, about one
 // adjoint item per two wavefront slots of the GPU.  Fill runs at h = 1 (runs)
 // are walked whole, and each chunk boundary in one costs a walk more, so that
-// longer chunks would be faster still (100 paths at 512^2 in 32 x 32 tiles,
-// forward and adjoint, at chunks of 512, 1024, 2048, 4096: 0.386, 0.342, 0.289,
-// 0.263 ms; the rule takes 1024), but the adjoint divides T back over a chunk
-// and loses precision with its length.  Entries taken one by one (strokes, more
-// than an eighth of the fill Gaussians, or fills at another h) take an adjoint
-// wavefront ten times as long per position, so that the longest chunk sets the
-// length of the pass: a quarter.  Adjoint at chunks of 512, 1024, 2048, 4096,
-// 8192: 16 mixed scenes at 768^2 in 32 x 32 tiles 1.66, 1.32, 1.26, 1.41, 1.46
-// ms (8192 without the quarter), 4 at 512^2 0.32, 0.44, 0.66, 0.96, 1.11 (1024),
-// 8 at 768^2 1.22, 0.92, 0.90, 1.07, 1.05 (4096).
+// longer chunks would be faster still, but the adjoint divides T back over a chunk
+// and loses precision with its length.  100 paths at 512^2 in 32 x 32 tiles at
+// chunks of 512, 1024, 2048, 4096: forward and adjoint 0.167, 0.132, 0.120, 0.112
+// ms, the key points' gradients off by 1.1, 1.2, 1.9, 4.1 e-7 (the rule takes 1024);
+// 256 paths in 16 x 16 tiles 0.239, 0.196, 0.179, 0.171 ms and 1.4, 4.6, 8.3, 14
+// e-7 (4096, as before the rule).  Entries taken one by one (strokes, more than an
+// eighth of the fill Gaussians, or fills at another h) take an adjoint wavefront
+// ten times as long per position, so that the longest chunk sets the length of the
+// pass: a quarter.  Adjoint at chunks of 512, 1024, 2048, 4096, 8192: 16 mixed
+// scenes at 768^2 in 32 x 32 tiles 1.22, 1.20, 1.17, 1.07, 1.03 ms (8192 without
+// the quarter, 2048 with it), when the rule was made 1.66, 1.32, 1.26, 1.41, 1.46;
+// 4 at 512^2 0.32, 0.44, 0.66, 0.96, 1.11 (1024), 8 at 768^2 1.22, 0.92, 0.90,
+// 1.07, 1.05 (4096).
 // Rounded to a power of two in [CK_MIN, CK_MAX].
 __host__ __device__ inline int auto_chunk_log2(int64_t pairs, int quads, int n_cu, bool runs) {
   double v = (double)pairs * quads / (8.0 * (n_cu > 0 ? n_cu : 1));

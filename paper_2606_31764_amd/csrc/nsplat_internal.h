@@ -93,13 +93,13 @@ __host__ __device__ inline int n_chunks(int len, int ck_lg) { return (len + (1 <
 // ms, the key points' gradients off by 1.1, 1.2, 1.9, 4.1 e-7 (the rule takes 1024);
 // 256 paths in 16 x 16 tiles 0.239, 0.196, 0.179, 0.171 ms and 1.4, 4.6, 8.3, 14
 // e-7 (4096, as before the rule).  Entries taken one by one (strokes, more than an
-// eighth of the fill Gaussians, or fills at another h) take an adjoint wavefront
-// ten times as long per position, so that the longest chunk sets the length of the
-// pass: a quarter.  Adjoint at chunks of 512, 1024, 2048, 4096, 8192: 16 mixed
-// scenes at 768^2 in 32 x 32 tiles 1.22, 1.20, 1.17, 1.07, 1.03 ms (8192 without
-// the quarter, 2048 with it), when the rule was made 1.66, 1.32, 1.26, 1.41, 1.46;
-// 4 at 512^2 0.32, 0.44, 0.66, 0.96, 1.11 (1024), 8 at 768^2 1.22, 0.92, 0.90,
-// 1.07, 1.05 (4096).
+// eighth of the fill Gaussians, or fills at another h): a quarter.  That is for the
+// precision (256 paths at 512^2 and h = 4 off by 1.5e-6 with it, 2.9e-6 without);
+// the quarter was also the faster choice while a 32 x 32 tile had four quadrants,
+// but since its 8 x 8 blocks share the work the longer chunks are: adjoint at 512,
+// 1024, 2048, 4096, 8192, in 32 x 32 tiles with a work queue, 16 mixed scenes at
+// 768^2 1.23, 1.20, 1.17, 1.08, 1.05 ms (the rule takes 2048), 8 at 768^2 0.68,
+// 0.84, 0.60, 0.53, 0.52 (2048), 4 at 512^2 0.31, 0.25, 0.27, 0.31, 0.34 (512).
 // Rounded to a power of two in [CK_MIN, CK_MAX].
 __host__ __device__ inline int auto_chunk_log2(int64_t pairs, int quads, int n_cu, bool runs) {
   double v = (double)pairs * quads / (8.0 * (n_cu > 0 ? n_cu : 1));

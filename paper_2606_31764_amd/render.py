@@ -272,8 +272,9 @@ class Renderer:
         the counters, made between binning and the forward, while the forward
         runs (an overflow leaves every step safe to run, and its results are
         thrown away); waiting after each of the first two steps left the GPU
-        idle twice: one open cubic at 64^2 under autograd 0.45 -> 0.28 ms a
-        step, 16 closed ones at 512^2 0.44 -> 0.40."""
+        idle twice.  A step under autograd, both ways in turn in one process:
+        one open cubic at 64^2 0.47 -> 0.365 ms, 16 closed ones at 512^2 0.47 ->
+        0.39 (0.36 -> 0.30 in another process: the host's part varies so much)."""
         for _ in range(4):
             self.sample(tensors, frozen=frozen, sync=False, params=params)
             self.bin(tensors, sync=False, params=params)
